@@ -37,6 +37,7 @@ struct grmhd_batch {
   bool electrons = false;          // some active job has entropies
   int totals[PH_COUNT] = {0};
   int nactive = 0;
+  int axi = 1;                     // no active job has Cartesian Kerr-Schild coordinates
   int stx = TILE_X, sty = SWEEP_TILE_Y, utx = TILE_X, uty = TILE_Y;  // tiles of every job
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -70,7 +71,7 @@ void drop_graph(grmhd_batch* b) {
 // enqueue one step of every job in the current job table (events around the
 // launches only when profiling, which never happens under capture)
 hipError_t enqueue_step(grmhd_batch* b) {
-  const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->stx, b->sty, b->utx, b->uty};
+  const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->stx, b->sty, b->utx, b->uty, b->axi};
   hipStream_t s = b->stream;
   hipError_t e;
   if ((e = launch_batch_reset(bv, 8, s)) != hipSuccess) return e;
@@ -117,6 +118,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
   std::vector<JobDesc> jobs;
   std::vector<int> counts;  // [job][phase]
   bool electrons = false;
+  int axi = 1;
   for (int j = 0; j < n; ++j) {
     if (active && !active[j]) continue;
     if (!P[j]) return bfail(b, GRMHD_EINVAL, "batch_step: NULL state for an active job");
@@ -136,6 +138,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
     JobDesc jd;
     std::memset(&jd, 0, sizeof(jd));
     jd.p = c->p;
+    if (c->p.coords == GRMHD_KERR_CKS) axi = 0;
     jd.d = c->d;
     jd.d.stx = b->stx;
     jd.d.sty = b->sty;
@@ -193,6 +196,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
         b->cur_fel[j] = fel[j];
       }
   b->electrons = electrons;
+  b->axi = axi;
   if (na == 0) return GRMHD_OK;
   // on the batch's stream, which may be a non-blocking one: a copy on the
   // null stream is not ordered before the graph launched on it, and a copy

@@ -67,14 +67,35 @@ __device__ inline void cks_point_geo(double x, double y, double z, double a, Geo
   g.alpha = (T)(1.0 / sqrt(1.0 + f));
 }
 
-// at the lower D-face (D = 1..3) of cell (i, j, k)
-template <typename T>
-__device__ inline void cks_face_geo(const CksBox& b, int D, int i, int j, int k, Geo<T>& g) {
+// at the lower D-face (D = 1..3) of cell (i, j, k), in the 3+1 form of the face
+// tables: g_ij = delta_ij + f l_i l_j, alpha^2 = 1/(1 + f), beta^i = alpha^2 f
+// l_i, gamma^ij = delta_ij - alpha^2 f l_i l_j
+__device__ inline void cks_face_geo(const CksBox& b, int D, int i, int j, int k, FaceGeo<double>& g) {
 #pragma clang fp contract(off)
   const double x = b.x0[0] + (D == 1 ? (double)i : i + 0.5) * b.dx[0];
   const double y = b.x0[1] + (D == 2 ? (double)j : j + 0.5) * b.dx[1];
   const double z = b.x0[2] + (D == 3 ? (double)k : k + 0.5) * b.dx[2];
-  cks_point_geo(x, y, z, b.a, g);
+  const double a = b.a;
+  const double r = cks_radius(x, y, z, a);
+  const double r2 = r * r;
+  const double f = 2.0 * r2 * r / (r2 * r2 + a * a * z * z);
+  const double ira = 1.0 / (r2 + a * a);
+  const double l1 = (r * x + a * y) * ira, l2 = (r * y - a * x) * ira, l3 = z / r;
+  const double f1 = f * l1, f2 = f * l2, f3 = f * l3;
+  const double ia = sqrt(1.0 + f), al = 1.0 / ia, a2 = al * al;
+  g.g11 = f1 * l1 + 1.0;
+  g.g12 = f1 * l2;
+  g.g13 = f1 * l3;
+  g.g22 = f2 * l2 + 1.0;
+  g.g23 = f2 * l3;
+  g.g33 = f3 * l3 + 1.0;
+  g.alpha = al;
+  g.ialpha = ia;
+  g.b1 = a2 * f1;
+  g.b2 = a2 * f2;
+  g.b3 = a2 * f3;
+  g.H = a2 * (1.0 - (D == 1 ? g.b1 * l1 : D == 2 ? g.b2 * l2 : g.b3 * l3));
+  g.hgdet = 0.5;
 }
 
 // at the centre of cell (i, j, k)

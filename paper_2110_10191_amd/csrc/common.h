@@ -25,11 +25,23 @@ enum {
   T_GCON = 10,    // 10: g^mn, same order
   T_GDET = 20,
   T_ALPHA = 21,
-  N_FACE = 22,
   T_CONN = 22,    // 40: Gamma^l_mn, l-major, (m,n) in the symmetric order
   T_RHOFL = 62,   // rho_fl * k        (k = 1/(r^2 (1 + r/10)))
   T_UFL = 63,     // u_fl * k^gamma
   N_CENT = 64
+};
+
+// face table components: the 3+1 form of the metric the face states are
+// written in. g_ij is the spatial metric, beta^i = alpha^2 g^ti the shift,
+// H = alpha^2 gamma^DD with gamma^ij the inverse of g_ij and D the face's
+// direction. MKS, FMKS and Minkowski have g_23 = beta^3 = 0 identically
+// (Kerr-Schild: g_theta phi = 0, g^t phi = 0), so their passes read the first
+// F_AXI components only.
+enum {
+  F_G11 = 0, F_G12, F_G13, F_G22, F_G33, F_ALPHA,
+  F_B1, F_B2, F_IALPHA, F_H, F_HGDET,  // 1/alpha, H, sqrt(-g)/2
+  F_B3, F_AXI = F_B3 + 1, F_G23 = F_AXI, F_USED = F_G23 + 2,  // a pair is read at a time
+  N_FACE = 22  // components a face table has room for
 };
 
 __host__ __device__ constexpr int sidx(int m, int n) {
@@ -110,28 +122,34 @@ __device__ inline void load_geo(Geo<T>& g, const S* __restrict__ tab, int ts, in
   g.alpha = (T)ldu(tab + (size_t)T_ALPHA * ts, bo);
 }
 
-// the same from a face table (paired components; off as above, tab the plane
-// from face_plane)
-template <typename T, typename S>
-__device__ inline void load_face_geo(Geo<T>& g, const S* __restrict__ tab, int ts, int off) {
+// geometry of one face
+template <typename T>
+struct FaceGeo {
+  T g11, g12, g13, g22, g23, g33;  // g_ij
+  T b1, b2, b3;                    // beta^i
+  T alpha, ialpha, H, hgdet;
+};
+
+// from a face table (paired components; off as above, tab the plane from
+// face_plane); AXI: the coordinates have g_23 = beta^3 = 0
+template <bool AXI, typename T, typename S>
+__device__ inline void load_face_geo(FaceGeo<T>& g, const S* __restrict__ tab, int ts, int off) {
   using P2 = typename pair_of<S>::type;
   const unsigned bo = (unsigned)off * (unsigned)(2 * sizeof(S));
   auto ld = [&](int c0) -> P2 { return *(const P2*)((const char*)(tab + (size_t)c0 * ts) + bo); };
-#pragma unroll
-  for (int c = 0; c < 10; c += 2) {
-    const P2 v = ld(T_GCOV + c);
-    g.gcov[c] = (T)v.x;
-    g.gcov[c + 1] = (T)v.y;
+  const P2 a = ld(F_G11), b = ld(F_G13), c = ld(F_G33), d = ld(F_B1), e = ld(F_IALPHA), f = ld(F_HGDET);
+  g.g11 = (T)a.x, g.g12 = (T)a.y;
+  g.g13 = (T)b.x, g.g22 = (T)b.y;
+  g.g33 = (T)c.x, g.alpha = (T)c.y;
+  g.b1 = (T)d.x, g.b2 = (T)d.y;
+  g.ialpha = (T)e.x, g.H = (T)e.y;
+  g.hgdet = (T)f.x;
+  g.b3 = T(0);
+  g.g23 = T(0);
+  if constexpr (!AXI) {
+    g.b3 = (T)f.y;
+    g.g23 = (T)ld(F_G23).x;
   }
-#pragma unroll
-  for (int c = 0; c < 10; c += 2) {
-    const P2 v = ld(T_GCON + c);
-    g.gcon[c] = (T)v.x;
-    g.gcon[c + 1] = (T)v.y;
-  }
-  const P2 v = ld(T_GDET);
-  g.gdet = (T)v.x;
-  g.alpha = (T)v.y;
 }
 
 // ---------------------------------------------------------------------------
@@ -156,26 +174,44 @@ __device__ inline T lorentz_sq(const T* gcov, T v1, T v2, T v3) {
          T(2) * (gcov[5] * v1 * v2 + gcov[6] * v1 * v3 + gcov[8] * v2 * v3);
 }
 
-// 1/sqrt(x) to full precision: the hardware estimate, then Newton steps
+// 1/sqrt(x), 1/x and sqrt(x) to within about one unit in the last place,
+// without the scaling and fix-up steps of the IEEE sequences: the hardware
+// estimate r (FP64: 2^-24 or better) and one correction of third order in its
+// residual e, r (1 + e/2 + 3/8 e^2) and r (1 + e + e^2). x must be a normal
+// number away from the ends of the range.
 __device__ inline double rsqrt_full(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  r = r * (1.5 - 0.5 * x * r * r);
-  return r * (1.5 - 0.5 * x * r * r);
+  const double r = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * r), r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
 }
 __device__ inline float rsqrt_full(float x) {
   const float r = __builtin_amdgcn_rsqf(x);
   return r * (1.5f - 0.5f * x * r * r);
 }
+__device__ inline double rcp_full(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+__device__ inline float rcp_full(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+// x >= 0; 0 below the smallest argument the estimate is taken at
+__device__ inline double sqrt_full(double x) {
+  const double y = __builtin_amdgcn_rsq(fmax(x, 1e-290));
+  const double g = x * y, h = 0.5 * y;
+  const double e = fma(-g, h, 0.5);
+  const double g1 = fma(g, e, g), h1 = fma(h, e, h);
+  return fma(fma(-g1, g1, x), h1, g1);
+}
+__device__ inline float sqrt_full(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// the fluid four-vectors of primitives P. RSQ: Gamma and 1/u^t from one
-// reciprocal square root (Gamma = G2 / sqrt(G2), 1/u^t = alpha / Gamma) instead
-// of a square root and a division (the face-flux pass, where it is faster;
-// the update keeps the plain form, whose register allocation it suits)
-template <typename T, bool RSQ = false>
+// the fluid four-vectors of primitives P
+template <typename T>
 __device__ inline void fluid_state(const T* P, const Geo<T>& g, T gam, Fluid<T>& f) {
   const T l2 = lorentz_sq(g.gcov, P[2], P[3], P[4]);
-  const T rl = RSQ ? rsqrt_full(l2) : T(0);
-  const T lor = RSQ ? l2 * rl : sqrt(l2);
+  const T lor = sqrt(l2);
   f.ucon[0] = lor / g.alpha;
   const T la = lor * g.alpha;
   f.ucon[1] = P[2] - la * g.gcon[1];
@@ -184,7 +220,7 @@ __device__ inline void fluid_state(const T* P, const Geo<T>& g, T gam, Fluid<T>&
 #pragma unroll
   for (int m = 0; m < 4; ++m) f.ucov[m] = lower(g.gcov, f.ucon, m);
   const T bt = P[5] * f.ucov[1] + P[6] * f.ucov[2] + P[7] * f.ucov[3];
-  const T iut = RSQ ? g.alpha * rl : T(1) / f.ucon[0];
+  const T iut = T(1) / f.ucon[0];
   f.bcon[0] = bt;
   f.bcon[1] = (P[5] + bt * f.ucon[1]) * iut;
   f.bcon[2] = (P[6] + bt * f.ucon[2]) * iut;
@@ -221,24 +257,104 @@ __device__ inline void flux_of(const T* P, const Fluid<T>& f, T gdet, T* F) {
   }
 }
 
-// Fast-magnetosonic speeds dx^D/dt: roots of A l^2 + B l + C = 0 with
-// c^2 = v_A^2 + c_s^2 (1 - v_A^2), v_A^2 = b^2/(b^2 + w), c_s^2 = gamma p / w,
-// which is the single quotient num/den = (b^2 + gamma p)/(b^2 + w); A, B and C
-// are taken times den > 0, which leaves the roots unchanged and saves the
-// division.
-template <int D, typename T>
-__device__ inline void signal_speeds(const Fluid<T>& f, const Geo<T>& g, T gam, T& cmax, T& cmin) {
-  const T num = f.bsq + gam * f.p, den = f.bsq + f.w;
-  const T ut = f.ucon[0], ud = f.ucon[D];
-  const T A = den * ut * ut - num * (g.gcon[0] + ut * ut);
-  const T B = T(-2) * (den * ut * ud - num * (g.gcon[D] + ut * ud));
-  const T C = den * ud * ud - num * (g.gcon[sidx(D, D)] + ud * ud);
-  const T disc = sqrt(fmax(B * B - T(4) * A * C, T(0)));
-  const T i2a = T(1) / (T(2) * A);
-  const T vp = (-B + disc) * i2a;
-  const T vm = (-B - disc) * i2a;
-  cmax = fmax(vp, vm);
-  cmin = fmin(vp, vm);
+// One side of a face of direction D (1..3): flux and conserved variables
+// divided by sqrt(-g) (hydrodynamic part, then the two field components the
+// flux has) and the fast-magnetosonic speeds, from primitives P.
+//
+// Written in the 3+1 form, which needs the spatial metric, shift and lapse
+// only and no index gymnastics with the four-metric:
+//   u_i = g_ij u~^j, Gamma^2 = 1 + u~^i u_i, u^t = Gamma/alpha, 1/u^t = alpha/Gamma,
+//   u_t = beta^i u_i - alpha Gamma, v^i = u^i/u^t = u~^i/u^t - beta^i,
+//   B_mu = g_mu i B^i, B_t = beta^i B_i, b^t = B^i u_i,
+//   b^i = B^i/u^t + b^t v^i, b_mu = (B_mu + b^t u_mu)/u^t, b^2 = (B^2 + (b^t)^2)/(u^t)^2,
+//   T^D_mu - p_tot delta = ((w + b^2) u^D - b^t b^D/u^t) u_mu - (b^D/u^t) B_mu,
+//   field flux of B^i: B^i v^D - B^D v^i.
+// Speeds: c^2 = num/den with num = b^2 + gamma p, den = b^2 + w (v_A^2 +
+// c_s^2 (1 - v_A^2) as one quotient). With m = den - num = rho + gamma (2 -
+// gamma) u, q = num/Gamma^2 and y = u~^D/u^t the two roots of the dispersion
+// relation are
+//   (m y +- sqrt(q ((m + q) H - m y^2)))/(m + q) - beta^D,
+// with no cancelling products.
+template <typename T>
+struct FaceSide {
+  T F[7], U[7];  // mass, energy, 3 momenta, then B of the two transverse directions (ascending)
+  T cp, cm;
+};
+
+template <int D, bool AXI, typename T>
+__device__ inline void face_side(const T* P, const FaceGeo<T>& g, T gam, FaceSide<T>& s) {
+#pragma clang fp contract(on)
+  const T v1 = P[2], v2 = P[3], v3 = P[4], B1 = P[5], B2 = P[6], B3 = P[7];
+  T ul1 = g.g11 * v1 + g.g12 * v2 + g.g13 * v3;
+  T ul2 = g.g12 * v1 + g.g22 * v2;
+  T ul3 = g.g13 * v1 + g.g33 * v3;
+  T Bl1 = g.g11 * B1 + g.g12 * B2 + g.g13 * B3;
+  T Bl2 = g.g12 * B1 + g.g22 * B2;
+  T Bl3 = g.g13 * B1 + g.g33 * B3;
+  if constexpr (!AXI) {
+    ul2 = ul2 + g.g23 * v3;
+    ul3 = ul3 + g.g23 * v2;
+    Bl2 = Bl2 + g.g23 * B3;
+    Bl3 = Bl3 + g.g23 * B2;
+  }
+  const T l2 = v1 * ul1 + v2 * ul2 + v3 * ul3 + T(1);
+  const T rl = rsqrt_full(l2);
+  const T lor = l2 * rl, ut = lor * g.ialpha, iut = g.alpha * rl;
+  T ult = g.b1 * ul1 + g.b2 * ul2 - g.alpha * lor;
+  T Blt = g.b1 * Bl1 + g.b2 * Bl2;
+  if constexpr (!AXI) {
+    ult = ult + g.b3 * ul3;
+    Blt = Blt + g.b3 * Bl3;
+  }
+  const T bt = B1 * ul1 + B2 * ul2 + B3 * ul3;
+  const T Bsq = B1 * Bl1 + B2 * Bl2 + B3 * Bl3;
+  const T bsq = (Bsq + bt * bt) * (iut * iut);
+  const T y = (D == 1 ? v1 : D == 2 ? v2 : v3) * iut;
+  const T bD = D == 1 ? g.b1 : D == 2 ? g.b2 : g.b3;
+  const T vD = (D == 3 && AXI) ? y : y - bD;
+  const T BD = D == 1 ? B1 : D == 2 ? B2 : B3;
+  const T gp = gam * (gam - T(1));
+  const T wb = P[0] + gam * P[1] + bsq;
+  const T pt = (gam - T(1)) * P[1] + T(0.5) * bsq;
+  const T rt = P[0] * ut;
+  // flux
+  const T c = (BD * iut + bt * vD) * iut;
+  const T a = wb * (ut * vD) - c * bt;
+  s.F[0] = rt * vD;
+  s.F[1] = a * ult - c * Blt + s.F[0];
+  s.F[2] = a * ul1 - c * Bl1;
+  s.F[3] = a * ul2 - c * Bl2;
+  s.F[4] = a * ul3 - c * Bl3;
+  s.F[1 + D] = s.F[1 + D] + pt;
+  const T Ba = D == 1 ? B2 : B1, Bb = D == 3 ? B2 : B3;
+  const T va = (D == 1 ? v2 : v1) * iut - (D == 1 ? g.b2 : g.b1);
+  T vb = (D == 3 ? v2 : v3) * iut;
+  if constexpr (D == 3) vb = vb - g.b2;
+  else if constexpr (!AXI) vb = vb - g.b3;
+  s.F[5] = Ba * vD - BD * va;
+  s.F[6] = Bb * vD - BD * vb;
+  // conserved variables
+  const T c0 = bt * iut;
+  const T a0 = wb * ut - c0 * bt;
+  s.U[0] = rt;
+  s.U[1] = a0 * ult - c0 * Blt + pt + rt;
+  s.U[2] = a0 * ul1 - c0 * Bl1;
+  s.U[3] = a0 * ul2 - c0 * Bl2;
+  s.U[4] = a0 * ul3 - c0 * Bl3;
+  s.U[5] = Ba;
+  s.U[6] = Bb;
+  // speeds
+  const T num = gp * P[1] + bsq;
+  const T m = P[0] + (gam - gp) * P[1];
+  const T q = num * (rl * rl);
+  const T A = m + q;
+  const T my = m * y;
+  const T disc = q * (A * g.H - my * y);
+  const T iA = rcp_full(A);
+  const T r = fabs(sqrt_full(fmax(disc, T(0))) * iA);
+  const T mid = (D == 3 && AXI) ? my * iA : my * iA - bD;
+  s.cp = mid + r;
+  s.cm = mid - r;
 }
 
 // ---------------------------------------------------------------------------

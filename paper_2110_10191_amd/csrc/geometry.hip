@@ -136,50 +136,71 @@ __device__ double invert4(const double m[4][4], double b[4][4]) {
   return det;
 }
 
-// write metric, inverse (upper triangle), sqrt(-g) and lapse of one point:
-// into the centre table (dt, one plane per component; ft null) or into a face
-// table and its float copy (paired components)
-__device__ void store_point(double x1, double x2, double x3, const grmhd_problem& p, double* dt, float* ft,
-                            size_t ts, int off, double gcon_out[4][4]) {
+// write metric, inverse (upper triangle), sqrt(-g) and lapse of one point
+// into the centre table
+__device__ void store_point(double x1, double x2, double x3, const grmhd_problem& p, double* dt, size_t ts, int off,
+                            double gcon_out[4][4]) {
   double g[4][4], gi[4][4];
   gcov_code(x1, x2, x3, p, g);
   const double det = invert4(g, gi);
-  auto at = [&](int c) -> size_t { return ft ? pair_index(c, ts, (size_t)off) : (size_t)c * ts + (size_t)off; };
+  auto at = [&](int c) -> size_t { return (size_t)c * ts + (size_t)off; };
   for (int m = 0; m < 4; ++m)
     for (int n = m; n < 4; ++n) {
       const int c = sidx(m, n);
       dt[at(T_GCOV + c)] = g[m][n];
       dt[at(T_GCON + c)] = gi[m][n];
-      if (ft) {
-        ft[at(T_GCOV + c)] = (float)g[m][n];
-        ft[at(T_GCON + c)] = (float)gi[m][n];
-      }
     }
-  const double gdet = sqrt(fabs(det));
-  const double alpha = 1.0 / sqrt(-gi[0][0]);
-  dt[at(T_GDET)] = gdet;
-  dt[at(T_ALPHA)] = alpha;
-  if (ft) {
-    ft[at(T_GDET)] = (float)gdet;
-    ft[at(T_ALPHA)] = (float)alpha;
-  }
-  if (gcon_out)
-    for (int m = 0; m < 4; ++m)
-      for (int n = 0; n < 4; ++n) gcon_out[m][n] = gi[m][n];
+  dt[at(T_GDET)] = sqrt(fabs(det));
+  dt[at(T_ALPHA)] = 1.0 / sqrt(-gi[0][0]);
+  for (int m = 0; m < 4; ++m)
+    for (int n = 0; n < 4; ++n) gcon_out[m][n] = gi[m][n];
+}
+
+// the 3+1 quantities of a face of direction D in MKS, FMKS or Minkowski
+// coordinates, whose g_23 and beta^3 vanish identically
+__device__ void face_point(double x1, double x2, double x3, int D, const grmhd_problem& p, FaceGeo<double>& f) {
+  double g[4][4], gi[4][4];
+  gcov_code(x1, x2, x3, p, g);
+  const double det = invert4(g, gi);
+  const double a2 = -1.0 / gi[0][0];
+  f.g11 = g[1][1];
+  f.g12 = g[1][2];
+  f.g13 = g[1][3];
+  f.g22 = g[2][2];
+  f.g23 = 0.0;
+  f.g33 = g[3][3];
+  f.alpha = sqrt(a2);
+  f.ialpha = sqrt(-gi[0][0]);
+  f.b1 = a2 * gi[0][1];
+  f.b2 = a2 * gi[0][2];
+  f.b3 = 0.0;
+  // gamma^DD by cofactors of g_ij
+  const double c11 = f.g22 * f.g33, c22 = f.g11 * f.g33 - f.g13 * f.g13, c33 = f.g11 * f.g22 - f.g12 * f.g12;
+  const double d3 = f.g33 * c33 - f.g13 * f.g13 * f.g22;
+  f.H = a2 * ((D == 1 ? c11 : D == 2 ? c22 : c33) / d3);
+  f.hgdet = 0.5 * sqrt(fabs(det));
 }
 
 // a face table entry (paired components) and its float copy
-__device__ void store_face(const Geo<double>& g, double* dt, float* ft, size_t ts, int off) {
-  for (int c = 0; c < 10; ++c) {
-    dt[pair_index(T_GCOV + c, ts, (size_t)off)] = g.gcov[c];
-    dt[pair_index(T_GCON + c, ts, (size_t)off)] = g.gcon[c];
-    ft[pair_index(T_GCOV + c, ts, (size_t)off)] = (float)g.gcov[c];
-    ft[pair_index(T_GCON + c, ts, (size_t)off)] = (float)g.gcon[c];
+__device__ void store_face(const FaceGeo<double>& g, double* dt, float* ft, size_t ts, int off) {
+  double v[F_USED] = {};
+  v[F_G11] = g.g11;
+  v[F_G12] = g.g12;
+  v[F_G13] = g.g13;
+  v[F_G22] = g.g22;
+  v[F_G33] = g.g33;
+  v[F_ALPHA] = g.alpha;
+  v[F_B1] = g.b1;
+  v[F_B2] = g.b2;
+  v[F_IALPHA] = g.ialpha;
+  v[F_H] = g.H;
+  v[F_HGDET] = g.hgdet;
+  v[F_B3] = g.b3;
+  v[F_G23] = g.g23;
+  for (int c = 0; c < F_USED; ++c) {
+    dt[pair_index(c, ts, (size_t)off)] = v[c];
+    ft[pair_index(c, ts, (size_t)off)] = (float)v[c];
   }
-  dt[pair_index(T_GDET, ts, (size_t)off)] = g.gdet;
-  dt[pair_index(T_ALPHA, ts, (size_t)off)] = g.alpha;
-  ft[pair_index(T_GDET, ts, (size_t)off)] = (float)g.gdet;
-  ft[pair_index(T_ALPHA, ts, (size_t)off)] = (float)g.alpha;
 }
 
 __global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t, CksBox box) {
@@ -211,26 +232,19 @@ __global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t, CksBox box) {
     for (int m = 0; m < 4; ++m)
       for (int n = 0; n < 4; ++n) gcon[m][n] = g.gcon[sidx(m, n)];
   } else {
-    store_point(x1c, x2c, x3c, p, t.cent, nullptr, ts, off, gcon);
+    store_point(x1c, x2c, x3c, p, t.cent, ts, off, gcon);
   }
-  if (k3) {
-    // Cartesian Kerr-Schild faces in closed form, the values the face-flux
-    // pass computes itself
-    // box: the zone corner and widths the face-flux pass uses (computed on the host)
-    const CksBox& b = box;
-    double* const dt[3] = {t.f1, t.f2, t.f3};
-    float* const ft[3] = {t.f1f, t.f2f, t.f3f};
-    for (int D = 1; D <= 3; ++D) {
-      Geo<double> g;
-      cks_face_geo(b, D, i, j, k, g);
-      store_face(g, dt[D - 1], ft[D - 1], ts, off);
-    }
-  } else {
-    store_point(x1f, x2c, x3c, p, t.f1, t.f1f, ts, off, nullptr);
-    store_point(x1c, x2f, x3c, p, t.f2, t.f2f, ts, off, nullptr);
-    // 2D tables: the metric does not depend on x3, and the x3-face table
-    // holds the centre values
-    store_point(x1c, x2c, x3c, p, t.f3, t.f3f, ts, off, nullptr);
+  // faces: Cartesian Kerr-Schild in closed form, the values the face-flux pass
+  // computes itself (box: the zone corner and widths it uses, computed on the
+  // host); the x3-face table of the 2D tables holds the centre values, the
+  // metric not depending on x3
+  double* const dt[3] = {t.f1, t.f2, t.f3};
+  float* const ft[3] = {t.f1f, t.f2f, t.f3f};
+  for (int D = 1; D <= 3; ++D) {
+    FaceGeo<double> g;
+    if (k3) cks_face_geo(box, D, i, j, k, g);
+    else face_point(D == 1 ? x1f : x1c, D == 2 ? x2f : x2c, x3c, D, p, g);
+    store_face(g, dt[D - 1], ft[D - 1], ts, off);
   }
 
   // connection: Gamma_kmn = (d_n g_km + d_m g_kn - d_k g_mn)/2, Gamma^l_mn = g^lk Gamma_kmn,

@@ -14,7 +14,7 @@
 // values, the metric not depending on x3).
 struct Tables {
   double* cent;   // centre table, N_CENT components
-  double* f1;     // x1-, x2-, x3-face tables, N_FACE components in pairs
+  double* f1;     // x1-, x2-, x3-face tables, room for N_FACE components in pairs (F_USED filled)
   double* f2;
   double* f3;
   float* f1f;     // float copies of the face tables (mixed precision)
@@ -76,6 +76,7 @@ struct BatchView {
   const int* offs;
   int njobs;
   int stx, sty, utx, uty;  // block tiles shared by every job of the batch
+  int axi;                 // every job's coordinates have g_23 = beta^3 = 0 (none is Cartesian Kerr-Schild)
 };
 
 // A pointer read from the device job table is a generic pointer to the
