@@ -106,6 +106,12 @@ int validate(const grmhd_problem* p, std::string& why) {
   return GRMHD_OK;
 }
 
+// the block shape of the face-flux pass from the tile asked for and the grid
+void pick_sweep_shape(Dims& d, const grmhd_problem& p) {
+  const bool mixed = p.precision == GRMHD_MIXED;
+  sweep_shape(d, p.recon, mixed, sweep_small(d, sweep_grid(d, large_bx(p.recon, mixed), large_by(p.recon, mixed))));
+}
+
 Dims make_dims(const grmhd_problem& p) {
   Dims d;
   d.n1 = p.n1;
@@ -124,6 +130,7 @@ Dims make_dims(const grmhd_problem& p) {
   d.utx = TILE_X;
   d.sty = SWEEP_TILE_Y;
   d.uty = TILE_Y;
+  pick_sweep_shape(d, p);
   d.out_lo = p.bc[0][0] == GRMHD_BC_OUTFLOW;
   d.out_hi = p.bc[0][1] == GRMHD_BC_OUTFLOW;
   return d;
@@ -131,7 +138,7 @@ Dims make_dims(const grmhd_problem& p) {
 
 void free_all(grmhd_ctx* c) {
   void* ptrs[] = {c->t.cent, c->t.f1, c->t.f2, c->t.f3, c->t.f1f, c->t.f2f, c->t.f3f,
-                  c->Ph, c->F[0], c->F[1], c->F[2], c->flags, c->ctr, c->Eh, c->Uk};
+                  c->Ph, c->F, c->flags, c->ctr, c->Eh, c->Uk};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
 }
@@ -183,20 +190,20 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
   }
   {
     ProfScope ps(c->prof, s, GRMHD_K_SWEEPS);
-    HIP_OR_FAIL(c, launch_sweeps(c->p, c->mixed, c->d, c->t, Ps, c->F, want_ctop ? c->ctr->ctop : nullptr,
-                                 s),
+    HIP_OR_FAIL(c, launch_sweeps(c->p, c->mixed, c->d, c->t, c->up, Ps, c->F, el != nullptr,
+                                 want_ctop ? c->ctr->ctop : nullptr, s),
                 "sweeps");
   }
   if (el) {
     // before the update: in the corrector it overwrites the base state in place
     ProfScope ps(c->prof, s, GRMHD_K_ELECTRONS);
-    HIP_OR_FAIL(c, launch_scalar_advect(c->mixed, c->p.recon, c->d, c->t, c->up, c->F[0], c->F[1], c->F[2], Pb,
+    HIP_OR_FAIL(c, launch_scalar_advect(c->mixed, c->p.recon, c->d, c->t, c->up, c->F, Pb,
                                         el->Eb, el->Es, c->Uk, dt, dt_dev, dt_scale, s),
                 "scalar advection");
   }
   {
     ProfScope ps(c->prof, s, GRMHD_K_UPDATE);
-    HIP_OR_FAIL(c, launch_update(c->mixed, c->d, c->t, c->up, c->F[0], c->F[1], c->F[2], Pb, Ps, Pout,
+    HIP_OR_FAIL(c, launch_update(c->mixed, c->d, c->t, c->up, c->F, Pb, Ps, Pout,
                                  fl, dt, dt_dev, dt_scale, c->ctr, s,
                                  c->p.coords == GRMHD_KERR_CKS ? &c->p : nullptr),
                 "update");
@@ -420,8 +427,7 @@ int grmhd_init(const grmhd_problem* p, void* hip_stream, grmhd_ctx** out) {
             dalloc(&c->t.f2f, N_FACE * ts * sizeof(float)) == hipSuccess &&
             dalloc(&c->t.f3f, N_FACE * ts * sizeof(float)) == hipSuccess &&
             dalloc(&c->Ph, NV * sv * sizeof(double)) == hipSuccess &&
-            dalloc(&c->F[0], NV * sv * fsz) == hipSuccess && dalloc(&c->F[1], NV * sv * fsz) == hipSuccess &&
-            dalloc(&c->F[2], NV * sv * fsz) == hipSuccess && dalloc(&c->flags, sv) == hipSuccess &&
+            dalloc(&c->F, 3 * NV * sv * fsz) == hipSuccess && dalloc(&c->flags, sv) == hipSuccess &&
             dalloc(&c->ctr, sizeof(Counters)) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -432,7 +438,7 @@ int grmhd_init(const grmhd_problem* p, void* hip_stream, grmhd_ctx** out) {
   // one-time clears (outside any captured work); padding stays finite
   hipError_t e = hipMemsetAsync(c->t.cent, 0, N_CENT * ts * sizeof(double), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->Ph, 0, NV * sv * sizeof(double), c->stream);
-  for (int q = 0; q < 3 && e == hipSuccess; ++q) e = hipMemsetAsync(c->F[q], 0, NV * sv * fsz, c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(c->F, 0, 3 * NV * sv * fsz, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->flags, 0, sv, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->ctr, 0, sizeof(Counters), c->stream);
   if (e == hipSuccess) e = launch_geometry(c->p, c->d, c->t, c->stream);
@@ -467,6 +473,7 @@ int grmhd_set_tiles(grmhd_ctx* ctx, int32_t which, int32_t tx, int32_t ty) {
   if (which == GRMHD_TILE_SWEEP) {
     ctx->d.stx = tx;
     ctx->d.sty = ty;
+    pick_sweep_shape(ctx->d, ctx->p);
   } else if (which == GRMHD_TILE_UPDATE) {
     ctx->d.utx = tx;
     ctx->d.uty = ty;
@@ -566,7 +573,7 @@ int grmhd_get_dt(grmhd_ctx* ctx, double* P, double* dt) {
   hipStream_t s = ctx->stream;
   HIP_OR_FAIL(ctx, launch_fill_ghosts(ctx->p, ctx->d, ctx->t, P, P, s), "ghost fill");
   HIP_OR_FAIL(ctx, launch_reset(ctx->ctr, 1, s), "reset");
-  HIP_OR_FAIL(ctx, launch_sweeps(ctx->p, ctx->mixed, ctx->d, ctx->t, P, ctx->F, ctx->ctr->ctop, s),
+  HIP_OR_FAIL(ctx, launch_sweeps(ctx->p, ctx->mixed, ctx->d, ctx->t, ctx->up, P, ctx->F, false, ctx->ctr->ctop, s),
               "sweeps");
   return read_dt(ctx, dt);
 }

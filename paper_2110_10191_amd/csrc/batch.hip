@@ -39,6 +39,7 @@ struct grmhd_batch {
   int nactive = 0;
   int axi = 1;                     // no active job has Cartesian Kerr-Schild coordinates
   int stx = TILE_X, sty = SWEEP_TILE_Y, utx = TILE_X, uty = TILE_Y;  // tiles of every job
+  int sbx = SMALL_BX, sby = SMALL_BY;  // block shape of the face-flux pass
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   Profiler prof;  // when on, steps run eagerly with each launch bracketed by events
@@ -71,7 +72,7 @@ void drop_graph(grmhd_batch* b) {
 // enqueue one step of every job in the current job table (events around the
 // launches only when profiling, which never happens under capture)
 hipError_t enqueue_step(grmhd_batch* b) {
-  const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->stx, b->sty, b->utx, b->uty, b->axi};
+  const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->sbx, b->sby, b->utx, b->uty, b->axi};
   hipStream_t s = b->stream;
   hipError_t e;
   if ((e = launch_batch_reset(bv, 8, s)) != hipSuccess) return e;
@@ -119,6 +120,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
   std::vector<int> counts;  // [job][phase]
   bool electrons = false;
   int axi = 1;
+  long long large = 0;  // blocks of the face-flux pass in its large shape, over all jobs
   for (int j = 0; j < n; ++j) {
     if (active && !active[j]) continue;
     if (!P[j]) return bfail(b, GRMHD_EINVAL, "batch_step: NULL state for an active job");
@@ -148,9 +150,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
     jd.up = c->up;
     jd.P = P[j];
     jd.Ph = c->Ph;
-    jd.F[0] = c->F[0];
-    jd.F[1] = c->F[1];
-    jd.F[2] = c->F[2];
+    jd.F = c->F;
     jd.flags = c->flags;
     jd.ctr = c->ctr;
     jd.dt = b->d_dt + j;
@@ -163,6 +163,12 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
       jd.fel = fel[j];
     }
     jobs.push_back(jd);
+    large += sweep_grid(jd.d, large_bx(b->recon, b->mixed), large_by(b->recon, b->mixed));
+  }
+  for (JobDesc& jd : jobs) {
+    sweep_shape(jd.d, b->recon, b->mixed, sweep_small(jd.d, large));
+    b->sbx = jd.d.sbx;
+    b->sby = jd.d.sby;
     int cnt[PH_COUNT];
     job_phase_blocks(jd.d, cnt);
     counts.insert(counts.end(), cnt, cnt + PH_COUNT);

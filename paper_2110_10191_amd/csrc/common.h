@@ -1,8 +1,8 @@
 // Shared device definitions of the GRMHD zone-update library (gfx950).
 //
 // Layout (see grmhd.h): a state is [8][n3+6][n2+6][n1p] float64, x1 fastest.
-// Face fluxes use the same layout: F_d at cell (k, j, i) is the flux through
-// the lower d-face of that cell. Geometry tables hold centre quantities
+// The results of the face-flux pass (FluxOut) use the same cells, a quantity
+// of a lower face or edge at the cell it belongs to. Geometry tables hold centre quantities
 // (metric, inverse, sqrt(-g), lapse, connection, floor scales) and face
 // quantities (metric, inverse, sqrt(-g), lapse) per direction. Axisymmetric
 // coordinates store them as 2D tables [component][n2+6][n1p] (k stride 0),
@@ -15,6 +15,12 @@
 #include <stdint.h>
 
 #include "grmhd.h"
+
+// Multiply-adds are fused where one expression spells them out, and nowhere
+// else: left to the back end ("fast", the default for HIP) the same function
+// could round differently in two kernels, and a batch would not repeat a
+// single context's bits.
+#pragma clang fp contract(on)
 
 #define NG GRMHD_NG
 #define NV GRMHD_NVAR
@@ -56,7 +62,8 @@ struct Dims {
   int sv;          // variable stride (= p3 * p2 * p1)
   int ts;          // table component stride (p2 * p1, or p3 * p2 * p1 for 3D tables)
   int tk;          // table k stride (0 for 2D tables, s3 for 3D)
-  int stx, sty;    // thread-block tile (x1 x x2) of the sweeps
+  int stx, sty;    // thread-block tile (x1 x x2) asked for the sweeps
+  int sbx, sby;    // and the block shape they use (sweep_shape)
   int utx, uty;    // thread-block tile of the update and fixup
   int out_lo, out_hi;  // x1 lower / upper boundary is an outflow boundary
 };
@@ -72,10 +79,23 @@ __host__ __device__ inline const S* tab_plane(const S* tab, const Dims& d, int k
   return tab + (size_t)(k + NG) * (size_t)d.tk;
 }
 
-// Loads as (wave-uniform base pointer) + (32-bit unsigned byte offset):
-// the backend can then keep the base in scalar registers and share one 32-bit
-// vector offset across all components, instead of a 64-bit vector address per
-// load. Every array here is < 4 GiB per component (checked at init).
+// Loads through a buffer descriptor: a wave-uniform base pointer and one 32-bit
+// byte offset a lane that every array of a kind shares (a component is < 4 GiB,
+// checked at init). The pointer form costs a 64-bit vector add per load as soon
+// as the compiler rewrites a family of addresses into a chain.
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xffffffffu, 0x00020000);
+}
+__device__ inline double buf_f64(const double* base, unsigned off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(buffer_of(base), (int)off, 0, 0));
+}
+__device__ inline double2 buf_pair(const double* base, unsigned off) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(buffer_of(base), (int)off, 0, 0));
+}
+__device__ inline float2 buf_pair(const float* base, unsigned off) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(buffer_of(base), (int)off, 0, 0));
+}
+// the pointer form
 template <typename S>
 __device__ inline S ldu(const S* base, unsigned byte_off) {
   return *(const S*)((const char*)base + byte_off);
@@ -136,7 +156,7 @@ template <bool AXI, typename T, typename S>
 __device__ inline void load_face_geo(FaceGeo<T>& g, const S* __restrict__ tab, int ts, int off) {
   using P2 = typename pair_of<S>::type;
   const unsigned bo = (unsigned)off * (unsigned)(2 * sizeof(S));
-  auto ld = [&](int c0) -> P2 { return *(const P2*)((const char*)(tab + (size_t)c0 * ts) + bo); };
+  auto ld = [&](int c0) -> P2 { return buf_pair(tab + (size_t)c0 * ts, bo); };
   const P2 a = ld(F_G11), b = ld(F_G13), c = ld(F_G33), d = ld(F_B1), e = ld(F_IALPHA), f = ld(F_HGDET);
   g.g11 = (T)a.x, g.g12 = (T)a.y;
   g.g13 = (T)b.x, g.g22 = (T)b.y;
@@ -257,108 +277,134 @@ __device__ inline void flux_of(const T* P, const Fluid<T>& f, T gdet, T* F) {
   }
 }
 
-// One side of a face of direction D (1..3): flux and conserved variables
-// divided by sqrt(-g) (hydrodynamic part, then the two field components the
-// flux has) and the fast-magnetosonic speeds, from primitives P.
+// One side of a face of direction D (1..3), in two steps: side_speeds finds the
+// fast-magnetosonic speeds and what it needs for them, and once both sides'
+// speeds have given ctop, side_flux adds the side's share of the
+// local Lax-Friedrichs flux.
 //
 // Written in the 3+1 form, which needs the spatial metric, shift and lapse
 // only and no index gymnastics with the four-metric:
 //   u_i = g_ij u~^j, Gamma^2 = 1 + u~^i u_i, u^t = Gamma/alpha, 1/u^t = alpha/Gamma,
 //   u_t = beta^i u_i - alpha Gamma, v^i = u^i/u^t = u~^i/u^t - beta^i,
 //   B_mu = g_mu i B^i, B_t = beta^i B_i, b^t = B^i u_i,
-//   b^i = B^i/u^t + b^t v^i, b_mu = (B_mu + b^t u_mu)/u^t, b^2 = (B^2 + (b^t)^2)/(u^t)^2,
-//   T^D_mu - p_tot delta = ((w + b^2) u^D - b^t b^D/u^t) u_mu - (b^D/u^t) B_mu,
-//   field flux of B^i: B^i v^D - B^D v^i.
+//   b^i = B^i/u^t + b^t v^i, b_mu = (B_mu + b^t u_mu)/u^t, b^2 = (B^2 + (b^t)^2)/(u^t)^2.
 // Speeds: c^2 = num/den with num = b^2 + gamma p, den = b^2 + w (v_A^2 +
 // c_s^2 (1 - v_A^2) as one quotient). With m = den - num = rho + gamma (2 -
 // gamma) u, q = num/Gamma^2 and y = u~^D/u^t the two roots of the dispersion
 // relation are
 //   (m y +- sqrt(q ((m + q) H - m y^2)))/(m + q) - beta^D,
 // with no cancelling products.
+// Flux and conserved variables differ in one factor only, v^D against 1 and
+// b^D against b^t, so F + s U (s = ctop on the left, -ctop on the right) is the
+// flux with the velocity W = v^D + s in place of v^D:
+//   mass rho u^t W, field B^i W - B^D v^i,
+//   T_mu = A u_mu - C B_mu, C = (B^D/u^t + b^t W)/u^t, A = (w + b^2) u^t W - C b^t,
+// plus the pressure: p_tot in the momentum along D, s p_tot in the energy.
 template <typename T>
 struct FaceSide {
-  T F[7], U[7];  // mass, energy, 3 momenta, then B of the two transverse directions (ascending)
-  T cp, cm;
+  T P[NV];
+  T lor, iut, bt, bsq;  // Gamma, 1/u^t, b^t, b^2
+  T cp, cm;             // speeds
 };
 
+// u_i = g_ij u~^j (or B_i)
+template <bool AXI, typename T>
+__device__ inline void lower3(const FaceGeo<T>& g, T v1, T v2, T v3, T& l1, T& l2, T& l3) {
+  l1 = g.g11 * v1 + g.g12 * v2 + g.g13 * v3;
+  l2 = g.g12 * v1 + g.g22 * v2;
+  l3 = g.g13 * v1 + g.g33 * v3;
+  if constexpr (!AXI) {
+    l2 = l2 + g.g23 * v3;
+    l3 = l3 + g.g23 * v2;
+  }
+}
+
 template <int D, bool AXI, typename T>
-__device__ inline void face_side(const T* P, const FaceGeo<T>& g, T gam, FaceSide<T>& s) {
-#pragma clang fp contract(on)
-  const T v1 = P[2], v2 = P[3], v3 = P[4], B1 = P[5], B2 = P[6], B3 = P[7];
-  T ul1 = g.g11 * v1 + g.g12 * v2 + g.g13 * v3;
-  T ul2 = g.g12 * v1 + g.g22 * v2;
-  T ul3 = g.g13 * v1 + g.g33 * v3;
-  T Bl1 = g.g11 * B1 + g.g12 * B2 + g.g13 * B3;
-  T Bl2 = g.g12 * B1 + g.g22 * B2;
-  T Bl3 = g.g13 * B1 + g.g33 * B3;
-  if constexpr (!AXI) {
-    ul2 = ul2 + g.g23 * v3;
-    ul3 = ul3 + g.g23 * v2;
-    Bl2 = Bl2 + g.g23 * B3;
-    Bl3 = Bl3 + g.g23 * B2;
-  }
-  const T l2 = v1 * ul1 + v2 * ul2 + v3 * ul3 + T(1);
+__device__ inline void side_speeds(FaceSide<T>& s, const FaceGeo<T>& g, T gam) {
+  const T* P = s.P;
+  T u1, u2, u3, B1, B2, B3;
+  lower3<AXI>(g, P[2], P[3], P[4], u1, u2, u3);
+  const T l2 = P[2] * u1 + P[3] * u2 + P[4] * u3 + T(1);
+  s.bt = P[5] * u1 + P[6] * u2 + P[7] * u3;
+  lower3<AXI>(g, P[5], P[6], P[7], B1, B2, B3);
+  const T Bsq = P[5] * B1 + P[6] * B2 + P[7] * B3;
   const T rl = rsqrt_full(l2);
-  const T lor = l2 * rl, ut = lor * g.ialpha, iut = g.alpha * rl;
-  T ult = g.b1 * ul1 + g.b2 * ul2 - g.alpha * lor;
-  T Blt = g.b1 * Bl1 + g.b2 * Bl2;
-  if constexpr (!AXI) {
-    ult = ult + g.b3 * ul3;
-    Blt = Blt + g.b3 * Bl3;
-  }
-  const T bt = B1 * ul1 + B2 * ul2 + B3 * ul3;
-  const T Bsq = B1 * Bl1 + B2 * Bl2 + B3 * Bl3;
-  const T bsq = (Bsq + bt * bt) * (iut * iut);
-  const T y = (D == 1 ? v1 : D == 2 ? v2 : v3) * iut;
-  const T bD = D == 1 ? g.b1 : D == 2 ? g.b2 : g.b3;
-  const T vD = (D == 3 && AXI) ? y : y - bD;
-  const T BD = D == 1 ? B1 : D == 2 ? B2 : B3;
+  s.lor = l2 * rl;
+  s.iut = g.alpha * rl;
+  s.bsq = (Bsq + s.bt * s.bt) * (s.iut * s.iut);
   const T gp = gam * (gam - T(1));
-  const T wb = P[0] + gam * P[1] + bsq;
-  const T pt = (gam - T(1)) * P[1] + T(0.5) * bsq;
-  const T rt = P[0] * ut;
-  // flux
-  const T c = (BD * iut + bt * vD) * iut;
-  const T a = wb * (ut * vD) - c * bt;
-  s.F[0] = rt * vD;
-  s.F[1] = a * ult - c * Blt + s.F[0];
-  s.F[2] = a * ul1 - c * Bl1;
-  s.F[3] = a * ul2 - c * Bl2;
-  s.F[4] = a * ul3 - c * Bl3;
-  s.F[1 + D] = s.F[1 + D] + pt;
-  const T Ba = D == 1 ? B2 : B1, Bb = D == 3 ? B2 : B3;
-  const T va = (D == 1 ? v2 : v1) * iut - (D == 1 ? g.b2 : g.b1);
-  T vb = (D == 3 ? v2 : v3) * iut;
-  if constexpr (D == 3) vb = vb - g.b2;
-  else if constexpr (!AXI) vb = vb - g.b3;
-  s.F[5] = Ba * vD - BD * va;
-  s.F[6] = Bb * vD - BD * vb;
-  // conserved variables
-  const T c0 = bt * iut;
-  const T a0 = wb * ut - c0 * bt;
-  s.U[0] = rt;
-  s.U[1] = a0 * ult - c0 * Blt + pt + rt;
-  s.U[2] = a0 * ul1 - c0 * Bl1;
-  s.U[3] = a0 * ul2 - c0 * Bl2;
-  s.U[4] = a0 * ul3 - c0 * Bl3;
-  s.U[5] = Ba;
-  s.U[6] = Bb;
-  // speeds
-  const T num = gp * P[1] + bsq;
   const T m = P[0] + (gam - gp) * P[1];
-  const T q = num * (rl * rl);
+  const T q = (gp * P[1] + s.bsq) * (rl * rl);
   const T A = m + q;
+  const T y = P[1 + D] * s.iut;
   const T my = m * y;
   const T disc = q * (A * g.H - my * y);
   const T iA = rcp_full(A);
   const T r = fabs(sqrt_full(fmax(disc, T(0))) * iA);
-  const T mid = (D == 3 && AXI) ? my * iA : my * iA - bD;
+  T mid = my * iA;
+  if constexpr (D == 1) mid = mid - g.b1;
+  else if constexpr (D == 2) mid = mid - g.b2;
+  else if constexpr (!AXI) mid = mid - g.b3;
   s.cp = mid + r;
   s.cm = mid - r;
 }
 
+// f: mass, energy, 3 momenta, then the two transverse field components
+// (ascending), divided by sqrt(-g)
+template <int D, bool AXI, typename T>
+__device__ inline void side_flux(const FaceSide<T>& s, const FaceGeo<T>& g, T gam, T st, T* f) {
+  const T* P = s.P;
+  T u1, u2, u3, B1, B2, B3;
+  lower3<AXI>(g, P[2], P[3], P[4], u1, u2, u3);
+  lower3<AXI>(g, P[5], P[6], P[7], B1, B2, B3);
+  T ult = g.b1 * u1 + g.b2 * u2 - g.alpha * s.lor;
+  T Blt = g.b1 * B1 + g.b2 * B2;
+  T W = P[1 + D] * s.iut + st;
+  if constexpr (D == 1) W = W - g.b1;
+  else if constexpr (D == 2) W = W - g.b2;
+  if constexpr (!AXI) {
+    ult = ult + g.b3 * u3;
+    Blt = Blt + g.b3 * B3;
+    if constexpr (D == 3) W = W - g.b3;
+  }
+  const T BD = P[4 + D];
+  const T m = s.lor * g.ialpha * W;
+  const T C = (BD * s.iut + s.bt * W) * s.iut;
+  const T A = (P[0] + gam * P[1] + s.bsq) * m - C * s.bt;
+  const T pt = (gam - T(1)) * P[1] + T(0.5) * s.bsq;
+  f[0] = P[0] * m;
+  f[1] = A * ult - C * Blt + st * pt + f[0];
+  f[2] = A * u1 - C * B1;
+  f[3] = A * u2 - C * B2;
+  f[4] = A * u3 - C * B3;
+  f[1 + D] = f[1 + D] + pt;
+  constexpr int a = D == 1 ? 2 : 1, b = D == 3 ? 2 : 3;
+  const T va = P[1 + a] * s.iut - (D == 1 ? g.b2 : g.b1);
+  T vb = P[1 + b] * s.iut;
+  if constexpr (D == 3) vb = vb - g.b2;
+  else if constexpr (!AXI) vb = vb - g.b3;
+  f[5] = P[4 + a] * W - BD * va;
+  f[6] = P[4 + b] * W - BD * vb;
+}
+
 // ---------------------------------------------------------------------------
 // reconstruction
+
+// Half the monotonised-central slope of a zone from its left and right
+// differences: min(|dm|, |dp|, |dm + dp|/4) with the sign of the flow, 0 at an
+// extremum. The 0 or 1 of that test multiplies the slope (one select instead of
+// two for a 64-bit zero).
+template <typename T>
+struct McSlope {
+  T h, one;
+  __device__ McSlope(T dm, T dp) {
+    const T c = T(0.25) * (dm + dp);
+    h = copysign(fmin(fmin(fabs(dm), fabs(dp)), fabs(c)), c);
+    one = dm * dp > T(0) ? T(1) : T(0);
+  }
+  __device__ T above(T p) const { return fma(h, one, p); }
+  __device__ T below(T p) const { return fma(-h, one, p); }
+};
 
 template <typename T>
 __device__ inline T mc_slope(T pm, T p0, T pp) {
@@ -432,6 +478,76 @@ constexpr int TILE_Y = 1;
 constexpr int SWEEP_MAX_THREADS = 512;   // launch bounds of the sweep kernels
 constexpr int UPDATE_MAX_THREADS = 256;  // launch bounds of the update and fixup kernels
 
+// What the face-flux pass leaves for the update, per cell:
+//   D   minus the divergence of the five hydrodynamic fluxes in x1 and x2;
+//   f3  the five hydrodynamic x3 fluxes;
+//   e   four times the EMF of the cell's lower x1, x2 and x3 edge, the first
+//       two without the flux of the plane below,
+//   b   which are the x2 and the x1 flux of B3;
+//   m   the mass fluxes through the lower x1 and x2 face (electron steps only;
+//       the x3 one is f3's first).
+// T is the precision of the fluxes. 17 values a cell, of the 24 T there is room
+// for (three flux arrays of a state's shape).
+template <typename T>
+struct FluxOut {
+  double* D;
+  T *f3, *e, *b, *m;
+};
+template <typename T>
+__host__ __device__ inline FluxOut<T> flux_out(unsigned char* base, int sv) {
+  FluxOut<T> o;
+  o.D = (double*)base;
+  o.f3 = (T*)(o.D + 5 * (size_t)sv);
+  o.e = o.f3 + 5 * (size_t)sv;
+  o.b = o.e + 3 * (size_t)sv;
+  o.m = o.b + 2 * (size_t)sv;
+  return o;
+}
+
+// its tiles cover the cells -1..n and overlap by one
+__host__ __device__ inline int sweep_tiles(int n, int b) { return (n + 1 + b - 2) / (b - 1); }
+// Block shapes of the face-flux pass, BX x BY threads in rows no longer than a
+// wave. The large one is 64 x 8, or 32 x 16 for FP64 WENO5, whose 64 x 8 plane
+// and exchange take 86 KB of LDS and leave one block a CU (131 x 67 x 45 torus:
+// 156 us against 117). The small one, 32 x 8, is for grids that make fewer than
+// 1024 large blocks, two rounds of the two a CU holds, and would leave CUs idle
+// (64 x 64 x 1: 14 us against 12; 96 x 64 x 32, 680 large blocks: 35 against
+// 33; 160 x 96 x 48, 2100 blocks: 58 against 61).
+constexpr int SMALL_BX = 32, SMALL_BY = 8;
+constexpr long long SMALL_BELOW = 1024;
+__host__ __device__ constexpr int large_bx(int recon, bool mixed) { return recon == GRMHD_RECON_WENO5 && !mixed ? 32 : 64; }
+__host__ __device__ constexpr int large_by(int recon, bool mixed) { return 512 / large_bx(recon, mixed); }
+// blocks of a grid in the shape (bx, by)
+inline long long sweep_grid(const Dims& d, int bx, int by) {
+  return (long long)sweep_tiles(d.n1, bx) * sweep_tiles(d.n2, by) * ((d.n3 + 2 + NXCD - 1) / NXCD) * NXCD;
+}
+// is the small shape right for a pass that makes so many large blocks? Tiles
+// set below 512 threads ask for it too.
+inline bool sweep_small(const Dims& d, long long large_blocks) {
+  return d.stx * d.sty <= SMALL_BX * SMALL_BY || large_blocks < SMALL_BELOW;
+}
+inline void sweep_shape(Dims& d, int recon, bool mixed, bool small) {
+  d.sbx = small ? SMALL_BX : large_bx(recon, mixed);
+  d.sby = small ? SMALL_BY : large_by(recon, mixed);
+}
+struct SweepTile {
+  int i0, j0, k;   // first cell of the tile and its plane
+  bool valid;
+};
+// XCD x takes a slab of planes, tile by tile with x2 fastest: a tile's planes
+// share its geometry and their x3 stencils in the XCD's L2, and the next tile
+// finds the rows it shares with them there
+__device__ inline SweepTile sweep_tile(const Dims& d, int bx, int by, int b) {
+  const int ty = sweep_tiles(d.n2, by), planes = d.n3 + 2, chunk = (planes + NXCD - 1) / NXCD;
+  const int x = b % NXCD, w = b / NXCD, tile = w / chunk;
+  SweepTile t;
+  t.k = -1 + x * chunk + (w - tile * chunk);
+  t.i0 = -1 + (tile / ty) * (bx - 1);
+  t.j0 = -1 + (tile % ty) * (by - 1);
+  t.valid = t.k <= d.n3;
+  return t;
+}
+
 struct TileK {
   int i0, j0, k;
   bool valid;
@@ -491,6 +607,23 @@ __device__ inline void block_max_to(double v, unsigned long long* dst) {
   }
 }
 
+// the maximum of non-negative values over a wave, in its last lane, by moves
+// between lanes (a shuffle goes through LDS)
+template <int CTRL>
+__device__ inline double dpp_max(double v) {
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  return fmax(v, __hiloint2double(hi, lo));
+}
+__device__ inline double wave_max_last(double v) {
+  v = dpp_max<0x111>(v);  // row_shr 1, 2, 4, 8: the last lane of each row of 16
+  v = dpp_max<0x112>(v);
+  v = dpp_max<0x114>(v);
+  v = dpp_max<0x118>(v);
+  v = dpp_max<0x142>(v);  // row_bcast 15 and 31: across the rows
+  return dpp_max<0x143>(v);
+}
+
 // block_max_to for three values at once into dst[0..2]: one barrier, and
 // the atomic only where the block's maximum exceeds the running one (values
 // only grow, so a stale read can only cost an unneeded atomic)
@@ -498,10 +631,10 @@ __device__ inline void block_max3_to(double a, double b, double c, unsigned long
   __shared__ double part3[3][16];
   const int tid = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
   const int nthr = blockDim.x * blockDim.y * blockDim.z;
-  a = wave_max(a + 0.0);
-  b = wave_max(b + 0.0);
-  c = wave_max(c + 0.0);
-  if ((tid & 63) == 0) {
+  a = wave_max_last(a + 0.0);
+  b = wave_max_last(b + 0.0);
+  c = wave_max_last(c + 0.0);
+  if ((tid & 63) == 63) {
     part3[0][tid >> 6] = a;
     part3[1][tid >> 6] = b;
     part3[2][tid >> 6] = c;

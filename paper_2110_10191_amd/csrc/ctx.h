@@ -95,7 +95,7 @@ struct grmhd_ctx {
   double* Ph;
   double* Eh;  // electron heating scratch (allocated on first use): half-step entropies
   double* Uk;  // and the advected sqrt(-g) rho u^t K of the current substep
-  void* F[3];
+  void* F;     // what the face-flux pass leaves (FluxOut)
   int8_t* flags;
   Counters* ctr;
   double* noalloc;  // this device's static scratch (grmhd_divb_noalloc), not owned

@@ -66,27 +66,27 @@ __device__ inline void scalar_flux(const double* E, int sv, int c, int st, doubl
 // b: block index within this job's grid (the update tile, XCD-aware order)
 template <typename TF, int RECON>
 __device__ void scalar_advect_body(const Dims& d, const double* __restrict__ cent, const UpdateParams& up,
-                                   const TF* __restrict__ F1, const TF* __restrict__ F2, const TF* __restrict__ F3,
-                                   const double* __restrict__ Pb, const double* __restrict__ Eb,
+                                   const FluxOut<TF>& F, const double* __restrict__ Pb, const double* __restrict__ Eb,
                                    const double* __restrict__ Es, double* __restrict__ Uk, double dt, int b) {
   const TileK tk = xcd_tile_k(b, d.utx, d.uty, d.n1, d.n3);
   const int i = tk.i0 + (int)threadIdx.x;
   const int j = tk.j0 + (int)threadIdx.y;
   if (!tk.valid || i >= d.n1 || j >= d.n2) return;
   const int c = cell_of(d, tk.k, j, i);
+  const TF *m = F.m, *m2 = F.m + d.sv, *m3 = F.f3;  // mass fluxes
   const bool pl = up.polar_lo && j == 0;
   const bool ph = up.polar_hi && j == d.n2 - 1;
   double fm[GRMHD_NSCALAR], fp[GRMHD_NSCALAR], div[GRMHD_NSCALAR];
-  scalar_flux<RECON>(Es, d.sv, c, 1, (double)F1[c], fm);
-  scalar_flux<RECON>(Es, d.sv, c + 1, 1, (double)F1[c + 1], fp);
+  scalar_flux<RECON>(Es, d.sv, c, 1, (double)m[c], fm);
+  scalar_flux<RECON>(Es, d.sv, c + 1, 1, (double)m[c + 1], fp);
 #pragma unroll
   for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] = (fp[s] - fm[s]) * up.idx1;
-  scalar_flux<RECON>(Es, d.sv, c, d.s2, pl ? 0.0 : (double)F2[c], fm);
-  scalar_flux<RECON>(Es, d.sv, c + d.s2, d.s2, ph ? 0.0 : (double)F2[c + d.s2], fp);
+  scalar_flux<RECON>(Es, d.sv, c, d.s2, pl ? 0.0 : (double)m2[c], fm);
+  scalar_flux<RECON>(Es, d.sv, c + d.s2, d.s2, ph ? 0.0 : (double)m2[c + d.s2], fp);
 #pragma unroll
   for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] += (fp[s] - fm[s]) * up.idx2;
-  scalar_flux<RECON>(Es, d.sv, c, d.s3, (double)F3[c], fm);
-  scalar_flux<RECON>(Es, d.sv, c + d.s3, d.s3, (double)F3[c + d.s3], fp);
+  scalar_flux<RECON>(Es, d.sv, c, d.s3, (double)m3[c], fm);
+  scalar_flux<RECON>(Es, d.sv, c + d.s3, d.s3, (double)m3[c + d.s3], fp);
 #pragma unroll
   for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] += (fp[s] - fm[s]) * up.idx3;
 
@@ -105,13 +105,12 @@ __device__ void scalar_advect_body(const Dims& d, const double* __restrict__ cen
 
 template <typename TF, int RECON>
 __global__ __launch_bounds__(256) void scalar_advect_kernel(Dims d, const double* __restrict__ cent, UpdateParams up,
-                                                            const TF* __restrict__ F1, const TF* __restrict__ F2,
-                                                            const TF* __restrict__ F3, const double* __restrict__ Pb,
+                                                            FluxOut<TF> F, const double* __restrict__ Pb,
                                                             const double* __restrict__ Eb, const double* __restrict__ Es,
                                                             double* __restrict__ Uk, double dt,
                                                             const double* __restrict__ dt_dev, double dt_scale) {
   if (dt_dev) dt = dt_scale * *dt_dev;
-  scalar_advect_body<TF, RECON>(d, cent, up, F1, F2, F3, Pb, Eb, Es, Uk, dt, (int)blockIdx.x);
+  scalar_advect_body<TF, RECON>(d, cent, up, F, Pb, Eb, Es, Uk, dt, (int)blockIdx.x);
 }
 
 // every job with entropies in one grid: predictor (E -> U_K, base P), corrector
@@ -123,8 +122,8 @@ __global__ __launch_bounds__(256) void scalar_advect_batch_kernel(BatchView bv, 
   const JobDesc& J = bv.jobs[jb];
   if (!J.E) return;
   const double dt = corrector ? *J.dt : 0.5 * *J.dt;
-  scalar_advect_body<TF, RECON>(J.d, global_ptr(J.t.cent), J.up, global_ptr((const TF*)J.F[0]),
-                                global_ptr((const TF*)J.F[1]), global_ptr((const TF*)J.F[2]), global_ptr(J.P),
+  scalar_advect_body<TF, RECON>(J.d, global_ptr(J.t.cent), J.up,
+                                flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv), global_ptr(J.P),
                                 global_ptr(J.E), global_ptr(corrector ? J.Eh : J.E), global_ptr(J.Uk), dt,
                                 (int)blockIdx.x - offs[jb]);
 }
@@ -216,27 +215,25 @@ __global__ __launch_bounds__(256) void electron_heat_batch_kernel(BatchView bv, 
 }
 
 template <typename TF>
-void advect_for(int recon, const Dims& d, const Tables& t, const UpdateParams& up, const void* F1, const void* F2,
-                const void* F3, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
+void advect_for(int recon, const Dims& d, const Tables& t, const UpdateParams& up, const void* F, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
                 const double* dt_dev, double dt_scale, hipStream_t s) {
   const dim3 grid(xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty)), block(d.utx, d.uty, 1);
-  const TF *f1 = (const TF*)F1, *f2 = (const TF*)F2, *f3 = (const TF*)F3;
+  const FluxOut<TF> f = flux_out<TF>((unsigned char*)F, d.sv);
   if (recon == GRMHD_RECON_MC)
-    hipLaunchKernelGGL((scalar_advect_kernel<TF, GRMHD_RECON_MC>), grid, block, 0, s, d, t.cent, up, f1, f2, f3, Pb,
+    hipLaunchKernelGGL((scalar_advect_kernel<TF, GRMHD_RECON_MC>), grid, block, 0, s, d, t.cent, up, f, Pb,
                        Eb, Es, Uk, dt, dt_dev, dt_scale);
   else
-    hipLaunchKernelGGL((scalar_advect_kernel<TF, GRMHD_RECON_WENO5>), grid, block, 0, s, d, t.cent, up, f1, f2, f3,
-                       Pb, Eb, Es, Uk, dt, dt_dev, dt_scale);
+    hipLaunchKernelGGL((scalar_advect_kernel<TF, GRMHD_RECON_WENO5>), grid, block, 0, s, d, t.cent, up, f, Pb,
+                       Eb, Es, Uk, dt, dt_dev, dt_scale);
 }
 
 }  // namespace
 
 hipError_t launch_scalar_advect(bool mixed, int recon, const Dims& d, const Tables& t, const UpdateParams& up,
-                                const void* F1, const void* F2, const void* F3, const double* Pb, const double* Eb,
-                                const double* Es, double* Uk, double dt, const double* dt_dev, double dt_scale,
-                                hipStream_t s) {
-  if (mixed) advect_for<float>(recon, d, t, up, F1, F2, F3, Pb, Eb, Es, Uk, dt, dt_dev, dt_scale, s);
-  else advect_for<double>(recon, d, t, up, F1, F2, F3, Pb, Eb, Es, Uk, dt, dt_dev, dt_scale, s);
+                                const void* F, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
+                                const double* dt_dev, double dt_scale, hipStream_t s) {
+  if (mixed) advect_for<float>(recon, d, t, up, F, Pb, Eb, Es, Uk, dt, dt_dev, dt_scale, s);
+  else advect_for<double>(recon, d, t, up, F, Pb, Eb, Es, Uk, dt, dt_dev, dt_scale, s);
   return hipGetLastError();
 }
 

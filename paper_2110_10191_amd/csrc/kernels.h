@@ -55,7 +55,7 @@ struct JobDesc {
   UpdateParams up;
   double* P;        // the job's state (caller-owned)
   double* Ph;       // half-step state
-  void* F[3];       // face fluxes (double or float)
+  void* F;          // what the face-flux pass leaves (FluxOut)
   int8_t* flags;
   Counters* ctr;
   double* dt;       // device scalar: the job's step size for the next step
@@ -75,7 +75,7 @@ struct BatchView {
   const JobDesc* jobs;
   const int* offs;
   int njobs;
-  int stx, sty, utx, uty;  // block tiles shared by every job of the batch
+  int sbx, sby, utx, uty;  // block shapes shared by every job of the batch
   int axi;                 // every job's coordinates have g_23 = beta^3 = 0 (none is Cartesian Kerr-Schild)
 };
 
@@ -139,21 +139,20 @@ hipError_t launch_fill_ghosts(const grmhd_problem& p, const Dims& d, const Table
                               const double* dirichlet_src, hipStream_t s, Counters* ctr = nullptr,
                               int reset_mask = 0, DtRule dt_rule = DtRule{});
 
-// face fluxes of all three directions of state P into F[0..2] (double for
-// fp64, float for mixed) with the problem's reconstruction and gamma;
-// Cartesian Kerr-Schild computes its face geometry instead of reading the
-// face tables; ctop (may be null) receives the per-direction maximum signal
-// speeds; sweep_blocks: the launch's grid size
+// flux divergence and EMFs of state P into F (FluxOut of double for fp64, of
+// float for mixed) with the problem's reconstruction and gamma; Cartesian
+// Kerr-Schild computes its face geometry instead of reading the face tables;
+// mass: the mass fluxes as well; ctop (may be null) receives the per-direction
+// maximum signal speeds; sweep_blocks: the launch's grid size
 unsigned sweep_blocks(const Dims& d);
-hipError_t launch_sweeps(const grmhd_problem& p, bool mixed, const Dims& d, const Tables& t, const double* P,
-                         void* const* F, unsigned long long* ctop, hipStream_t s);
+hipError_t launch_sweeps(const grmhd_problem& p, bool mixed, const Dims& d, const Tables& t, const UpdateParams& up,
+                         const double* P, void* F, bool mass, unsigned long long* ctop, hipStream_t s);
 
 // the step is dt, or dt_scale * *dt_dev when dt_dev is not null; cks (the
 // problem, Cartesian Kerr-Schild only): the update computes the centre
 // metric in closed form instead of reading it
 hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const UpdateParams& up,
-                         const void* F1, const void* F2, const void* F3, const double* Pb,
-                         const double* Ps, double* Pout, int8_t* flags, double dt,
+                         const void* F, const double* Pb, const double* Ps, double* Pout, int8_t* flags, double dt,
                          const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s,
                          const grmhd_problem* cks = nullptr);
 
@@ -193,9 +192,8 @@ hipError_t launch_divb_noalloc(const grmhd_problem& p, const Dims& d, const Tabl
 hipError_t launch_fill_scalar_ghosts(const grmhd_problem& p, const Dims& d, double* E, const double* dirichlet_src,
                                      hipStream_t s);
 hipError_t launch_scalar_advect(bool mixed, int recon, const Dims& d, const Tables& t, const UpdateParams& up,
-                                const void* F1, const void* F2, const void* F3, const double* Pb, const double* Eb,
-                                const double* Es, double* Uk, double dt, const double* dt_dev, double dt_scale,
-                                hipStream_t s);
+                                const void* F, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
+                                const double* dt_dev, double dt_scale, hipStream_t s);
 hipError_t launch_electron_heat(const Dims& d, const Tables& t, double gam, double* P, const double* Uk, double* E,
                                 int model, double fel, Counters* ctr, hipStream_t s);
 

@@ -1,35 +1,56 @@
-// Face fluxes of all three directions in one pass: reconstruct the primitives
-// at the lower d-face of each zone (MC or WENO5), evaluate both face states
-// (four-velocity, field four-vector, flux, conserved variables, fast-
-// magnetosonic speeds) and combine them with the local Lax-Friedrichs flux
+// Face fluxes of all three directions, their divergence and the Flux-CT edge
+// EMFs in one pass: reconstruct the primitives at the lower d-face of each zone
+// (MC or WENO5), evaluate both face states (flux, conserved variables, fast-
+// magnetosonic speeds), combine them with the local Lax-Friedrichs flux
 //   F = (F_L + F_R)/2 - ctop (U_R - U_L)/2,
-//   ctop = max(max(0, c+_L, c+_R), max(0, -c-_L, -c-_R)).
+//   ctop = max(max(0, c+_L, c+_R), max(0, -c-_L, -c-_R)),
+// and keep what the update needs of them: the divergence of the five
+// hydrodynamic fluxes and the three EMFs of the zone's lower edges.
 // Functionality section: HARM updates conserved variables by finite volumes;
-// the reconstruction and Riemann solver follow the HARM literature.
+// the reconstruction and Riemann solver follow the HARM literature. Flux-CT:
+// Implementation Notes, after Toth 2000.
 //
-// Faces covered in direction d: 0..n_d along d, and -1..n_t in both
-// transverse directions (the extra transverse layer feeds the Flux-CT EMFs).
-// One thread per cell (i, j, k) with i, j, k in [-1, n] computes the faces of
-// every direction whose range holds it, so a cell's primitives are read from
-// HBM once for the three directions and one launch replaces three. A block
-// first copies its tile of the x3 plane, with the reconstruction halo in x1
-// and x2, into LDS (coalesced along x1); the x1 and x2 stencils then come
-// from LDS and only the other planes of the x3 stencil from the state. The
-// per-direction maximum of ctop over the faces with interior transverse index
-// feeds the Courant step (one atomic max per block and direction); a face with
-// a NaN speed counts as +inf there, which the step reports as a non-finite
-// state. The face geometry comes from the face tables, or for Cartesian
-// Kerr-Schild in FP64 from its closed form (the same bits as the table).
+// Cells covered: faces 0..n_d along d, transverse indices -1..n_t (the extra
+// transverse layer feeds the EMFs). A block holds a tile of (x1, x2) cells of
+// one x3 plane, one thread per cell. It stages the plane's primitives with the
+// stencil halo in LDS (the x1 and x2 stencils come from there, the rest of the
+// x3 stencil from the state) and computes the x3, x1 and x2 face of each cell.
+// The x1 neighbours' fluxes come from the next and previous lane (a row of the
+// tile lies within a wave), the x2 neighbours' through LDS. A cell's divergence
+// needs the next thread of its row and the next row, its EMFs the previous
+// ones, so neighbouring tiles overlap by one cell; what needs the plane above
+// or below (the x3 fluxes, the x1 and x2 flux of B3) goes out as it is.
 //
-// The face states are written in the 3+1 form (face_side): 12 or 14 geometry
-// values a face instead of 22, about a third fewer operations a state. On the
-// 288 x 128 x 128 torus in FP64 with MC slopes the pass takes 0.451 ms (0.513
-// with the four-metric), with mixed-precision WENO5 0.500 (0.567).
+// What bounds it: FP64 issue and the latency of its loads, about half each (a
+// wave issues some 1300 VALU instructions, 500 of them the MC slopes). It runs
+// at four waves a SIMD, so a face may hold 128 registers: sums and speeds wait
+// in LDS, and FACE_FENCE keeps the three faces apart. On the 288 x 128 x 128
+// torus in FP64 with MC slopes it takes 0.410 ms; writing the three flux arrays
+// it took 0.451, and the update, which read 66 of their values a cell and now
+// reads 35, 0.605 against 0.470 (mixed-precision WENO5: the pass 0.50 -> 0.55,
+// the update 0.57 -> 0.42). The tiles are walked x2 first, so a block finds the
+// rows it shares with the tile before in the XCD's L2 (0.94 -> 0.61 GB read).
+// A block that walks along 4 to 32 planes with running sums writes 8 values a
+// cell instead of 15, but its registers leave three waves a SIMD and its
+// geometry falls out of the L2 between planes: 0.50 ms.
+//
+// The face states are written in the 3+1 form (side_speeds, side_flux): 12 or
+// 14 geometry values a face.
+//
+// The per-direction maximum of ctop over the faces with interior transverse
+// index feeds the Courant step (one atomic max per block and direction); a
+// face with a NaN speed counts as +inf there, which the step reports as a
+// non-finite state. The face geometry comes from the face tables, or for
+// Cartesian Kerr-Schild in FP64 from its closed form (the same bits).
 #include <atomic>
 #include <type_traits>
 
 #include "cks_geometry.h"
 #include "kernels.h"
+
+// Keeps one face's arithmetic out of the next one's: interleaved, the three
+// faces of a cell need more registers than four waves a SIMD leave.
+#define FACE_FENCE do { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); } while (0)
 
 namespace {
 
@@ -40,136 +61,224 @@ enum { GEO_AXI = 0, GEO_TABLE, GEO_CKS };
 
 // the block's x3 plane of primitives with the stencil halo in x1 and x2,
 // [8][lh][lw] of T, cells (ib + li, jb + lj)
-template <typename T>
-struct PlaneTile {
-  const T* lds;
-  int lw, lh;    // row length and rows
-  int li, lj;    // this thread's cell in the tile
-  int plane;     // lw * lh
+// The block shape is a template parameter: the row length and the distance
+// between variables are then constants, and a stencil read needs no address of
+// its own per variable (with runtime strides the loop over planes kept some 50
+// such addresses in registers and spilled).
+template <int RECON, int BX, int BY>
+struct PlaneShape {
+  // halo of the reconstruction: zones below / above the cell (MC 2 / 1, WENO5 3 / 2)
+  static constexpr int LO = RECON == GRMHD_RECON_MC ? 2 : 3, HI = RECON == GRMHD_RECON_MC ? 1 : 2;
+  static constexpr int LW = BX + LO + HI, LH = BY + LO + HI, PLANE = LW * LH, NTHR = BX * BY;
 };
 
-// halo of the reconstruction: zones below / above the cell (MC 2 / 1, WENO5 3 / 2)
-template <int RECON>
-constexpr int halo_lo() { return RECON == GRMHD_RECON_MC ? 2 : 3; }
-template <int RECON>
-constexpr int halo_hi() { return RECON == GRMHD_RECON_MC ? 1 : 2; }
+// the value a lane's neighbour holds: the next lane of the wave, or the
+// previous one (every lane of the wave must be active)
+template <int CTRL>
+__device__ inline int dpp32(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false); }
+constexpr int WAVE_SHL1 = 0x130, WAVE_SHR1 = 0x138;
+template <int CTRL>
+__device__ inline float dpp(float x) { return __int_as_float(dpp32<CTRL>(__float_as_int(x))); }
+template <int CTRL>
+__device__ inline double dpp(double x) {
+  return __hiloint2double(dpp32<CTRL>(__double2hiint(x)), dpp32<CTRL>(__double2loint(x)));
+}
+template <typename T>
+__device__ inline T next_lane(T x) { return dpp<WAVE_SHL1>(x); }
+template <typename T>
+__device__ inline T prev_lane(T x) { return dpp<WAVE_SHR1>(x); }
 
-// the face of direction D at the lower D-face of cell (k, j, i): store the
-// flux (all but the face-normal field component, which Flux-CT replaces by
-// zero and nothing reads) and return the signal speed for the Courant maximum
-// (0 for a face with a transverse ghost index, +inf when its speeds are not
-// finite)
-// GEO: where the face geometry comes from
-template <int D, int RECON, typename T, int GEO>
-__device__ inline double one_face(const Dims& d, const double* __restrict__ P, const PlaneTile<T>& pt,
-                                  const T* __restrict__ tab, const CksBox& box, T* __restrict__ F, T gam, int i,
-                                  int j, int k) {
-  const int c = cell_of(d, k, j, i);
-  T PL[NV], PR[NV];
+// both sides of the lower D-face of the cell whose place in the staged plane
+// is q; the other planes of an x3 stencil come from the state, at byte offset cb
+// of each variable (planes pb apart)
+template <int D, int RECON, typename T, typename SH>
+__device__ inline void face_sides(const double* __restrict__ P, size_t sv, const T* q, unsigned cb, unsigned pb,
+                                  FaceSide<T>& L, FaceSide<T>& R) {
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    // x1 and x2 stencils from the LDS tile, x3 from the state
-    const T* ql = pt.lds + v * pt.plane + pt.lj * pt.lw + pt.li;
-    const double* qg = P + v * d.sv + c;
-    const int st = (D == 1) ? 1 : pt.lw;
+    const T* ql = q + v * SH::PLANE;
+    constexpr int st = (D == 1) ? 1 : SH::LW;
     // the cell's own value from the LDS tile in every direction
-    auto at = [&](int o) -> T { return (D == 3 && o != 0) ? (T)qg[o * d.s3] : ql[o * st]; };
-    if (RECON == GRMHD_RECON_MC) {
+    auto at = [&](int o) -> T { return (D == 3 && o != 0) ? (T)buf_f64(P + v * sv, cb + (unsigned)o * pb) : ql[o * st]; };
+    if constexpr (RECON == GRMHD_RECON_MC) {
       const T a = at(-2), bb = at(-1), e = at(0), f = at(1);
-      PL[v] = bb + T(0.5) * mc_slope(a, bb, e);
-      PR[v] = e - T(0.5) * mc_slope(bb, e, f);
+      const T dl = bb - a, dc = e - bb, dr = f - e;
+      L.P[v] = McSlope<T>(dl, dc).above(bb);
+      R.P[v] = McSlope<T>(dc, dr).below(e);
     } else {
       const T x0 = at(-3), x1 = at(-2), x2 = at(-1), x3 = at(0), x4 = at(1), x5 = at(2);
-      PL[v] = weno5_edge(x0, x1, x2, x3, x4);
-      PR[v] = weno5_edge(x5, x4, x3, x2, x1);
+      L.P[v] = weno5_edge(x0, x1, x2, x3, x4);
+      R.P[v] = weno5_edge(x5, x4, x3, x2, x1);
     }
   }
-  FaceGeo<T> g;
-  if constexpr (GEO == GEO_CKS) cks_face_geo(box, D, i, j, k, g);
-  else load_face_geo<GEO == GEO_AXI>(g, face_plane(tab, d, k), d.ts, tab_of(d, j, i));
-  constexpr bool AXI = GEO == GEO_AXI;
-  FaceSide<T> L, R;
-  face_side<D, AXI>(PL, g, gam, L);
-  face_side<D, AXI>(PR, g, gam, R);
-  const T ct = fmax(fmax(fmax(T(0), L.cp), R.cp), fmax(-L.cm, -R.cm));
-  T fv[NV];
-  {
-#pragma clang fp contract(on)
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      const int v = q < 5 ? q : q == 5 ? (D == 1 ? 6 : 5) : (D == 3 ? 6 : 7);
-      fv[v] = g.hgdet * ((L.F[q] + R.F[q]) - ct * (R.U[q] - L.U[q]));
-    }
-  }
-  // no mass enters through an outflow boundary: the rest-mass flux through
-  // the inner radial face is at most 0, through the outer one at least 0
-  if (D == 1 && d.out_lo && i == 0) fv[0] = fmin(fv[0], T(0));
-  if (D == 1 && d.out_hi && i == d.n1) fv[0] = fmax(fv[0], T(0));
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-    if (v != 4 + D) F[v * d.sv + c] = fv[v];
-  bool inner;
-  if (D == 1) inner = (j >= 0 && j < d.n2 && k >= 0 && k < d.n3);
-  else if (D == 2) inner = (i >= 0 && i < d.n1 && k >= 0 && k < d.n3);
-  else inner = (i >= 0 && i < d.n1 && j >= 0 && j < d.n2);
-  if (!inner) return 0.0;
-  // fmax drops a NaN operand, so a face whose states are not finite would
-  // report a finite (often zero) speed: any NaN speed makes it +inf, so the
-  // Courant step sees the non-finite state
-  const T chk = (L.cp + L.cm) + (R.cp + R.cm);
-  return (chk == chk) ? (double)ct : __builtin_inf();
 }
 
-// b: block index within this job's grid of tiles over (n1+2) x (n2+2) x (n3+2)
-// cells starting at (-1, -1, -1)
-template <int RECON, typename T, int GEO>
-__device__ void sweep_body(const Dims& d, const double* __restrict__ P, const T* __restrict__ t1,
-                           const T* __restrict__ t2, const T* __restrict__ t3, const CksBox& box, T* __restrict__ F1,
-                           T* __restrict__ F2, T* __restrict__ F3, T gam, int b, unsigned long long* ctop) {
-  const TileK t = xcd_tile_k(b, d.stx, d.sty, d.n1 + 2, d.n3 + 2);
-  const int i = -1 + t.i0 + (int)threadIdx.x;
-  const int j = -1 + t.j0 + (int)threadIdx.y;
-  const int k = -1 + t.k;
-  const bool ok = t.valid && i <= d.n1 && j <= d.n2;
-  // stage this x3 plane of the tile and its x1 / x2 halo in LDS, once for the
-  // block: cells [ib, ib + lw) x [jb, jb + lh), those inside the padded state
-  // (cells outside it are never read: faces start at cell 0 and end at n)
-  extern __shared__ __align__(16) unsigned char sweep_lds[];
-  PlaneTile<T> pt;
-  pt.lds = reinterpret_cast<const T*>(sweep_lds);
-  pt.lw = d.stx + halo_lo<RECON>() + halo_hi<RECON>();
-  pt.lh = d.sty + halo_lo<RECON>() + halo_hi<RECON>();
-  pt.plane = pt.lw * pt.lh;
-  pt.li = (int)threadIdx.x + halo_lo<RECON>();
-  pt.lj = (int)threadIdx.y + halo_lo<RECON>();
-  if (t.valid) {
-    T* L = reinterpret_cast<T*>(sweep_lds);
-    const int ib = -1 + t.i0 - halo_lo<RECON>(), jb = -1 + t.j0 - halo_lo<RECON>();
-    const int nthr = d.stx * d.sty;
-    for (int e = (int)threadIdx.y * d.stx + (int)threadIdx.x; e < pt.plane; e += nthr) {
-      const int lj = e / pt.lw, li = e - lj * pt.lw;
-      const int gi = ib + li, gj = jb + lj;
-      if (gi >= -NG && gi < d.n1 + NG && gj >= -NG && gj < d.n2 + NG) {
-        const int c = cell_of(d, k, gj, gi);
+// The local Lax-Friedrichs flux of a face (mass, energy, 3 momenta, then the
+// two transverse field components in ascending order) in f. CTOP: *top takes
+// the signal speed for the Courant maximum, 0 for a face outside it (inner
+// false) and +inf when a speed is not finite (fmax drops a NaN operand, so such
+// a face would report a finite, often zero, speed)
+template <int D, bool AXI, bool CTOP, typename T>
+__device__ inline void face_flux(FaceSide<T>& L, FaceSide<T>& R, const FaceGeo<T>& g, T gam, T* f, T* top, bool inner) {
+  side_speeds<D, AXI>(L, g, gam);
+  side_speeds<D, AXI>(R, g, gam);
+  const T ct = fmax(fmax(fmax(T(0), L.cp), R.cp), fmax(-L.cm, -R.cm));
+  if (CTOP) {
+    const T chk = (L.cp + L.cm) + (R.cp + R.cm);
+    *top = !inner ? T(0) : chk == chk ? ct : (T)__builtin_inf();
+  }
+  T fr[7];
+  side_flux<D, AXI>(L, g, gam, ct, f);
+  side_flux<D, AXI>(R, g, gam, -ct, fr);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) L[v * pt.plane + e] = (T)P[v * d.sv + c];
-      }
+  for (int v = 0; v < 7; ++v) f[v] = g.hgdet * (f[v] + fr[v]);
+}
+
+// exchange through LDS between the rows of a tile: the x2 flux's five
+// hydrodynamic components, the x1 flux of B2 and the x3 flux of B2
+constexpr int NEXCH = 7;
+
+// what a job's pass reads and writes
+template <typename T>
+struct SweepArgs {
+  const double* P;
+  const T *t1, *t2, *t3;
+  FluxOut<T> out;
+  T* mass;  // the three mass fluxes as well, for the electron entropies (null: not kept)
+  double idx1, idx2, idx3;
+  T gam;
+  int polar_lo, polar_hi;
+};
+
+// b: block index within this job's grid; BX x BY threads
+template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
+__device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, const CksBox& box, int b, unsigned long long* ctop) {
+  using SH = PlaneShape<RECON, BX, BY>;
+  const SweepTile t = sweep_tile(d, BX, BY, b);
+  if (!t.valid) return;
+  const int li = (int)threadIdx.x, lj = (int)threadIdx.y;
+  const int i = t.i0 + li, j = t.j0 + lj, k = t.k;
+  const bool ok = i <= d.n1 && j <= d.n2;
+  extern __shared__ __align__(16) unsigned char sweep_lds[];
+  T* const L = reinterpret_cast<T*>(sweep_lds);
+  const T* const q = L + (lj + SH::LO) * SH::LW + li + SH::LO;
+  const int tid = lj * BX + li;
+  T* const X = L + NV * SH::PLANE + tid;  // this thread's slot of the exchange, [NEXCH][BY][BX]
+  const int ib = t.i0 - SH::LO, jb = t.j0 - SH::LO;
+  // the cells this thread writes: a divergence needs the next thread of the row and the next
+  // row, an EMF the previous ones
+  const bool wd = i >= 0 && i < d.n1 && j >= 0 && j < d.n2 && li < BX - 1 && lj < BY - 1;
+  const bool we = ok && i >= 0 && j >= 0 && li > 0 && lj > 0;
+  const bool axis = (a.polar_lo && j == 0) || (a.polar_hi && j == d.n2);
+  const bool in1 = i >= 0 && i < d.n1, in2 = j >= 0 && j < d.n2;
+  // threads beyond the grid, and on faces no one asks for, compute on the nearest cell's data
+  // and write nothing: no branch splits a face's arithmetic
+  const int ic = min(i, d.n1), jc = min(j, d.n2);
+  const unsigned pb = (unsigned)d.s3 * (unsigned)sizeof(double);
+  const int toff = tab_of(d, jc, ic);
+  constexpr bool AXI = GEO == GEO_AXI;
+  // stage the plane: cells [ib, ib + LW) x [jb, jb + LH), those inside the padded state
+  // (cells outside it are never read: faces start at cell 0 and end at n)
+#pragma unroll
+  for (int e0 = 0; e0 < SH::PLANE; e0 += SH::NTHR) {
+    const int e = e0 + tid;
+    const int ej = e / SH::LW, ei = e - ej * SH::LW;
+    const int gi = ib + ei, gj = jb + ej;
+    if (e < SH::PLANE && gi >= -NG && gi < d.n1 + NG && gj >= -NG && gj < d.n2 + NG) {
+      const unsigned c = (unsigned)cell_of(d, k, gj, gi) * (unsigned)sizeof(double);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) L[v * SH::PLANE + e] = (T)buf_f64(a.P + (size_t)v * d.sv, c);
     }
   }
   __syncthreads();
+  const int c = cell_of(d, k, j, i);
+  const unsigned cb = (unsigned)cell_of(d, k, jc, ic) * (unsigned)sizeof(double);
+  const size_t sv = (size_t)d.sv;
+  const bool hydro = k >= 0 && k < d.n3;
+  auto geo = [&](int D, const T* tab, FaceGeo<T>& g) {
+    if constexpr (GEO == GEO_CKS) cks_face_geo(box, D, ic, jc, k, g);
+    else load_face_geo<AXI>(g, face_plane(tab, d, k), d.ts, toff);
+  };
+  T f[7];
+  T g2 = T(0);  // x3 fluxes of B1 of this cell and the one before it
+  if (k >= 0) {
+    FaceGeo<T> g;
+    geo(3, a.t3, g);
+    FaceSide<T> SL, SR;
+    face_sides<3, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
+    // the speeds wait in slots that the exchange uses later
+    face_flux<3, AXI, CTOP>(SL, SR, g, a.gam, f, X, in1 && in2);
+    if (wd) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) a.out.f3[v * sv + c] = f[v];
+    }
+    g2 = f[5] + prev_lane(f[5]);
+    X[6 * SH::NTHR] = f[6];
+  }
+  FACE_FENCE;
+  double acc[5];
+  {
+    FaceGeo<T> g;
+    geo(1, a.t1, g);
+    FaceSide<T> SL, SR;
+    face_sides<1, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
+    face_flux<1, AXI, CTOP>(SL, SR, g, a.gam, f, X + SH::NTHR, ok && i >= 0 && in2 && hydro);
+    // no mass enters through an outflow boundary: the rest-mass flux through
+    // the inner radial face is at most 0, through the outer one at least 0
+    if (d.out_lo && i == 0) f[0] = fmin(f[0], T(0));
+    if (d.out_hi && i == d.n1) f[0] = fmax(f[0], T(0));
+    if (a.mass && we && hydro) a.mass[c] = f[0];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) acc[v] = ((double)next_lane(f[v]) - (double)f[v]) * a.idx1;
+    X[5 * SH::NTHR] = f[5];
+    if (we) {
+      a.out.b[sv + c] = f[6];
+      if (k >= 0) a.out.e[sv + c] = g2 - f[6];
+    }
+  }
+  FACE_FENCE;
+  {
+    FaceGeo<T> g;
+    geo(2, a.t2, g);
+    FaceSide<T> SL, SR;
+    face_sides<2, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
+    face_flux<2, AXI, CTOP>(SL, SR, g, a.gam, f, X + 2 * SH::NTHR, ok && j >= 0 && in1 && hydro);
+    if (a.mass && we && hydro) a.mass[sv + c] = f[0];
+    if (axis) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) f[v] = T(0);
+      f[6] = T(0);
+    }
+  }
+  FACE_FENCE;
+  const T g3 = prev_lane(f[5]);
   double c1 = 0.0, c2 = 0.0, c3 = 0.0;
-  if (ok && i >= 0) c1 = one_face<1, RECON, T, GEO>(d, P, pt, t1, box, F1, gam, i, j, k);
-  if (ok && j >= 0) c2 = one_face<2, RECON, T, GEO>(d, P, pt, t2, box, F2, gam, i, j, k);
-  if (ok && k >= 0) c3 = one_face<3, RECON, T, GEO>(d, P, pt, t3, box, F3, gam, i, j, k);
-  if (ctop) block_max3_to(c1, c2, c3, ctop);
+  if (CTOP) {
+    if (k >= 0) c3 = (double)X[0];
+    c1 = (double)X[SH::NTHR];
+    c2 = (double)X[2 * SH::NTHR];
+  }
+  // rows exchange what the next and previous ones need
+#pragma unroll
+  for (int v = 0; v < 5; ++v) X[v * SH::NTHR] = f[v];
+  __syncthreads();
+  if (wd && hydro) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) a.out.D[v * sv + c] = fma(-((double)X[v * SH::NTHR + BX] - (double)f[v]), a.idx2, -acc[v]);
+  }
+  if (we) {
+    a.out.b[c] = f[6];
+    // four times the EMFs of the zone's lower edges (0 on a polar axis)
+    if (hydro) a.out.e[2 * sv + c] = axis ? T(0) : ((X[5 * SH::NTHR] + X[5 * SH::NTHR - BX]) - f[5]) - g3;
+    if (k >= 0) a.out.e[c] = axis ? T(0) : f[6] - (X[6 * SH::NTHR] + X[6 * SH::NTHR - BX]);
+  }
+  if (CTOP) block_max3_to(c1, c2, c3, ctop);
 }
 
-template <int RECON, typename T, int GEO>
-__global__ __launch_bounds__(512) void sweep_kernel(Dims d, const double* __restrict__ P, const T* __restrict__ t1,
-                                                    const T* __restrict__ t2, const T* __restrict__ t3, CksBox box,
-                                                    T* __restrict__ F1, T* __restrict__ F2, T* __restrict__ F3, T gam,
-                                                    unsigned long long* ctop) {
-  sweep_body<RECON, T, GEO>(d, P, t1, t2, t3, box, F1, F2, F3, gam, (int)blockIdx.x, ctop);
+template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
+__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_kernel(Dims d, SweepArgs<T> a, CksBox box,
+                                                                          unsigned long long* ctop) {
+  sweep_body<RECON, T, GEO, CTOP, BX, BY>(d, a, box, (int)blockIdx.x, ctop);
 }
 
 template <typename T>
@@ -188,22 +297,23 @@ struct FaceTables<float> {
 };
 
 // every job of a batch in one grid; predictor sweeps P, corrector sweeps P_h
-template <int RECON, typename T, int GEO>
-__global__ __launch_bounds__(512) void sweep_batch_kernel(BatchView bv, int corrector, int want_ctop) {
+template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
+__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_batch_kernel(BatchView bv, int corrector) {
   const int* offs = bv.offs + PH_SWEEP * (bv.njobs + 1);
   const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
   const JobDesc& J = bv.jobs[jb];
   const CksBox none{};
-  sweep_body<RECON, T, GEO>(J.d, global_ptr(corrector ? J.Ph : J.P), global_ptr(FaceTables<T>::f1(J.t)),
-                       global_ptr(FaceTables<T>::f2(J.t)), global_ptr(FaceTables<T>::f3(J.t)), none,
-                       global_ptr((T*)J.F[0]), global_ptr((T*)J.F[1]), global_ptr((T*)J.F[2]), (T)J.p.gam,
-                       (int)blockIdx.x - offs[jb], want_ctop ? global_ptr(J.ctr->ctop) : nullptr);
+  const FluxOut<T> out = flux_out<T>(global_ptr((unsigned char*)J.F), J.d.sv);
+  const SweepArgs<T> a{global_ptr(corrector ? J.Ph : J.P), global_ptr(FaceTables<T>::f1(J.t)),
+                       global_ptr(FaceTables<T>::f2(J.t)), global_ptr(FaceTables<T>::f3(J.t)), out,
+                       J.E ? out.m : nullptr, J.up.idx1, J.up.idx2, J.up.idx3, (T)J.p.gam, J.up.polar_lo,
+                       J.up.polar_hi};
+  sweep_body<RECON, T, GEO, CTOP, BX, BY>(J.d, a, none, (int)blockIdx.x - offs[jb], CTOP ? global_ptr(J.ctr->ctop) : nullptr);
 }
 
-template <int RECON, typename T>
-size_t tile_bytes(int stx, int sty) {
-  return (size_t)NV * (stx + halo_lo<RECON>() + halo_hi<RECON>()) * (sty + halo_lo<RECON>() + halo_hi<RECON>()) *
-         sizeof(T);
+template <int RECON, typename T, int BX, int BY>
+constexpr size_t tile_bytes() {
+  return ((size_t)NV * PlaneShape<RECON, BX, BY>::PLANE + (size_t)NEXCH * BX * BY) * sizeof(T);
 }
 
 // A kernel may use more dynamic LDS than the default 64 KiB only once the
@@ -221,17 +331,37 @@ hipError_t allow_lds(size_t bytes) {
   return e;
 }
 
+// f(std::integral_constant BX, BY) for the block shape in d
+template <int RECON, typename T, typename F>
+hipError_t with_shape(const Dims& d, F f) {
+  constexpr bool MIXED = std::is_same<T, float>::value;
+  if (d.sbx == SMALL_BX && d.sby == SMALL_BY)
+    return f(std::integral_constant<int, SMALL_BX>(), std::integral_constant<int, SMALL_BY>());
+  return f(std::integral_constant<int, large_bx(RECON, MIXED)>(), std::integral_constant<int, large_by(RECON, MIXED)>());
+}
+
+template <int RECON, typename T, int GEO, bool CTOP>
+hipError_t launch_ctop(const Dims& d, const SweepArgs<T>& a, const CksBox& box, unsigned long long* ctop,
+                       hipStream_t s) {
+  return with_shape<RECON, T>(d, [&](auto bx, auto by) {
+    constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
+    constexpr size_t lds = tile_bytes<RECON, T, BX, BY>();
+    const hipError_t e = allow_lds<sweep_kernel<RECON, T, GEO, CTOP, BX, BY>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sweep_kernel<RECON, T, GEO, CTOP, BX, BY>), dim3(sweep_blocks(d)), dim3(BX, BY, 1), lds, s, d, a,
+                       box, ctop);
+    return hipGetLastError();
+  });
+}
+
 template <int RECON, typename T, int GEO>
-hipError_t launch_geo(const Dims& d, const Tables& t, const CksBox& box, double gam, const double* P,
-                      void* const* F, unsigned long long* ctop, hipStream_t s) {
-  const unsigned nblk = sweep_blocks(d);
-  const size_t lds = tile_bytes<RECON, T>(d.stx, d.sty);
-  const hipError_t e = allow_lds<sweep_kernel<RECON, T, GEO>>(lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((sweep_kernel<RECON, T, GEO>), dim3(nblk), dim3(d.stx, d.sty, 1), lds, s, d, P,
-                     FaceTables<T>::f1(t), FaceTables<T>::f2(t), FaceTables<T>::f3(t), box, (T*)F[0], (T*)F[1],
-                     (T*)F[2], (T)gam, ctop);
-  return hipGetLastError();
+hipError_t launch_geo(const Dims& d, const Tables& t, const UpdateParams& up, const CksBox& box, const double* P,
+                      void* F, bool mass, unsigned long long* ctop, hipStream_t s) {
+  const FluxOut<T> out = flux_out<T>((unsigned char*)F, d.sv);
+  const SweepArgs<T> a{P,       FaceTables<T>::f1(t), FaceTables<T>::f2(t), FaceTables<T>::f3(t), out, mass ? out.m : nullptr,
+                       up.idx1, up.idx2,              up.idx3,              (T)up.gam,            up.polar_lo, up.polar_hi};
+  if (ctop) return launch_ctop<RECON, T, GEO, true>(d, a, box, ctop, s);
+  return launch_ctop<RECON, T, GEO, false>(d, a, box, ctop, s);
 }
 
 // Cartesian Kerr-Schild in FP64 computes its face geometry instead of
@@ -239,52 +369,63 @@ hipError_t launch_geo(const Dims& d, const Tables& t, const CksBox& box, double 
 // FP32 pass reads the float tables, cheaper than evaluating the metric in
 // FP64; the other coordinates read their 2D tables
 template <int RECON, typename T>
-hipError_t launch_for(const grmhd_problem& p, const Dims& d, const Tables& t, const double* P, void* const* F,
-                      unsigned long long* ctop, hipStream_t s) {
-  if (p.coords != GRMHD_KERR_CKS) return launch_geo<RECON, T, GEO_AXI>(d, t, CksBox{}, p.gam, P, F, ctop, s);
-  if constexpr (std::is_same<T, double>::value) return launch_geo<RECON, T, GEO_CKS>(d, t, cks_box(p), p.gam, P, F, ctop, s);
-  else return launch_geo<RECON, T, GEO_TABLE>(d, t, CksBox{}, p.gam, P, F, ctop, s);
+hipError_t launch_for(const grmhd_problem& p, const Dims& d, const Tables& t, const UpdateParams& up, const double* P,
+                      void* F, bool mass, unsigned long long* ctop, hipStream_t s) {
+  if (p.coords != GRMHD_KERR_CKS) return launch_geo<RECON, T, GEO_AXI>(d, t, up, CksBox{}, P, F, mass, ctop, s);
+  if constexpr (std::is_same<T, double>::value)
+    return launch_geo<RECON, T, GEO_CKS>(d, t, up, cks_box(p), P, F, mass, ctop, s);
+  else return launch_geo<RECON, T, GEO_TABLE>(d, t, up, CksBox{}, P, F, mass, ctop, s);
 }
 
 // a batch whose jobs all have g_23 = beta^3 = 0 reads the shorter tables (the
 // same bits: the components left out are zeros)
-template <int RECON, typename T, int GEO>
-hipError_t launch_batch_geo(const BatchView& bv, dim3 grd, dim3 blk, int c, int w, hipStream_t s) {
-  const size_t lds = tile_bytes<RECON, T>(bv.stx, bv.sty);
-  const hipError_t e = allow_lds<sweep_batch_kernel<RECON, T, GEO>>(lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((sweep_batch_kernel<RECON, T, GEO>), grd, blk, lds, s, bv, c, w);
-  return hipGetLastError();
+template <int RECON, typename T, int GEO, bool CTOP>
+hipError_t launch_batch_ctop(const BatchView& bv, const Dims& d, dim3 grd, int c, hipStream_t s) {
+  return with_shape<RECON, T>(d, [&](auto bx, auto by) {
+    constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
+    constexpr size_t lds = tile_bytes<RECON, T, BX, BY>();
+    const hipError_t e = allow_lds<sweep_batch_kernel<RECON, T, GEO, CTOP, BX, BY>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sweep_batch_kernel<RECON, T, GEO, CTOP, BX, BY>), grd, dim3(BX, BY, 1), lds, s, bv, c);
+    return hipGetLastError();
+  });
 }
 
 template <int RECON, typename T>
-hipError_t launch_batch_for(const BatchView& bv, dim3 grd, dim3 blk, int c, int w, hipStream_t s) {
-  if (bv.axi) return launch_batch_geo<RECON, T, GEO_AXI>(bv, grd, blk, c, w, s);
-  return launch_batch_geo<RECON, T, GEO_TABLE>(bv, grd, blk, c, w, s);
+hipError_t launch_batch_for(const BatchView& bv, dim3 grd, int c, bool ctop, hipStream_t s) {
+  Dims d{};
+  d.sbx = bv.sbx;
+  d.sby = bv.sby;
+  if (bv.axi)
+    return ctop ? launch_batch_ctop<RECON, T, GEO_AXI, true>(bv, d, grd, c, s)
+                : launch_batch_ctop<RECON, T, GEO_AXI, false>(bv, d, grd, c, s);
+  return ctop ? launch_batch_ctop<RECON, T, GEO_TABLE, true>(bv, d, grd, c, s)
+              : launch_batch_ctop<RECON, T, GEO_TABLE, false>(bv, d, grd, c, s);
 }
 
 }  // namespace
 
-unsigned sweep_blocks(const Dims& d) { return xcd_grid(d.n1 + 2, d.n2 + 2, d.n3 + 2, d.stx, d.sty); }
+unsigned sweep_blocks(const Dims& d) { return (unsigned)sweep_grid(d, d.sbx, d.sby); }
 
-hipError_t launch_sweeps(const grmhd_problem& p, bool mixed, const Dims& d, const Tables& t, const double* P,
-                         void* const* F, unsigned long long* ctop, hipStream_t s) {
+hipError_t launch_sweeps(const grmhd_problem& p, bool mixed, const Dims& d, const Tables& t, const UpdateParams& up,
+                         const double* P, void* F, bool mass, unsigned long long* ctop, hipStream_t s) {
   if (mixed) {
-    if (p.recon == GRMHD_RECON_MC) return launch_for<GRMHD_RECON_MC, float>(p, d, t, P, F, ctop, s);
-    return launch_for<GRMHD_RECON_WENO5, float>(p, d, t, P, F, ctop, s);
+    if (p.recon == GRMHD_RECON_MC) return launch_for<GRMHD_RECON_MC, float>(p, d, t, up, P, F, mass, ctop, s);
+    return launch_for<GRMHD_RECON_WENO5, float>(p, d, t, up, P, F, mass, ctop, s);
   }
-  if (p.recon == GRMHD_RECON_MC) return launch_for<GRMHD_RECON_MC, double>(p, d, t, P, F, ctop, s);
-  return launch_for<GRMHD_RECON_WENO5, double>(p, d, t, P, F, ctop, s);
+  if (p.recon == GRMHD_RECON_MC) return launch_for<GRMHD_RECON_MC, double>(p, d, t, up, P, F, mass, ctop, s);
+  return launch_for<GRMHD_RECON_WENO5, double>(p, d, t, up, P, F, mass, ctop, s);
 }
 
 hipError_t launch_batch_sweeps(const BatchView& bv, const int* totals, int recon, bool mixed, bool corrector,
                                bool want_ctop, hipStream_t s) {
-  const dim3 blk(bv.stx, bv.sty, 1), grd(totals[PH_SWEEP]);
-  const int c = corrector ? 1 : 0, w = want_ctop ? 1 : 0;
+  const dim3 grd(totals[PH_SWEEP]);
+  const int c = corrector ? 1 : 0;
+  const bool w = want_ctop;
   if (mixed) {
-    if (recon == GRMHD_RECON_MC) return launch_batch_for<GRMHD_RECON_MC, float>(bv, grd, blk, c, w, s);
-    return launch_batch_for<GRMHD_RECON_WENO5, float>(bv, grd, blk, c, w, s);
+    if (recon == GRMHD_RECON_MC) return launch_batch_for<GRMHD_RECON_MC, float>(bv, grd, c, w, s);
+    return launch_batch_for<GRMHD_RECON_WENO5, float>(bv, grd, c, w, s);
   }
-  if (recon == GRMHD_RECON_MC) return launch_batch_for<GRMHD_RECON_MC, double>(bv, grd, blk, c, w, s);
-  return launch_batch_for<GRMHD_RECON_WENO5, double>(bv, grd, blk, c, w, s);
+  if (recon == GRMHD_RECON_MC) return launch_batch_for<GRMHD_RECON_MC, double>(bv, grd, c, w, s);
+  return launch_batch_for<GRMHD_RECON_WENO5, double>(bv, grd, c, w, s);
 }

@@ -135,22 +135,13 @@ __device__ void apply_floors(double* P, const Geo<double>& g, double rfl, double
   P[1] = u;
 }
 
-template <typename TF>
-struct FluxView {
-  const TF* F;
-  int sv;
-  __device__ double at(int v, int c) const { return (double)F[v * sv + c]; }
-  __device__ TF raw(int v, int c) const { return F[v * sv + c]; }
-};
-
 // b: block index within this job's grid (the update tile d.utx x d.uty, XCD-aware order)
 // CKS: the centre metric of Cartesian Kerr-Schild computed in closed form
 // (the values of the centre table) instead of read; the connection and the
 // floor scales still come from the table
 template <typename TF, bool EARLY_PS = false, bool CKS = false>
 __device__ void update_body(const Dims& d, const double* __restrict__ cent, const CksBox& box, const UpdateParams& up,
-                            const TF* __restrict__ F1p, const TF* __restrict__ F2p, const TF* __restrict__ F3p,
-                            const double* Pb, const double* __restrict__ Ps, double* Pout,
+                            const FluxOut<TF>& F, const double* Pb, const double* __restrict__ Ps, double* Pout,
                             int8_t* __restrict__ flags, double dt, Counters* ctr, int b) {
   const TileK tk = xcd_tile_k(b, d.utx, d.uty, d.n1, d.n3);
   const int i = tk.i0 + threadIdx.x;
@@ -159,50 +150,29 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
   int failed = 0;
   if (tk.valid && i < d.n1 && j < d.n2) {
     const int c = cell_of(d, k, j, i);
-    const FluxView<TF> F1{F1p, d.sv}, F2{F2p, d.sv}, F3{F3p, d.sv};
-    const int s1 = 1, s2 = d.s2, s3 = d.s3;
-    const bool pl = up.polar_lo && j == 0;
-    const bool ph = up.polar_hi && j == d.n2 - 1;
-
     double ps[NV];
     if (EARLY_PS) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) ps[v] = Ps[v * d.sv + c];
     }
     double rhs[NV];
-    // hydrodynamic flux divergence
+    const size_t sv = (size_t)d.sv;
+    const int s2 = d.s2, s3 = d.s3;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      const double f2m = pl ? 0.0 : F2.at(v, c);
-      const double f2p = ph ? 0.0 : F2.at(v, c + s2);
-      rhs[v] = -((F1.at(v, c + s1) - F1.at(v, c)) * up.idx1 + (f2p - f2m) * up.idx2 +
-                 (F3.at(v, c + s3) - F3.at(v, c)) * up.idx3);
+      const TF* f = F.f3 + v * sv + c;
+      rhs[v] = fma(-((double)f[s3] - (double)f[0]), up.idx3, F.D[v * sv + c]);
     }
-    // Flux-CT: edge EMFs (in the flux precision)
-    const TF q = TF(0.25), h = TF(0.5);
-    // emf3 at edge (ii-1/2, jj-1/2, k), for ii in {i, i+1}, jj in {j, j+1}
-    auto e3 = [&](int di, int dj) -> TF {
-      const int jj = j + dj;
-      if ((up.polar_lo && jj == 0) || (up.polar_hi && jj == d.n2)) return TF(0);
-      const int cc = c + di * s1 + dj * s2;
-      return q * (F1.raw(6, cc) + F1.raw(6, cc - s2) - F2.raw(5, cc) - F2.raw(5, cc - s1));
-    };
-    // emf1 at edge (i, jj-1/2, kk-1/2)
-    auto e1 = [&](int dj, int dk) -> TF {
-      const int jj = j + dj;
-      if ((up.polar_lo && jj == 0) || (up.polar_hi && jj == d.n2)) return TF(0);
-      const int cc = c + dj * s2 + dk * s3;
-      return q * (F2.raw(7, cc) + F2.raw(7, cc - s3) - F3.raw(6, cc) - F3.raw(6, cc - s2));
-    };
-    // emf2 at edge (ii-1/2, j, kk-1/2)
-    auto e2 = [&](int di, int dk) -> TF {
-      const int cc = c + di * s1 + dk * s3;
-      return q * (F3.raw(5, cc) + F3.raw(5, cc - s1) - F1.raw(7, cc) - F1.raw(7, cc - s3));
-    };
+    // Flux-CT: the zone's twelve edge EMFs (times four; in the flux precision)
     {
-      const TF e3_00 = e3(0, 0), e3_10 = e3(1, 0), e3_01 = e3(0, 1), e3_11 = e3(1, 1);
-      const TF e1_00 = e1(0, 0), e1_10 = e1(1, 0), e1_01 = e1(0, 1), e1_11 = e1(1, 1);
-      const TF e2_00 = e2(0, 0), e2_10 = e2(1, 0), e2_01 = e2(0, 1), e2_11 = e2(1, 1);
+      const TF *E1 = F.e, *E2 = F.e + sv, *E3 = F.e + 2 * sv, *b2 = F.b, *b1 = F.b + sv;
+      const TF e3_00 = E3[c], e3_10 = E3[c + 1], e3_01 = E3[c + s2], e3_11 = E3[c + s2 + 1];
+      const TF e1_00 = E1[c] + b2[c - s3], e1_10 = E1[c + s2] + b2[c + s2 - s3];
+      const TF e1_01 = E1[c + s3] + b2[c], e1_11 = E1[c + s2 + s3] + b2[c + s2];
+      const TF e2_00 = E2[c] - b1[c - s3], e2_10 = E2[c + 1] - b1[c + 1 - s3];
+      const TF e2_01 = E2[c + s3] - b1[c], e2_11 = E2[c + s3 + 1] - b1[c + 1];
+      // the face's field flux is half the sum of the two EMFs bounding it
+      const TF h = TF(0.125);
       const double f1b2m = (double)(h * (e3_00 + e3_01)), f1b2p = (double)(h * (e3_10 + e3_11));
       const double f1b3m = (double)(-h * (e2_00 + e2_01)), f1b3p = (double)(-h * (e2_10 + e2_11));
       const double f2b1m = (double)(-h * (e3_00 + e3_10)), f2b1p = (double)(-h * (e3_01 + e3_11));
@@ -277,14 +247,13 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
 // are the bound).
 template <typename TF, bool DEV_DT, bool CKS = false>
 __global__ __launch_bounds__(256, 3) void update_kernel(Dims d, const double* __restrict__ cent, CksBox box, UpdateParams up,
-                                                     const TF* __restrict__ F1, const TF* __restrict__ F2,
-                                                     const TF* __restrict__ F3, const double* Pb,
+                                                     FluxOut<TF> F, const double* Pb,
                                                      const double* __restrict__ Ps, double* Pout,
                                                      int8_t* __restrict__ flags, double dt,
                                                      const double* __restrict__ dt_dev, double dt_scale,
                                                      Counters* ctr) {
   if (DEV_DT) dt = dt_scale * *dt_dev;
-  update_body<TF, false, CKS>(d, cent, box, up, F1, F2, F3, Pb, Ps, Pout, flags, dt, ctr, (int)blockIdx.x);
+  update_body<TF, false, CKS>(d, cent, box, up, F, Pb, Ps, Pout, flags, dt, ctr, (int)blockIdx.x);
 }
 
 // every job of a batch: predictor P -> P_h with dt/2, corrector (P, P_h) -> P with dt
@@ -296,8 +265,7 @@ __global__ __launch_bounds__(256, 3) void update_batch_kernel(BatchView bv, int 
   const double dt = corrector ? *J.dt : 0.5 * *J.dt;
   // the FP64 batch variant runs faster with the source state loaded first (and
   // without spilling); the float-flux one and the single-job kernels slower
-  update_body<TF, std::is_same<TF, double>::value>(J.d, global_ptr(J.t.cent), CksBox{}, J.up, global_ptr((const TF*)J.F[0]), global_ptr((const TF*)J.F[1]),
-                  global_ptr((const TF*)J.F[2]), global_ptr(J.P), global_ptr(corrector ? J.Ph : J.P),
+  update_body<TF, std::is_same<TF, double>::value>(J.d, global_ptr(J.t.cent), CksBox{}, J.up, flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv), global_ptr(J.P), global_ptr(corrector ? J.Ph : J.P),
                   global_ptr(corrector ? J.P : J.Ph), global_ptr(J.flags), dt, global_ptr(J.ctr),
                   (int)blockIdx.x - offs[jb]);
 }
@@ -425,40 +393,40 @@ __global__ __launch_bounds__(256) void u2p_kernel(Dims d, const double* __restri
 
 }  // namespace
 
-hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const UpdateParams& up, const void* F1,
-                         const void* F2, const void* F3, const double* Pb, const double* Ps, double* Pout,
+hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const UpdateParams& up, const void* F,
+                         const double* Pb, const double* Ps, double* Pout,
                          int8_t* flags, double dt, const double* dt_dev, double dt_scale, Counters* ctr,
                          hipStream_t s, const grmhd_problem* cks) {
   const unsigned nblk = xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty);
   dim3 blk(d.utx, d.uty, 1), grd(nblk);
   const CksBox box = cks ? cks_box(*cks) : CksBox{};
   if (mixed) {
-    const float *f1 = (const float*)F1, *f2 = (const float*)F2, *f3 = (const float*)F3;
+    const FluxOut<float> f = flux_out<float>((unsigned char*)F, d.sv);
     if (cks && dt_dev)
-      hipLaunchKernelGGL((update_kernel<float, true, true>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps,
+      hipLaunchKernelGGL((update_kernel<float, true, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
                          Pout, flags, dt, dt_dev, dt_scale, ctr);
     else if (cks)
-      hipLaunchKernelGGL((update_kernel<float, false, true>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps,
+      hipLaunchKernelGGL((update_kernel<float, false, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
                          Pout, flags, dt, dt_dev, dt_scale, ctr);
     else if (dt_dev)
-      hipLaunchKernelGGL((update_kernel<float, true>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps, Pout,
+      hipLaunchKernelGGL((update_kernel<float, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
                          flags, dt, dt_dev, dt_scale, ctr);
     else
-      hipLaunchKernelGGL((update_kernel<float, false>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps, Pout,
+      hipLaunchKernelGGL((update_kernel<float, false>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
                          flags, dt, dt_dev, dt_scale, ctr);
   } else {
-    const double *f1 = (const double*)F1, *f2 = (const double*)F2, *f3 = (const double*)F3;
+    const FluxOut<double> f = flux_out<double>((unsigned char*)F, d.sv);
     if (cks && dt_dev)
-      hipLaunchKernelGGL((update_kernel<double, true, true>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps,
+      hipLaunchKernelGGL((update_kernel<double, true, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
                          Pout, flags, dt, dt_dev, dt_scale, ctr);
     else if (cks)
-      hipLaunchKernelGGL((update_kernel<double, false, true>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps,
+      hipLaunchKernelGGL((update_kernel<double, false, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
                          Pout, flags, dt, dt_dev, dt_scale, ctr);
     else if (dt_dev)
-      hipLaunchKernelGGL((update_kernel<double, true>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps, Pout,
+      hipLaunchKernelGGL((update_kernel<double, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
                          flags, dt, dt_dev, dt_scale, ctr);
     else
-      hipLaunchKernelGGL((update_kernel<double, false>), grd, blk, 0, s, d, t.cent, box, up, f1, f2, f3, Pb, Ps, Pout,
+      hipLaunchKernelGGL((update_kernel<double, false>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
                          flags, dt, dt_dev, dt_scale, ctr);
   }
   return hipGetLastError();
