@@ -12,6 +12,7 @@
 #include <string>
 #include <vector>
 
+#include "cks_geometry.h"
 #include "ctx.h"
 
 namespace {
@@ -133,6 +134,7 @@ Dims make_dims(const grmhd_problem& p) {
   pick_sweep_shape(d, p);
   d.out_lo = p.bc[0][0] == GRMHD_BC_OUTFLOW;
   d.out_hi = p.bc[0][1] == GRMHD_BC_OUTFLOW;
+  d.box = cks_box(p);
   return d;
 }
 
@@ -204,8 +206,7 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
   {
     ProfScope ps(c->prof, s, GRMHD_K_UPDATE);
     HIP_OR_FAIL(c, launch_update(c->mixed, c->d, c->t, c->up, c->F, Pb, Ps, Pout,
-                                 fl, dt, dt_dev, dt_scale, c->ctr, s,
-                                 c->p.coords == GRMHD_KERR_CKS ? &c->p : nullptr),
+                                 fl, dt, dt_dev, dt_scale, c->ctr, s),
                 "update");
   }
   if (fix) {
@@ -411,6 +412,11 @@ int grmhd_init(const grmhd_problem* p, void* hip_stream, grmhd_ctx** out) {
   c->up.idx1 = 1.0 / c->dx[0];
   c->up.idx2 = 1.0 / c->dx[1];
   c->up.idx3 = 1.0 / c->dx[2];
+  c->up.igam = 1.0 / p->gam;
+  c->up.gf = (p->gam - 1.0) / p->gam;
+  c->up.isigma = 1.0 / p->sigma_max;
+  c->up.iuorho = 1.0 / p->uorho_max;
+  c->up.beta_fl = p->beta_min / (2.0 * (p->gam - 1.0));
   c->up.floors = p->floors ? 1 : 0;
   c->up.polar_lo = p->bc[1][0] == GRMHD_BC_POLAR;
   c->up.polar_hi = p->bc[1][1] == GRMHD_BC_POLAR;

@@ -13,6 +13,7 @@
 //               into the half-step state).
 #include <mutex>
 
+#include "cks_geometry.h"
 #include "kernels.h"
 
 namespace {
@@ -32,19 +33,20 @@ __device__ inline int wrap(int x, int n) {
 // c = alpha g^{t1}, Gamma the positive root of
 // (1 - g11 c^2) G^2 - 2 c (g12 v2 + g13 v3) G - (1 + g_jk v^j v^k) = 0
 // (q: the ghost's primitives)
-__device__ void inflow_fix(double* q, const double* cent, int ts, int toff, int side) {
-  Geo<double> g;
-  load_geo(g, cent, ts, toff);
+__device__ void inflow_fix(double* q, const double* ct, const Dims& d, int off, int side) {
+  const double2 a = zone_pair(ct, d, off, C_G11), b = zone_pair(ct, d, off, C_G13), e = zone_pair(ct, d, off, C_G33),
+                h = zone_pair(ct, d, off, C_B1), f = zone_pair(ct, d, off, C_IALPHA);
+  const double g11 = a.x, g12 = a.y, g13 = b.x, g22 = b.y, g33 = e.x;  // g_23 = 0: outflow needs MKS or FMKS
   const double v1 = q[2], v2 = q[3], v3 = q[4];
-  const double lor = sqrt(lorentz_sq(g.gcov, v1, v2, v3));
-  const double u1 = v1 - lor * g.alpha * g.gcon[1];
+  const double G = g12 * v2 + g13 * v3;
+  const double H = g22 * v2 * v2 + g33 * v3 * v3;
+  const double lor = sqrt(1.0 + v1 * (g11 * v1 + 2.0 * G) + H);
+  const double c = h.x * f.x;  // alpha g^{t1} = beta^1 / alpha
+  const double u1 = v1 - lor * c;
   const bool bad = side == 0 ? (u1 > 0.0) : (u1 < 0.0);
   if (!bad) return;
-  const double c = g.alpha * g.gcon[1];
-  const double qa = 1.0 - g.gcov[4] * c * c;
+  const double qa = 1.0 - g11 * c * c;
   if (!(qa > 0.0)) return;
-  const double G = g.gcov[5] * v2 + g.gcov[6] * v3;
-  const double H = g.gcov[7] * v2 * v2 + 2.0 * g.gcov[8] * v2 * v3 + g.gcov[9] * v3 * v3;
   const double root = (c * G + sqrt(c * c * G * G + qa * (1.0 + H))) / qa;
   q[2] = c * root;
 }
@@ -106,7 +108,7 @@ __device__ void ghost_cell(const grmhd_problem& p, const Dims& d, const double* 
   double q[NVAR];
   for (int v = 0; v < NVAR; ++v) q[v] = from[v * d.sv + cs];
   if constexpr (!SCALAR) {
-    if (fix_side >= 0) inflow_fix(q, tab_plane(cent, d, sk), d.ts, tab_of(d, sj, i), fix_side);
+    if (fix_side >= 0) inflow_fix(q, pair_plane(cent, d, sk), d, tab_of(d, sj, i), fix_side);
     if (flip) {
       q[3] = -q[3];
       q[6] = -q[6];
@@ -207,7 +209,9 @@ __device__ double divb_at(const grmhd_problem& p, const Dims& d, const double* _
   const int im = wrap(i - 1, d.n1), jm = wrap(j - 1, d.n2), km = wrap(k - 1, d.n3);
   // G_d(kk, jj, ii) = sqrt(-g) B^d
   auto G = [&](int v, int kk, int jj, int ii) {
-    return tab_plane(cent, d, kk)[T_GDET * d.ts + tab_of(d, jj, ii)] * P[(5 + v) * d.sv + cell_of(d, kk, jj, ii)];
+    const double* ct = pair_plane(cent, d, kk);
+    const double gdet = ct[pair_index(d.tk ? K_GDET : C_GDET, (size_t)d.ts, (size_t)tab_of(d, jj, ii))];
+    return gdet * P[(5 + v) * d.sv + cell_of(d, kk, jj, ii)];
   };
   // sum over the two transverse offsets, differencing along the direction
   const double s1 = (G(0, k, j, i) - G(0, k, j, im)) + (G(0, k, jm, i) - G(0, k, jm, im)) +

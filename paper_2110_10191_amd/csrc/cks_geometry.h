@@ -1,6 +1,6 @@
 // Cartesian Kerr-Schild geometry of a point in closed form, for the face
-// tables and the metric part of the centre table, and for the face-flux pass
-// and the update, which compute it instead of reading it. Implementation Notes section: a change of coordinates or background
+// tables, and for the kernels that compute it instead of reading it; and the
+// geometry of a zone centre, wherever it comes from. Implementation Notes section: a change of coordinates or background
 // spacetime only changes the metric evaluation. The metric is
 // g = eta + f l l with f = 2 r^3 / (r^4 + a^2 z^2) and the covector
 // l = (1, (r x + a y)/(r^2 + a^2), (r y - a x)/(r^2 + a^2), z/r), null for
@@ -11,12 +11,6 @@
 #pragma once
 
 #include "common.h"
-
-struct CksBox {
-  double x0[3];  // x1min, x2min, x3min
-  double dx[3];  // zone widths
-  double a;
-};
 
 // on the host, so that every user of the box has the same bits
 inline CksBox cks_box(const grmhd_problem& p) {
@@ -36,35 +30,6 @@ __device__ inline double cks_radius(double x, double y, double z, double a) {
 #pragma clang fp contract(off)
   const double h = 0.5 * (x * x + y * y + z * z - a * a);
   return sqrt(h + sqrt(h * h + a * a * z * z));
-}
-
-// metric, inverse, sqrt(-g) and lapse at the point (x, y, z); double
-// precision, stored as T
-template <typename T>
-__device__ inline void cks_point_geo(double x, double y, double z, double a, Geo<T>& g) {
-#pragma clang fp contract(off)
-  const double r = cks_radius(x, y, z, a);
-  const double r2 = r * r;
-  const double f = 2.0 * r2 * r / (r2 * r2 + a * a * z * z);
-  const double ra = r2 + a * a;
-  const double l[4] = {1.0, (r * x + a * y) / ra, (r * y - a * x) / ra, z / r};
-  const double lu[4] = {-1.0, l[1], l[2], l[3]};
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int n = m; n < 4; ++n) {
-      const double eta = m != n ? 0.0 : (m == 0 ? -1.0 : 1.0);
-      g.gcov[sidx(m, n)] = (T)(f * l[m] * l[n] + eta);
-      g.gcon[sidx(m, n)] = (T)(eta - f * lu[m] * lu[n]);
-    }
-  // sqrt(-g) = 1, held in a register the compiler cannot see through: a
-  // known 1 would let it drop the products with sqrt(-g) and fuse the
-  // remaining operations differently from the same code reading the value
-  // from a table, and the two must round alike
-  double one = 1.0;
-  asm volatile("" : "+v"(one));
-  g.gdet = (T)one;
-  g.alpha = (T)(1.0 / sqrt(1.0 + f));
 }
 
 // at the lower D-face (D = 1..3) of cell (i, j, k), in the 3+1 form of the face
@@ -99,11 +64,82 @@ __device__ inline void cks_face_geo(const CksBox& b, int D, int i, int j, int k,
 }
 
 // at the centre of cell (i, j, k)
-template <typename T>
-__device__ inline void cks_centre_geo(const CksBox& b, int i, int j, int k, Geo<T>& g) {
+__device__ inline void cks_centre_geo(const CksBox& b, int i, int j, int k, ZoneGeo& g) {
 #pragma clang fp contract(off)
   const double x = b.x0[0] + (i + 0.5) * b.dx[0];
   const double y = b.x0[1] + (j + 0.5) * b.dx[1];
   const double z = b.x0[2] + (k + 0.5) * b.dx[2];
-  cks_point_geo(x, y, z, b.a, g);
+  const double a = b.a;
+  const double r = cks_radius(x, y, z, a);
+  const double r2 = r * r;
+  const double f = 2.0 * r2 * r / (r2 * r2 + a * a * z * z);
+  const double ira = 1.0 / (r2 + a * a);
+  const double l1 = (r * x + a * y) * ira, l2 = (r * y - a * x) * ira, l3 = z / r;
+  const double f1 = f * l1, f2 = f * l2, f3 = f * l3;
+  const double ia = sqrt(1.0 + f), al = 1.0 / ia, a2 = al * al;
+  g.g11 = f1 * l1 + 1.0;
+  g.g12 = f1 * l2;
+  g.g13 = f1 * l3;
+  g.g22 = f2 * l2 + 1.0;
+  g.g23 = f2 * l3;
+  g.g33 = f3 * l3 + 1.0;
+  g.alpha = al;
+  g.ialpha = ia;
+  g.b1 = a2 * f1;
+  g.b2 = a2 * f2;
+  g.b3 = a2 * f3;
+  g.h11 = 1.0 - g.b1 * l1;
+  g.h12 = -g.b1 * l2;
+  g.h13 = -g.b1 * l3;
+  g.h22 = 1.0 - g.b2 * l2;
+  g.h23 = -g.b2 * l3;
+  g.h33 = 1.0 - g.b3 * l3;
+  g.gdet = 1.0;
+  g.igdet = 1.0;
 }
+
+// The geometry of a zone: read from the table (MKS, FMKS, Minkowski; ct the
+// plane of pair_plane, off the point of tab_of), evaluated (Cartesian
+// Kerr-Schild), or whichever the context's coordinates call for.
+enum { ZONE_AXI = 0, ZONE_CKS, ZONE_ANY };
+__device__ inline double2 zone_pair(const double* ct, const Dims& d, int off, int c) {
+  return buf_pair(ct + (size_t)c * d.ts, (unsigned)off * 16u);
+}
+template <int Z>
+__device__ inline void zone_geo(ZoneGeo& g, const double* ct, const Dims& d, int off, int i, int j, int k) {
+  if (Z == ZONE_CKS || (Z == ZONE_ANY && d.tk != 0)) {
+    cks_centre_geo(d.box, i, j, k, g);
+    return;
+  }
+  double2 q = zone_pair(ct, d, off, C_G11);
+  g.g11 = q.x, g.g12 = q.y;
+  q = zone_pair(ct, d, off, C_G13);
+  g.g13 = q.x, g.g22 = q.y;
+  q = zone_pair(ct, d, off, C_G33);
+  g.g33 = q.x, g.alpha = q.y;
+  q = zone_pair(ct, d, off, C_B1);
+  g.b1 = q.x, g.b2 = q.y;
+  q = zone_pair(ct, d, off, C_IALPHA);
+  g.ialpha = q.x, g.gdet = q.y;
+  q = zone_pair(ct, d, off, C_H11);
+  g.h11 = q.x, g.h12 = q.y;
+  q = zone_pair(ct, d, off, C_H13);
+  g.h13 = q.x, g.h22 = q.y;
+  q = zone_pair(ct, d, off, C_H23);
+  g.h23 = q.x, g.h33 = q.y;
+  g.igdet = zone_pair(ct, d, off, C_IGDET).x;
+  g.g23 = 0.0;
+  g.b3 = 0.0;
+}
+// rho_fl k and u_fl k^gamma
+template <int Z>
+__device__ inline void zone_floors(double& rfl, double& ufl, const double* ct, const Dims& d, int off) {
+  if (Z == ZONE_CKS || (Z == ZONE_ANY && d.tk != 0)) {
+    rfl = zone_pair(ct, d, off, K_RHOFL & ~1).y;
+    ufl = zone_pair(ct, d, off, K_UFL).x;
+  } else {
+    rfl = zone_pair(ct, d, off, C_RHOFL & ~1).y;
+    ufl = zone_pair(ct, d, off, C_UFL).x;
+  }
+}
+static_assert((K_RHOFL & 1) && !(K_UFL & 1) && (C_RHOFL & 1) && !(C_UFL & 1) && !(C_IGDET & 1), "pairs of the centre table");

@@ -25,17 +25,23 @@
 #define NG GRMHD_NG
 #define NV GRMHD_NVAR
 
-// geometry table components
+// Centre table components, in pairs. MKS, FMKS and Minkowski (g_23 = beta^3 =
+// 0): the 3+1 metric, the source coefficients S_k of x1 and x2 (eight
+// derivatives each, then the pressure's), gamma^ij, 1/sqrt(-g), floor scales.
+// Cartesian Kerr-Schild, whose metric the kernels evaluate themselves: the
+// source coefficients of x1, x2 and x3 (ten derivatives each, then the
+// pressure's), floor scales and sqrt(-g).
+// The source of the momentum along x^n is sqrt(-g) T^km d_n g_km / 2 (zero for
+// the energy, the metric being stationary): the coefficients are sqrt(-g) d_n
+// g_km, halved for k = m, and sqrt(-g) g^km d_n g_km / 2 for the pressure.
 enum {
-  T_GCOV = 0,     // 10: symmetric g_mn, order 00 01 02 03 11 12 13 22 23 33
-  T_GCON = 10,    // 10: g^mn, same order
-  T_GDET = 20,
-  T_ALPHA = 21,
-  T_CONN = 22,    // 40: Gamma^l_mn, l-major, (m,n) in the symmetric order
-  T_RHOFL = 62,   // rho_fl * k        (k = 1/(r^2 (1 + r/10)))
-  T_UFL = 63,     // u_fl * k^gamma
-  N_CENT = 64
+  C_G11 = 0, C_G12, C_G13, C_G22, C_G33, C_ALPHA, C_B1, C_B2, C_IALPHA, C_GDET,
+  C_S1 = 10, C_S2 = 19, C_H11 = 28, C_H12, C_H13, C_H22, C_H23, C_H33, C_IGDET, C_RHOFL, C_UFL,
+  K_S1 = 0, K_S2 = 11, K_S3 = 22, K_RHOFL = 33, K_UFL, K_GDET,
+  N_CENT = 64  // components the centre table has room for
 };
+// the (k, m) of the eight derivatives of an axisymmetric table
+constexpr int AXI_KM[8][2] = {{0, 0}, {0, 1}, {0, 3}, {1, 1}, {1, 2}, {1, 3}, {2, 2}, {3, 3}};
 
 // face table components: the 3+1 form of the metric the face states are
 // written in. g_ij is the spatial metric, beta^i = alpha^2 g^ti the shift,
@@ -54,6 +60,13 @@ __host__ __device__ constexpr int sidx(int m, int n) {
   return (m <= n) ? (m * 4 - (m * (m - 1)) / 2 + (n - m)) : (n * 4 - (n * (n - 1)) / 2 + (m - n));
 }
 
+// Cartesian Kerr-Schild box
+struct CksBox {
+  double x0[3];  // x1min, x2min, x3min
+  double dx[3];  // zone widths
+  double a;
+};
+
 struct Dims {
   int n1, n2, n3;
   int p1, p2, p3;  // padded extents: n1p, n2 + 6, n3 + 6
@@ -66,18 +79,14 @@ struct Dims {
   int sbx, sby;    // and the block shape they use (sweep_shape)
   int utx, uty;    // thread-block tile of the update and fixup
   int out_lo, out_hi;  // x1 lower / upper boundary is an outflow boundary
+  CksBox box;          // Cartesian Kerr-Schild (tk != 0) only
 };
 
 __host__ __device__ inline int cell_of(const Dims& d, int k, int j, int i) {
   return (k + NG) * d.s3 + (j + NG) * d.s2 + (i + NG);
 }
-// point index of (j, i) within one x3 plane of the tables; tab_plane gives the
-// plane of x3 index k (the only plane of 2D tables)
+// point index of (j, i) within one x3 plane of the tables
 __host__ __device__ inline int tab_of(const Dims& d, int j, int i) { return (j + NG) * d.s2 + (i + NG); }
-template <typename S>
-__host__ __device__ inline const S* tab_plane(const S* tab, const Dims& d, int k) {
-  return tab + (size_t)(k + NG) * (size_t)d.tk;
-}
 
 // Loads through a buffer descriptor: a wave-uniform base pointer and one 32-bit
 // byte offset a lane that every array of a kind shares (a component is < 4 GiB,
@@ -95,20 +104,22 @@ __device__ inline double2 buf_pair(const double* base, unsigned off) {
 __device__ inline float2 buf_pair(const float* base, unsigned off) {
   return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(buffer_of(base), (int)off, 0, 0));
 }
-// the pointer form
-template <typename S>
-__device__ inline S ldu(const S* base, unsigned byte_off) {
-  return *(const S*)((const char*)base + byte_off);
+__device__ inline float buf_f32(const float* base, unsigned off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(buffer_of(base), (int)off, 0, 0));
 }
-// The face tables hold their components in pairs: component c of point off
-// at (c & ~1) * ts + 2 * off + (c & 1), so one 16-byte (FP64) or 8-byte
-// (FP32) load per lane brings two components. The centre table keeps one
-// plane per component (c * ts + off).
+// element off of an array
+__device__ inline double buf_at(const double* base, int off) { return buf_f64(base, (unsigned)off * 8u); }
+__device__ inline float buf_at(const float* base, int off) { return buf_f32(base, (unsigned)off * 4u); }
+
+// The tables hold their components in pairs: component c of point off at
+// (c & ~1) * ts + 2 * off + (c & 1), so one 16-byte (FP64) or 8-byte (FP32)
+// load per lane brings two components. pair_plane gives the plane of x3 index
+// k (the only plane of 2D tables).
 __host__ __device__ inline size_t pair_index(int c, size_t ts, size_t off) {
   return (size_t)(c & ~1) * ts + 2 * off + (size_t)(c & 1);
 }
 template <typename S>
-__host__ __device__ inline const S* face_plane(const S* tab, const Dims& d, int k) {
+__host__ __device__ inline const S* pair_plane(const S* tab, const Dims& d, int k) {
   return tab + 2 * (size_t)(k + NG) * (size_t)d.tk;
 }
 template <typename S>
@@ -122,26 +133,6 @@ struct pair_of<float> {
   using type = float2;
 };
 
-template <typename T>
-struct Geo {
-  T gcov[10];
-  T gcon[10];
-  T gdet;
-  T alpha;
-};
-
-// centre table: component c lives at tab + c * ts; off is the point index (tab_of)
-template <typename T, typename S>
-__device__ inline void load_geo(Geo<T>& g, const S* __restrict__ tab, int ts, int off) {
-  const unsigned bo = (unsigned)off * (unsigned)sizeof(S);
-#pragma unroll
-  for (int c = 0; c < 10; ++c) g.gcov[c] = (T)ldu(tab + (size_t)(T_GCOV + c) * ts, bo);
-#pragma unroll
-  for (int c = 0; c < 10; ++c) g.gcon[c] = (T)ldu(tab + (size_t)(T_GCON + c) * ts, bo);
-  g.gdet = (T)ldu(tab + (size_t)T_GDET * ts, bo);
-  g.alpha = (T)ldu(tab + (size_t)T_ALPHA * ts, bo);
-}
-
 // geometry of one face
 template <typename T>
 struct FaceGeo {
@@ -151,7 +142,7 @@ struct FaceGeo {
 };
 
 // from a face table (paired components; off as above, tab the plane from
-// face_plane); AXI: the coordinates have g_23 = beta^3 = 0
+// pair_plane); AXI: the coordinates have g_23 = beta^3 = 0
 template <bool AXI, typename T, typename S>
 __device__ inline void load_face_geo(FaceGeo<T>& g, const S* __restrict__ tab, int ts, int off) {
   using P2 = typename pair_of<S>::type;
@@ -174,25 +165,6 @@ __device__ inline void load_face_geo(FaceGeo<T>& g, const S* __restrict__ tab, i
 
 // ---------------------------------------------------------------------------
 // point physics (HARM variables; units GM = c = 1, b^2/2 magnetic pressure)
-
-template <typename T>
-struct Fluid {
-  T ucon[4], ucov[4], bcon[4], bcov[4];
-  T bsq, p, w;
-};
-
-template <typename T>
-__device__ inline T lower(const T* gcov, const T* vcon, int m) {
-  return gcov[sidx(m, 0)] * vcon[0] + gcov[sidx(m, 1)] * vcon[1] + gcov[sidx(m, 2)] * vcon[2] +
-         gcov[sidx(m, 3)] * vcon[3];
-}
-
-// Gamma^2 = 1 + g_ij u~^i u~^j
-template <typename T>
-__device__ inline T lorentz_sq(const T* gcov, T v1, T v2, T v3) {
-  return T(1) + gcov[4] * v1 * v1 + gcov[7] * v2 * v2 + gcov[9] * v3 * v3 +
-         T(2) * (gcov[5] * v1 * v2 + gcov[6] * v1 * v3 + gcov[8] * v2 * v3);
-}
 
 // 1/sqrt(x), 1/x and sqrt(x) to within about one unit in the last place,
 // without the scaling and fix-up steps of the IEEE sequences: the hardware
@@ -227,56 +199,6 @@ __device__ inline double sqrt_full(double x) {
 }
 __device__ inline float sqrt_full(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// the fluid four-vectors of primitives P
-template <typename T>
-__device__ inline void fluid_state(const T* P, const Geo<T>& g, T gam, Fluid<T>& f) {
-  const T l2 = lorentz_sq(g.gcov, P[2], P[3], P[4]);
-  const T lor = sqrt(l2);
-  f.ucon[0] = lor / g.alpha;
-  const T la = lor * g.alpha;
-  f.ucon[1] = P[2] - la * g.gcon[1];
-  f.ucon[2] = P[3] - la * g.gcon[2];
-  f.ucon[3] = P[4] - la * g.gcon[3];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) f.ucov[m] = lower(g.gcov, f.ucon, m);
-  const T bt = P[5] * f.ucov[1] + P[6] * f.ucov[2] + P[7] * f.ucov[3];
-  const T iut = T(1) / f.ucon[0];
-  f.bcon[0] = bt;
-  f.bcon[1] = (P[5] + bt * f.ucon[1]) * iut;
-  f.bcon[2] = (P[6] + bt * f.ucon[2]) * iut;
-  f.bcon[3] = (P[7] + bt * f.ucon[3]) * iut;
-#pragma unroll
-  for (int m = 0; m < 4; ++m) f.bcov[m] = lower(g.gcov, f.bcon, m);
-  f.bsq = f.bcon[0] * f.bcov[0] + f.bcon[1] * f.bcov[1] + f.bcon[2] * f.bcov[2] + f.bcon[3] * f.bcov[3];
-  f.p = (gam - T(1)) * P[1];
-  f.w = P[0] + P[1] + f.p;
-}
-
-// sqrt(-g) F^D for D = 1..3, or U for D = 0 (B part sqrt(-g) B exactly).
-// Energy component carries the rest-mass flux: T^D_t + rho u^D.
-template <int D, typename T>
-__device__ inline void flux_of(const T* P, const Fluid<T>& f, T gdet, T* F) {
-  const T ud = f.ucon[D];
-  const T mass = P[0] * ud;
-  const T eb = (f.w + f.bsq) * ud;
-  const T pt = f.p + T(0.5) * f.bsq;
-  const T bd = f.bcon[D];
-  F[0] = gdet * mass;
-  F[1] = gdet * (eb * f.ucov[0] - bd * f.bcov[0] + (D == 0 ? pt : T(0)) + mass);
-  F[2] = gdet * (eb * f.ucov[1] - bd * f.bcov[1] + (D == 1 ? pt : T(0)));
-  F[3] = gdet * (eb * f.ucov[2] - bd * f.bcov[2] + (D == 2 ? pt : T(0)));
-  F[4] = gdet * (eb * f.ucov[3] - bd * f.bcov[3] + (D == 3 ? pt : T(0)));
-  if (D == 0) {
-    F[5] = gdet * P[5];
-    F[6] = gdet * P[6];
-    F[7] = gdet * P[7];
-  } else {
-    F[5] = (D == 1) ? T(0) : gdet * (f.bcon[1] * ud - bd * f.ucon[1]);
-    F[6] = (D == 2) ? T(0) : gdet * (f.bcon[2] * ud - bd * f.ucon[2]);
-    F[7] = (D == 3) ? T(0) : gdet * (f.bcon[3] * ud - bd * f.ucon[3]);
-  }
-}
-
 // One side of a face of direction D (1..3), in two steps: side_speeds finds the
 // fast-magnetosonic speeds and what it needs for them, and once both sides'
 // speeds have given ctop, side_flux adds the side's share of the
@@ -308,8 +230,8 @@ struct FaceSide {
 };
 
 // u_i = g_ij u~^j (or B_i)
-template <bool AXI, typename T>
-__device__ inline void lower3(const FaceGeo<T>& g, T v1, T v2, T v3, T& l1, T& l2, T& l3) {
+template <bool AXI, typename G, typename T>
+__device__ inline void lower3(const G& g, T v1, T v2, T v3, T& l1, T& l2, T& l3) {
   l1 = g.g11 * v1 + g.g12 * v2 + g.g13 * v3;
   l2 = g.g12 * v1 + g.g22 * v2;
   l3 = g.g13 * v1 + g.g33 * v3;
@@ -385,6 +307,56 @@ __device__ inline void side_flux(const FaceSide<T>& s, const FaceGeo<T>& g, T ga
   else if constexpr (!AXI) vb = vb - g.b3;
   f[5] = P[4 + a] * W - BD * va;
   f[6] = P[4 + b] * W - BD * vb;
+}
+
+// Geometry of a zone centre in the same 3+1 form, with gamma^ij.
+struct ZoneGeo {
+  double g11, g12, g13, g22, g23, g33;
+  double b1, b2, b3;
+  double alpha, ialpha, gdet, igdet;
+  double h11, h12, h13, h22, h23, h33;
+};
+
+// what the conserved variables and the source need of primitives P
+struct ZoneState {
+  double u1, u2, u3, B1, B2, B3;       // u_i, B_i
+  double l2, lor, ut, iut, bt, bsq;    // Gamma^2, Gamma, u^t, 1/u^t, b^t, b^2
+};
+
+template <bool AXI>
+__device__ inline void zone_state(const double* P, const ZoneGeo& g, ZoneState& s) {
+  lower3<AXI>(g, P[2], P[3], P[4], s.u1, s.u2, s.u3);
+  s.l2 = P[2] * s.u1 + P[3] * s.u2 + P[4] * s.u3 + 1.0;
+  s.bt = P[5] * s.u1 + P[6] * s.u2 + P[7] * s.u3;
+  lower3<AXI>(g, P[5], P[6], P[7], s.B1, s.B2, s.B3);
+  const double Bsq = P[5] * s.B1 + P[6] * s.B2 + P[7] * s.B3;
+  const double rl = rsqrt_full(s.l2);
+  s.lor = s.l2 * rl;
+  s.ut = s.lor * g.ialpha;
+  s.iut = g.alpha * rl;
+  s.bsq = (Bsq + s.bt * s.bt) * (s.iut * s.iut);
+}
+
+// sqrt(-g) (rho u^t, T^t_t + rho u^t, T^t_i, B^i)
+template <bool AXI>
+__device__ inline void conserved(const double* P, const ZoneState& s, const ZoneGeo& g, double gam, double* U) {
+  const double rt = P[0] * s.ut;
+  const double C = s.bt * s.iut;
+  const double A = (P[0] + gam * P[1] + s.bsq) * s.ut - C * s.bt;
+  const double pt = (gam - 1.0) * P[1] + 0.5 * s.bsq;
+  double ut = g.b1 * s.u1 + g.b2 * s.u2 - g.alpha * s.lor, Bt = g.b1 * s.B1 + g.b2 * s.B2;
+  if constexpr (!AXI) {
+    ut = ut + g.b3 * s.u3;
+    Bt = Bt + g.b3 * s.B3;
+  }
+  U[0] = g.gdet * rt;
+  U[1] = g.gdet * (A * ut - C * Bt + pt + rt);
+  U[2] = g.gdet * (A * s.u1 - C * s.B1);
+  U[3] = g.gdet * (A * s.u2 - C * s.B2);
+  U[4] = g.gdet * (A * s.u3 - C * s.B3);
+  U[5] = g.gdet * P[5];
+  U[6] = g.gdet * P[6];
+  U[7] = g.gdet * P[7];
 }
 
 // ---------------------------------------------------------------------------

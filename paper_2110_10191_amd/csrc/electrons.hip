@@ -30,6 +30,7 @@
 //             c2 = 1.2/theta, c3 = 18 otherwise, beta_i^x capped at e^700;
 //   Sharma:   Q_e/Q_i = sqrt(T_e/T_i) / 3, i.e. Q_i/Q_e = 3 sqrt(T_i/T_e);
 // with f_e = 1 / (1 + Q_i/Q_e) where a ratio is given.
+#include "cks_geometry.h"
 #include "kernels.h"
 
 namespace {
@@ -91,14 +92,13 @@ __device__ void scalar_advect_body(const Dims& d, const double* __restrict__ cen
   for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] += (fp[s] - fm[s]) * up.idx3;
 
   // rest-mass density of the base state: sqrt(-g) rho u^t, u^t = Gamma / alpha
-  const int toff = tab_of(d, j, i);
-  const double* ck = tab_plane(cent, d, tk.k);
-  double gcov[10];
-#pragma unroll
-  for (int m = 0; m < 10; ++m) gcov[m] = ck[(T_GCOV + m) * d.ts + toff];
-  const double gdet = ck[T_GDET * d.ts + toff], alpha = ck[T_ALPHA * d.ts + toff];
-  const double ut = sqrt(lorentz_sq(gcov, Pb[2 * d.sv + c], Pb[3 * d.sv + c], Pb[4 * d.sv + c])) / alpha;
-  const double D = gdet * Pb[c] * ut;
+  ZoneGeo g;
+  zone_geo<ZONE_ANY>(g, pair_plane(cent, d, tk.k), d, tab_of(d, j, i), i, j, tk.k);
+  const double v1 = Pb[2 * d.sv + c], v2 = Pb[3 * d.sv + c], v3 = Pb[4 * d.sv + c];
+  double u1, u2, u3;
+  lower3<false>(g, v1, v2, v3, u1, u2, u3);
+  const double l2 = v1 * u1 + v2 * u2 + v3 * u3 + 1.0;
+  const double D = g.gdet * Pb[c] * (l2 * rsqrt_full(l2) * g.ialpha);
 #pragma unroll
   for (int s = 0; s < GRMHD_NSCALAR; ++s) Uk[s * d.sv + c] = D * Eb[s * d.sv + c] - dt * div[s];
 }
@@ -180,11 +180,11 @@ __device__ void electron_heat_body(const Dims& d, const double* __restrict__ cen
     p[1] = umax;
     P[d.sv + c] = umax;
   }
-  Geo<double> g;
-  load_geo(g, tab_plane(cent, d, tk.k), d.ts, tab_of(d, j, i));
-  Fluid<double> f;
-  fluid_state(p, g, gam, f);
-  const double D = g.gdet * rho * f.ucon[0];
+  ZoneGeo g;
+  zone_geo<ZONE_ANY>(g, pair_plane(cent, d, tk.k), d, tab_of(d, j, i), i, j, tk.k);
+  ZoneState f;
+  zone_state<false>(p, g, f);
+  const double D = g.gdet * rho * f.ut;
   const double ktot_adv = Uk[c] / D, kel_adv = Uk[d.sv + c] / D;
   const double ktot = (gam - 1.0) * p[1] / rg;
   const double fe = heating_fraction(model, fel, rho, p[1], kel_adv, f.bsq, gam);

@@ -1,6 +1,6 @@
-// Geometry tables: metric, inverse, sqrt(-g) and lapse at zone centres and
-// faces; connection at centres by centred differences of the metric; floor
-// scales. Implementation Notes section: every metric-dependent quantity is
+// Geometry tables: the metric in 3+1 form at zone centres and faces, the source
+// coefficients (centred differences of the metric) and floor scales at centres.
+// Implementation Notes section: every metric-dependent quantity is
 // evaluated numerically from an analytic line element, the coordinates act as
 // static mesh refinement (MKS / funky MKS concentrate zones towards the disk
 // midplane), and another coordinate system or stationary spacetime is a small
@@ -9,8 +9,8 @@
 #include "kernels.h"
 #include "cks_geometry.h"
 
-// No fused multiply-adds here: the connection's centred differences (step
-// 1e-5) turn a one-ulp change of the metric into a 1e-10 change of Gamma, so
+// No fused multiply-adds here: the centred differences (step 1e-5) turn a
+// one-ulp change of the metric into a 1e-10 change of its derivative, so
 // every table value is the plain sequence of correctly rounded operations its
 // formula spells out.
 #pragma clang fp contract(off)
@@ -136,26 +136,6 @@ __device__ double invert4(const double m[4][4], double b[4][4]) {
   return det;
 }
 
-// write metric, inverse (upper triangle), sqrt(-g) and lapse of one point
-// into the centre table
-__device__ void store_point(double x1, double x2, double x3, const grmhd_problem& p, double* dt, size_t ts, int off,
-                            double gcon_out[4][4]) {
-  double g[4][4], gi[4][4];
-  gcov_code(x1, x2, x3, p, g);
-  const double det = invert4(g, gi);
-  auto at = [&](int c) -> size_t { return (size_t)c * ts + (size_t)off; };
-  for (int m = 0; m < 4; ++m)
-    for (int n = m; n < 4; ++n) {
-      const int c = sidx(m, n);
-      dt[at(T_GCOV + c)] = g[m][n];
-      dt[at(T_GCON + c)] = gi[m][n];
-    }
-  dt[at(T_GDET)] = sqrt(fabs(det));
-  dt[at(T_ALPHA)] = 1.0 / sqrt(-gi[0][0]);
-  for (int m = 0; m < 4; ++m)
-    for (int n = 0; n < 4; ++n) gcon_out[m][n] = gi[m][n];
-}
-
 // the 3+1 quantities of a face of direction D in MKS, FMKS or Minkowski
 // coordinates, whose g_23 and beta^3 vanish identically
 __device__ void face_point(double x1, double x2, double x3, int D, const grmhd_problem& p, FaceGeo<double>& f) {
@@ -203,7 +183,7 @@ __device__ void store_face(const FaceGeo<double>& g, double* dt, float* ft, size
   }
 }
 
-__global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t, CksBox box) {
+__global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t) {
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) - NG;
   const int j = (int)(blockIdx.y * blockDim.y + threadIdx.y) - NG;
   const int k = (int)blockIdx.z - NG;  // 2D tables: a single plane (k = -NG, tk = 0)
@@ -216,24 +196,8 @@ __global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t, CksBox box) {
   const double x1c = p.x1min + (i + 0.5) * dx1, x2c = p.x2min + (j + 0.5) * dx2, x3c = p.x3min + (k + 0.5) * dx3;
   const double x1f = p.x1min + i * dx1, x2f = p.x2min + j * dx2;
   const bool k3 = p.coords == GRMHD_KERR_CKS;
+  const CksBox& box = d.box;  // the zone corner and widths, computed on the host
 
-  double gcon[4][4];
-  if (k3) {
-    // Cartesian Kerr-Schild centres in closed form, the values the update
-    // computes itself (the connection below uses this inverse)
-    Geo<double> g;
-    cks_centre_geo(box, i, j, k, g);
-    for (int c = 0; c < 10; ++c) {
-      t.cent[(size_t)(T_GCOV + c) * ts + off] = g.gcov[c];
-      t.cent[(size_t)(T_GCON + c) * ts + off] = g.gcon[c];
-    }
-    t.cent[(size_t)T_GDET * ts + off] = g.gdet;
-    t.cent[(size_t)T_ALPHA * ts + off] = g.alpha;
-    for (int m = 0; m < 4; ++m)
-      for (int n = 0; n < 4; ++n) gcon[m][n] = g.gcon[sidx(m, n)];
-  } else {
-    store_point(x1c, x2c, x3c, p, t.cent, ts, off, gcon);
-  }
   // faces: Cartesian Kerr-Schild in closed form, the values the face-flux pass
   // computes itself (box: the zone corner and widths it uses, computed on the
   // host); the x3-face table of the 2D tables holds the centre values, the
@@ -247,43 +211,75 @@ __global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t, CksBox box) {
     store_face(g, dt[D - 1], ft[D - 1], ts, off);
   }
 
-  // connection: Gamma_kmn = (d_n g_km + d_m g_kn - d_k g_mn)/2, Gamma^l_mn = g^lk Gamma_kmn,
-  // derivatives by centred differences in x1, x2 and (3D tables) x3; d_t = 0
-  double dg[3][4][4];  // dg[c-1][a][b] = d_c g_ab, c = 1..3
-  for (int c = 0; c < 3; ++c)
-    for (int a = 0; a < 4; ++a)
-      for (int b = 0; b < 4; ++b) dg[c][a][b] = 0.0;
+  // centres: source coefficients from centred differences of the metric
+  // (d_t = 0), floor scales, and for 2D tables the metric itself
+  double v[N_CENT] = {};
+  double gi[4][4], gdet = 1.0;
+  {
+    double g[4][4];
+    gcov_code(x1c, x2c, x3c, p, g);
+    if (k3) {
+      // g^-1 = eta - f l^ l^ in closed form, from gamma^ij, beta^i and alpha
+      ZoneGeo z;
+      cks_centre_geo(box, i, j, k, z);
+      const double ia2 = z.ialpha * z.ialpha, bb[3] = {z.b1, z.b2, z.b3};
+      const double h[3][3] = {{z.h11, z.h12, z.h13}, {z.h12, z.h22, z.h23}, {z.h13, z.h23, z.h33}};
+      gi[0][0] = -ia2;
+      for (int m = 0; m < 3; ++m) {
+        gi[0][m + 1] = gi[m + 1][0] = bb[m] * ia2;
+        for (int n = 0; n < 3; ++n) gi[m + 1][n + 1] = h[m][n] - bb[m] * bb[n] * ia2;
+      }
+    } else {
+      const double det = invert4(g, gi);
+      const double a2 = -1.0 / gi[0][0];
+      gdet = sqrt(fabs(det));
+      v[C_G11] = g[1][1];
+      v[C_G12] = g[1][2];
+      v[C_G13] = g[1][3];
+      v[C_G22] = g[2][2];
+      v[C_G33] = g[3][3];
+      v[C_ALPHA] = 1.0 / sqrt(-gi[0][0]);
+      v[C_B1] = a2 * gi[0][1];
+      v[C_B2] = a2 * gi[0][2];
+      v[C_IALPHA] = sqrt(-gi[0][0]);
+      v[C_GDET] = gdet;
+      v[C_IGDET] = 1.0 / gdet;
+      // gamma^ij = g^ij + alpha^2 g^ti g^tj
+      v[C_H11] = gi[1][1] + a2 * gi[0][1] * gi[0][1];
+      v[C_H12] = gi[1][2] + a2 * gi[0][1] * gi[0][2];
+      v[C_H13] = gi[1][3];
+      v[C_H22] = gi[2][2] + a2 * gi[0][2] * gi[0][2];
+      v[C_H23] = gi[2][3];
+      v[C_H33] = gi[3][3];
+    }
+  }
   if (p.coords != GRMHD_MINKOWSKI_CART) {
-    const int nd = k3 ? 3 : 2;
-    for (int c = 0; c < nd; ++c) {
+    for (int c = 0; c < (k3 ? 3 : 2); ++c) {
       const double e1 = c == 0 ? FD_DELTA : 0.0, e2 = c == 1 ? FD_DELTA : 0.0, e3 = c == 2 ? FD_DELTA : 0.0;
       double gp[4][4], gm[4][4];
       gcov_code(x1c + e1, x2c + e2, x3c + e3, p, gp);
       gcov_code(x1c - e1, x2c - e2, x3c - e3, p, gm);
+      double tr = 0.0;
       for (int a = 0; a < 4; ++a)
-        for (int b = 0; b < 4; ++b) dg[c][a][b] = (gp[a][b] - gm[a][b]) / (2.0 * FD_DELTA);
+        for (int b = a; b < 4; ++b) {
+          const double dg = gdet * ((gp[a][b] - gm[a][b]) / (2.0 * FD_DELTA)) * (a == b ? 0.5 : 1.0);
+          tr += gi[a][b] * dg;
+          if (k3) v[K_S1 + 11 * c + sidx(a, b)] = dg;
+          else
+            for (int q = 0; q < 8; ++q)
+              if (AXI_KM[q][0] == a && AXI_KM[q][1] == b) v[C_S1 + 9 * c + q] = dg;
+        }
+      v[k3 ? K_S1 + 11 * c + 10 : C_S1 + 9 * c + 8] = tr;
     }
-  }
-  auto D = [&](int c, int a, int b) -> double { return c > 0 ? dg[c - 1][a][b] : 0.0; };
-  for (int l = 0; l < 4; ++l)
-    for (int m = 0; m < 4; ++m)
-      for (int n = m; n < 4; ++n) {
-        double s = 0.0;
-        for (int q = 0; q < 4; ++q) s += gcon[l][q] * 0.5 * (D(n, q, m) + D(m, q, n) - D(q, m, n));
-        t.cent[(T_CONN + 10 * l + sidx(m, n)) * ts + off] = s;
-      }
-
-  // floor scales: k = 1/(r^2 (1 + r/10)) with r = exp(x1) (MKS / FMKS) or the
-  // Kerr-Schild radius of the Cartesian point
-  double rfl = 0.0, ufl = 0.0;
-  if (p.coords != GRMHD_MINKOWSKI_CART) {
+    // floor scales: k = 1/(r^2 (1 + r/10)) with r = exp(x1) (MKS / FMKS) or the
+    // Kerr-Schild radius of the Cartesian point
     const double r = k3 ? cks_radius(x1c, x2c, x3c, p.a) : exp(x1c);
     const double kk = 1.0 / (r * r * (1.0 + r / 10.0));
-    rfl = p.rho_fl * kk;
-    ufl = p.u_fl * pow(kk, p.gam);
+    v[k3 ? K_RHOFL : C_RHOFL] = p.rho_fl * kk;
+    v[k3 ? K_UFL : C_UFL] = p.u_fl * pow(kk, p.gam);
   }
-  t.cent[T_RHOFL * ts + off] = rfl;
-  t.cent[T_UFL * ts + off] = ufl;
+  if (k3) v[K_GDET] = 1.0;
+  for (int c = 0; c < (k3 ? K_GDET : C_UFL) + 1; ++c) t.cent[pair_index(c, ts, (size_t)off)] = v[c];
 }
 
 }  // namespace
@@ -291,6 +287,6 @@ __global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t, CksBox box) {
 hipError_t launch_geometry(const grmhd_problem& p, const Dims& d, const Tables& t, hipStream_t s) {
   dim3 blk(64, 4, 1);
   dim3 grd((d.n1 + 2 * NG + 63) / 64, (d.n2 + 2 * NG + 3) / 4, d.tk ? d.p3 : 1);
-  hipLaunchKernelGGL(geometry_kernel, grd, blk, 0, s, p, d, t, cks_box(p));
+  hipLaunchKernelGGL(geometry_kernel, grd, blk, 0, s, p, d, t);
   return hipGetLastError();
 }

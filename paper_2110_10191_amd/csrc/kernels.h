@@ -7,13 +7,12 @@
 #include "common.h"
 
 // Geometry tables over the padded (x1, x2) points (2D) or (x1, x2, x3) points
-// (3D, Dims::tk != 0), ts points a component: the centre table one plane per
-// component, [N_CENT][points]; the face tables two components interleaved
-// per point, [N_FACE / 2][points][2] (pair_index), so the face-flux pass
-// loads them two at a time. 2D tables hold the x3-face table too (the centre
-// values, the metric not depending on x3).
+// (3D, Dims::tk != 0), ts points a component, two components interleaved per
+// point (pair_index), so the kernels load them two at a time: the centre table
+// with room for N_CENT components, the face tables for N_FACE. 2D tables hold
+// the x3-face table too (the centre values, the metric not depending on x3).
 struct Tables {
-  double* cent;   // centre table, N_CENT components
+  double* cent;   // centre table
   double* f1;     // x1-, x2-, x3-face tables, room for N_FACE components in pairs (F_USED filled)
   double* f2;
   double* f3;
@@ -39,6 +38,8 @@ struct UpdateParams {
   double sigma_max, beta_min, uorho_max, gamma_max;
   double dx1, dx2, dx3;
   double idx1, idx2, idx3;  // 1 / dx_d
+  double igam, gf;                 // 1 / gam, (gam - 1) / gam
+  double isigma, iuorho, beta_fl;  // 1 / sigma_max, 1 / uorho_max, beta_min / (2 (gam - 1))
   int floors;
   int polar_lo, polar_hi;  // x2 boundaries are polar axes
   int periodic[3];         // direction d (0 = x1) is periodic
@@ -148,13 +149,11 @@ unsigned sweep_blocks(const Dims& d);
 hipError_t launch_sweeps(const grmhd_problem& p, bool mixed, const Dims& d, const Tables& t, const UpdateParams& up,
                          const double* P, void* F, bool mass, unsigned long long* ctop, hipStream_t s);
 
-// the step is dt, or dt_scale * *dt_dev when dt_dev is not null; cks (the
-// problem, Cartesian Kerr-Schild only): the update computes the centre
-// metric in closed form instead of reading it
+// the step is dt, or dt_scale * *dt_dev when dt_dev is not null; in Cartesian
+// Kerr-Schild the update computes the centre metric in closed form
 hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const UpdateParams& up,
                          const void* F, const double* Pb, const double* Ps, double* Pout, int8_t* flags, double dt,
-                         const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s,
-                         const grmhd_problem* cks = nullptr);
+                         const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s);
 
 // ctr->dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 ctr->dt) on the device
 hipError_t launch_ctx_dt(Counters* ctr, double cfl, double dx1, double dx2, double dx3, hipStream_t s);

@@ -152,7 +152,7 @@ struct SweepArgs {
 
 // b: block index within this job's grid; BX x BY threads
 template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
-__device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, const CksBox& box, int b, unsigned long long* ctop) {
+__device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned long long* ctop) {
   using SH = PlaneShape<RECON, BX, BY>;
   const SweepTile t = sweep_tile(d, BX, BY, b);
   if (!t.valid) return;
@@ -196,8 +196,8 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, const CksBox& b
   const size_t sv = (size_t)d.sv;
   const bool hydro = k >= 0 && k < d.n3;
   auto geo = [&](int D, const T* tab, FaceGeo<T>& g) {
-    if constexpr (GEO == GEO_CKS) cks_face_geo(box, D, ic, jc, k, g);
-    else load_face_geo<AXI>(g, face_plane(tab, d, k), d.ts, toff);
+    if constexpr (GEO == GEO_CKS) cks_face_geo(d.box, D, ic, jc, k, g);
+    else load_face_geo<AXI>(g, pair_plane(tab, d, k), d.ts, toff);
   };
   T f[7];
   T g2 = T(0);  // x3 fluxes of B1 of this cell and the one before it
@@ -276,9 +276,9 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, const CksBox& b
 }
 
 template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
-__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_kernel(Dims d, SweepArgs<T> a, CksBox box,
+__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_kernel(Dims d, SweepArgs<T> a,
                                                                           unsigned long long* ctop) {
-  sweep_body<RECON, T, GEO, CTOP, BX, BY>(d, a, box, (int)blockIdx.x, ctop);
+  sweep_body<RECON, T, GEO, CTOP, BX, BY>(d, a, (int)blockIdx.x, ctop);
 }
 
 template <typename T>
@@ -302,13 +302,12 @@ __global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_batch_k
   const int* offs = bv.offs + PH_SWEEP * (bv.njobs + 1);
   const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
   const JobDesc& J = bv.jobs[jb];
-  const CksBox none{};
   const FluxOut<T> out = flux_out<T>(global_ptr((unsigned char*)J.F), J.d.sv);
   const SweepArgs<T> a{global_ptr(corrector ? J.Ph : J.P), global_ptr(FaceTables<T>::f1(J.t)),
                        global_ptr(FaceTables<T>::f2(J.t)), global_ptr(FaceTables<T>::f3(J.t)), out,
                        J.E ? out.m : nullptr, J.up.idx1, J.up.idx2, J.up.idx3, (T)J.p.gam, J.up.polar_lo,
                        J.up.polar_hi};
-  sweep_body<RECON, T, GEO, CTOP, BX, BY>(J.d, a, none, (int)blockIdx.x - offs[jb], CTOP ? global_ptr(J.ctr->ctop) : nullptr);
+  sweep_body<RECON, T, GEO, CTOP, BX, BY>(J.d, a, (int)blockIdx.x - offs[jb], CTOP ? global_ptr(J.ctr->ctop) : nullptr);
 }
 
 template <int RECON, typename T, int BX, int BY>
@@ -341,27 +340,26 @@ hipError_t with_shape(const Dims& d, F f) {
 }
 
 template <int RECON, typename T, int GEO, bool CTOP>
-hipError_t launch_ctop(const Dims& d, const SweepArgs<T>& a, const CksBox& box, unsigned long long* ctop,
-                       hipStream_t s) {
+hipError_t launch_ctop(const Dims& d, const SweepArgs<T>& a, unsigned long long* ctop, hipStream_t s) {
   return with_shape<RECON, T>(d, [&](auto bx, auto by) {
     constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
     constexpr size_t lds = tile_bytes<RECON, T, BX, BY>();
     const hipError_t e = allow_lds<sweep_kernel<RECON, T, GEO, CTOP, BX, BY>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((sweep_kernel<RECON, T, GEO, CTOP, BX, BY>), dim3(sweep_blocks(d)), dim3(BX, BY, 1), lds, s, d, a,
-                       box, ctop);
+                       ctop);
     return hipGetLastError();
   });
 }
 
 template <int RECON, typename T, int GEO>
-hipError_t launch_geo(const Dims& d, const Tables& t, const UpdateParams& up, const CksBox& box, const double* P,
-                      void* F, bool mass, unsigned long long* ctop, hipStream_t s) {
+hipError_t launch_geo(const Dims& d, const Tables& t, const UpdateParams& up, const double* P, void* F,
+                      bool mass, unsigned long long* ctop, hipStream_t s) {
   const FluxOut<T> out = flux_out<T>((unsigned char*)F, d.sv);
   const SweepArgs<T> a{P,       FaceTables<T>::f1(t), FaceTables<T>::f2(t), FaceTables<T>::f3(t), out, mass ? out.m : nullptr,
                        up.idx1, up.idx2,              up.idx3,              (T)up.gam,            up.polar_lo, up.polar_hi};
-  if (ctop) return launch_ctop<RECON, T, GEO, true>(d, a, box, ctop, s);
-  return launch_ctop<RECON, T, GEO, false>(d, a, box, ctop, s);
+  if (ctop) return launch_ctop<RECON, T, GEO, true>(d, a, ctop, s);
+  return launch_ctop<RECON, T, GEO, false>(d, a, ctop, s);
 }
 
 // Cartesian Kerr-Schild in FP64 computes its face geometry instead of
@@ -371,10 +369,10 @@ hipError_t launch_geo(const Dims& d, const Tables& t, const UpdateParams& up, co
 template <int RECON, typename T>
 hipError_t launch_for(const grmhd_problem& p, const Dims& d, const Tables& t, const UpdateParams& up, const double* P,
                       void* F, bool mass, unsigned long long* ctop, hipStream_t s) {
-  if (p.coords != GRMHD_KERR_CKS) return launch_geo<RECON, T, GEO_AXI>(d, t, up, CksBox{}, P, F, mass, ctop, s);
+  if (p.coords != GRMHD_KERR_CKS) return launch_geo<RECON, T, GEO_AXI>(d, t, up, P, F, mass, ctop, s);
   if constexpr (std::is_same<T, double>::value)
-    return launch_geo<RECON, T, GEO_CKS>(d, t, up, cks_box(p), P, F, mass, ctop, s);
-  else return launch_geo<RECON, T, GEO_TABLE>(d, t, up, CksBox{}, P, F, mass, ctop, s);
+    return launch_geo<RECON, T, GEO_CKS>(d, t, up, P, F, mass, ctop, s);
+  else return launch_geo<RECON, T, GEO_TABLE>(d, t, up, P, F, mass, ctop, s);
 }
 
 // a batch whose jobs all have g_23 = beta^3 = 0 reads the shorter tables (the

@@ -30,63 +30,60 @@
 
 namespace {
 
+constexpr int POINT_TX = 64, POINT_TY = 1;  // tile of the pointwise kernels
 constexpr double INV_TOL = 1e-8;
 constexpr int INV_EXTRA = 2;
 constexpr int INV_MAXIT = 50;
 constexpr double V2MAX = 1.0 - 1e-12;
 
-__device__ bool invert_1dw(const double* U, const double* guess, const Geo<double>& g, double gam,
-                           double* P) {
-  const double igd = 1.0 / g.gdet;
+// guess_l2: Gamma^2 of the guess. Divisions and square roots by rcp_full and
+// rsqrt_full (an IEEE division is some ten instructions, and an iteration had
+// three and a square root).
+template <bool AXI>
+__device__ bool invert_1dw(const double* U, const double* guess, double guess_l2, const ZoneGeo& g,
+                           const UpdateParams& up, double* P) {
   const double a = g.alpha;
-  const double ut0 = U[0] * igd, ut1 = U[1] * igd;
+  const double ut0 = U[0] * g.igdet, ut1 = U[1] * g.igdet;
+  const double q1 = U[2] * g.igdet, q2 = U[3] * g.igdet, q3 = U[4] * g.igdet;
+  const double Bu1 = U[5] * g.igdet, Bu2 = U[6] * g.igdet, Bu3 = U[7] * g.igdet;
   const double D = a * ut0;
-  const double Q1 = a * (U[2] * igd), Q2 = a * (U[3] * igd), Q3 = a * (U[4] * igd);
-  const double Bu1 = U[5] * igd, Bu2 = U[6] * igd, Bu3 = U[7] * igd;
+  const double Q1 = a * q1, Q2 = a * q2, Q3 = a * q3;
   const double B1 = a * Bu1, B2 = a * Bu2, B3 = a * Bu3;
-  const double qn_d = ut1 + (a - 1.0) * ut0 - a * (g.gcon[1] * Q1 + g.gcon[2] * Q2 + g.gcon[3] * Q3);
-  const double a2 = a * a;
-  // spatial metric gamma^ij = g^ij + alpha^2 g^ti g^tj
-  const double h11 = g.gcon[4] + a2 * g.gcon[1] * g.gcon[1];
-  const double h12 = g.gcon[5] + a2 * g.gcon[1] * g.gcon[2];
-  const double h13 = g.gcon[6] + a2 * g.gcon[1] * g.gcon[3];
-  const double h22 = g.gcon[7] + a2 * g.gcon[2] * g.gcon[2];
-  const double h23 = g.gcon[8] + a2 * g.gcon[2] * g.gcon[3];
-  const double h33 = g.gcon[9] + a2 * g.gcon[3] * g.gcon[3];
-  const double qt1 = h11 * Q1 + h12 * Q2 + h13 * Q3;
-  const double qt2 = h12 * Q1 + h22 * Q2 + h23 * Q3;
-  const double qt3 = h13 * Q1 + h23 * Q2 + h33 * Q3;
+  double bq = g.b1 * q1 + g.b2 * q2;
+  if constexpr (!AXI) bq = bq + g.b3 * q3;
+  const double qn_d = ut1 + (a - 1.0) * ut0 - bq;
+  const double qt1 = g.h11 * Q1 + g.h12 * Q2 + g.h13 * Q3;
+  const double qt2 = g.h12 * Q1 + g.h22 * Q2 + g.h23 * Q3;
+  const double qt3 = g.h13 * Q1 + g.h23 * Q2 + g.h33 * Q3;
   const double qtsq = Q1 * qt1 + Q2 * qt2 + Q3 * qt3;
   const double qdb = Q1 * B1 + Q2 * B2 + Q3 * B3;
   const double qdb2 = qdb * qdb;
-  const double bsq = g.gcov[4] * B1 * B1 + g.gcov[7] * B2 * B2 + g.gcov[9] * B3 * B3 +
-                     2.0 * (g.gcov[5] * B1 * B2 + g.gcov[6] * B1 * B3 + g.gcov[8] * B2 * B3);
-  const double gf = (gam - 1.0) / gam;
+  double bl1, bl2, bl3;
+  lower3<AXI>(g, B1, B2, B3, bl1, bl2, bl3);
+  const double bsq = B1 * bl1 + B2 * bl2 + B3 * bl3;
+  const double gf = up.gf;
 
-  double x = (guess[0] + gam * guess[1]) * lorentz_sq(g.gcov, guess[2], guess[3], guess[4]) - D;
+  double x = (guess[0] + up.gam * guess[1]) * guess_l2 - D;
   int extra = -1;
   for (int it = 0; it < INV_MAXIT && extra < INV_EXTRA; ++it) {
-    // three divisions per iteration: 1/(W bw) gives 1/W and 1/bw,
-    // 1/(s (1 + s)) gives 1/s and 1/(1 + s), and the Newton quotient
     const double W = x + D;
-    const double W2 = W * W, bw = bsq + W;
-    const double rwb = 1.0 / (W * bw);
-    const double iW = bw * rwb, ibw = W * rwb;
-    const double iW2 = iW * iW, ibw2 = ibw * ibw;
-    const double v2raw = (qtsq * W2 + qdb2 * (bsq + 2.0 * W)) * (ibw2 * iW2);
+    const double W2 = W * W, bw = bsq + W, Wbw = W * bw;
+    const double rwb = rcp_full(Wbw);  // 1/(W bw), and 1/W = bw rwb
+    const double iW = bw * rwb, iW2 = iW * iW, rwb2 = rwb * rwb;
+    const double v2raw = (qtsq * W2 + qdb2 * (bw + W)) * rwb2;
     const double v2 = fmin(fmax(v2raw, 0.0), V2MAX);
-    const double s = sqrt(1.0 - v2);
-    const double rs = 1.0 / (s * (1.0 + s));
-    const double is = (1.0 + s) * rs, i1s = s * rs;
-    const double wmr = x * (1.0 - v2) - D * s * v2 * i1s;
+    const double g2 = 1.0 - v2;
+    const double is = rsqrt_full(g2), s = g2 * is;
+    const double Ds = D * s;
+    const double wmr = x * g2 - Ds * v2 * rcp_full(1.0 + s);
     const double f = qn_d + x - gf * wmr + 0.5 * bsq * (1.0 + v2) - 0.5 * qdb2 * iW2;
-    double dv2 = -2.0 * (qtsq * W2 * W + qdb2 * (3.0 * W2 + 3.0 * W * bsq + bsq * bsq)) * (ibw2 * ibw * iW2 * iW);
+    double dv2 = -2.0 * (qtsq * (W2 * W) + qdb2 * (3.0 * Wbw + bsq * bsq)) * (rwb2 * rwb);
     if (v2raw > V2MAX || v2raw < 0.0) dv2 = 0.0;
-    const double dp = gf * ((1.0 - v2) + (-W + 0.5 * D * is) * dv2);
+    const double dp = gf * (g2 + (0.5 * D * is - W) * dv2);
     const double df = 1.0 - dp + 0.5 * bsq * dv2 + qdb2 * (iW2 * iW);
-    const double dx = -f / df;
+    const double dx = -f * rcp_full(df);
     double xn = x + dx;
-    if (xn + D <= 0.0) xn = 0.5 * (x + D) - D;
+    if (xn + D <= 0.0) xn = 0.5 * W - D;
     x = xn;
     if (extra < 0) {
       if (fabs(dx) <= INV_TOL * fabs(x + D)) extra = 0;
@@ -96,14 +93,15 @@ __device__ bool invert_1dw(const double* U, const double* guess, const Geo<doubl
   }
   const double W = x + D;
   const double bw = bsq + W;
-  const double v2 = (qtsq * W * W + qdb2 * (bsq + 2.0 * W)) / (bw * bw * W * W);
+  const double rwb = rcp_full(W * bw);
+  const double v2 = (qtsq * W * W + qdb2 * (bw + W)) * (rwb * rwb);
   bool failed = (extra < 0) || !(W > 0.0) || !(v2 < V2MAX) || !isfinite(v2) || !isfinite(W);
   const double v2c = fmin(fmax(v2, 0.0), V2MAX);
-  const double s = sqrt(1.0 - v2c);
-  const double lor = 1.0 / s;
+  const double g2 = 1.0 - v2c;
+  const double lor = rsqrt_full(g2), s = g2 * lor;
   P[0] = D * s;
-  P[1] = (x * (1.0 - v2c) - D * s * v2c / (1.0 + s)) / gam;
-  const double fac = lor / bw, qw = qdb / W;
+  P[1] = (x * g2 - D * s * v2c * rcp_full(1.0 + s)) * up.igam;
+  const double fac = lor * (W * rwb), qw = qdb * (bw * rwb);
   P[2] = fac * (qt1 + qw * B1);
   P[3] = fac * (qt2 + qw * B2);
   P[4] = fac * (qt3 + qw * B3);
@@ -116,33 +114,88 @@ __device__ bool invert_1dw(const double* U, const double* guess, const Geo<doubl
   return failed;
 }
 
-__device__ void apply_floors(double* P, const Geo<double>& g, double rfl, double ufl, const UpdateParams& up) {
-  const double lor2 = lorentz_sq(g.gcov, P[2], P[3], P[4]);
+template <bool AXI>
+__device__ void apply_floors(double* P, const ZoneGeo& g, double rfl, double ufl, const UpdateParams& up) {
+  double u1, u2, u3, B1, B2, B3;
+  lower3<AXI>(g, P[2], P[3], P[4], u1, u2, u3);
+  double l2 = P[2] * u1 + P[3] * u2 + P[4] * u3 + 1.0;
+  double bt = P[5] * u1 + P[6] * u2 + P[7] * u3;
   const double gm2 = up.gamma_max * up.gamma_max;
-  if (lor2 > gm2) {
-    const double sc = sqrt((gm2 - 1.0) / (lor2 - 1.0));
+  if (l2 > gm2) {
+    const double sc = sqrt((gm2 - 1.0) / (l2 - 1.0));
     P[2] *= sc;
     P[3] *= sc;
     P[4] *= sc;
+    bt *= sc;
+    l2 = gm2;
   }
-  Fluid<double> f;
-  fluid_state(P, g, up.gam, f);
-  const double bsq = f.bsq;
-  double rho = fmax(fmax(P[0], rfl), bsq / up.sigma_max);
-  const double u = fmax(fmax(P[1], ufl), up.beta_min * bsq / (2.0 * (up.gam - 1.0)));
-  rho = fmax(rho, u / up.uorho_max);
+  lower3<AXI>(g, P[5], P[6], P[7], B1, B2, B3);
+  const double Bsq = P[5] * B1 + P[6] * B2 + P[7] * B3;
+  // b^2 = (B^2 + (b^t)^2) / (u^t)^2
+  const double bsq = (Bsq + bt * bt) * (g.alpha * g.alpha * rcp_full(l2));
+  double rho = fmax(fmax(P[0], rfl), bsq * up.isigma);
+  const double u = fmax(fmax(P[1], ufl), up.beta_fl * bsq);
+  rho = fmax(rho, u * up.iuorho);
   P[0] = rho;
   P[1] = u;
 }
 
+// sqrt(-g) T^km d_n g_km / 2 for n = 1..3 (the coefficients of the table) of
+// state P, s into S (zero along x3 in MKS, FMKS and Minkowski)
+template <bool AXI>
+__device__ inline void source(const double* P, const ZoneState& s, const ZoneGeo& g, double gam, const double* ct,
+                              const Dims& d, int off, double* S) {
+  double u[4], b[4];
+  const double li = s.lor * g.ialpha;  // u^i = u~^i - Gamma beta^i / alpha
+  u[0] = s.ut;
+  u[1] = P[2] - li * g.b1;
+  u[2] = P[3] - li * g.b2;
+  u[3] = AXI ? P[4] : P[4] - li * g.b3;
+  b[0] = s.bt;
+#pragma unroll
+  for (int m = 1; m < 4; ++m) b[m] = (P[4 + m] + s.bt * u[m]) * s.iut;
+  const double wb = P[0] + gam * P[1] + s.bsq, pt = (gam - 1.0) * P[1] + 0.5 * s.bsq;
+  S[0] = S[1] = S[2] = 0.0;
+  if constexpr (AXI) {
+    double M[9];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int k = AXI_KM[q][0], m = AXI_KM[q][1];
+      M[q] = wb * (u[k] * u[m]) - b[k] * b[m];
+    }
+    M[8] = pt;
+    // coefficients C_S1 .. C_S1 + 17 in pairs: nine of x1, then nine of x2
+    static_assert(!(C_S1 & 1) && C_S2 == C_S1 + 9, "pairs of the source coefficients");
+#pragma unroll
+    for (int c = 0; c < 18; c += 2) {
+      const double2 q = zone_pair(ct, d, off, C_S1 + c);
+      S[c / 9] = S[c / 9] + M[c % 9] * q.x;
+      S[(c + 1) / 9] = S[(c + 1) / 9] + M[(c + 1) % 9] * q.y;
+    }
+  } else {
+    double M[11];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int m = k; m < 4; ++m) M[sidx(k, m)] = wb * (u[k] * u[m]) - b[k] * b[m];
+    M[10] = pt;
+    static_assert(K_S1 == 0 && K_S2 == 11 && K_S3 == 22, "pairs of the source coefficients");
+#pragma unroll
+    for (int c = 0; c < 33; c += 2) {
+      const double2 q = zone_pair(ct, d, off, c);
+      S[c / 11] = S[c / 11] + M[c % 11] * q.x;
+      if (c + 1 < 33) S[(c + 1) / 11] = S[(c + 1) / 11] + M[(c + 1) % 11] * q.y;
+    }
+  }
+}
+
 // b: block index within this job's grid (the update tile d.utx x d.uty, XCD-aware order)
-// CKS: the centre metric of Cartesian Kerr-Schild computed in closed form
-// (the values of the centre table) instead of read; the connection and the
-// floor scales still come from the table
-template <typename TF, bool EARLY_PS = false, bool CKS = false>
-__device__ void update_body(const Dims& d, const double* __restrict__ cent, const CksBox& box, const UpdateParams& up,
+// Z: where the zone's geometry comes from
+template <typename TF, int Z>
+__device__ void update_body(const Dims& d, const double* __restrict__ cent, const UpdateParams& up,
                             const FluxOut<TF>& F, const double* Pb, const double* __restrict__ Ps, double* Pout,
                             int8_t* __restrict__ flags, double dt, Counters* ctr, int b) {
+  constexpr bool AXI = Z == ZONE_AXI;
   const TileK tk = xcd_tile_k(b, d.utx, d.uty, d.n1, d.n3);
   const int i = tk.i0 + threadIdx.x;
   const int j = tk.j0 + threadIdx.y;
@@ -150,27 +203,24 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
   int failed = 0;
   if (tk.valid && i < d.n1 && j < d.n2) {
     const int c = cell_of(d, k, j, i);
-    double ps[NV];
-    if (EARLY_PS) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) ps[v] = Ps[v * d.sv + c];
-    }
-    double rhs[NV];
     const size_t sv = (size_t)d.sv;
     const int s2 = d.s2, s3 = d.s3;
+    const int off = tab_of(d, j, i);
+    const double* ct = pair_plane(cent, d, k);
+    double rhs[NV];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      const TF* f = F.f3 + v * sv + c;
-      rhs[v] = fma(-((double)f[s3] - (double)f[0]), up.idx3, F.D[v * sv + c]);
+      const TF* f = F.f3 + v * sv;
+      rhs[v] = fma(-((double)buf_at(f + s3, c) - (double)buf_at(f, c)), up.idx3, buf_at(F.D + v * sv, c));
     }
     // Flux-CT: the zone's twelve edge EMFs (times four; in the flux precision)
     {
       const TF *E1 = F.e, *E2 = F.e + sv, *E3 = F.e + 2 * sv, *b2 = F.b, *b1 = F.b + sv;
-      const TF e3_00 = E3[c], e3_10 = E3[c + 1], e3_01 = E3[c + s2], e3_11 = E3[c + s2 + 1];
-      const TF e1_00 = E1[c] + b2[c - s3], e1_10 = E1[c + s2] + b2[c + s2 - s3];
-      const TF e1_01 = E1[c + s3] + b2[c], e1_11 = E1[c + s2 + s3] + b2[c + s2];
-      const TF e2_00 = E2[c] - b1[c - s3], e2_10 = E2[c + 1] - b1[c + 1 - s3];
-      const TF e2_01 = E2[c + s3] - b1[c], e2_11 = E2[c + s3 + 1] - b1[c + 1];
+      const TF e3_00 = buf_at(E3, c), e3_10 = buf_at(E3 + 1, c), e3_01 = buf_at(E3 + s2, c), e3_11 = buf_at(E3 + s2 + 1, c);
+      const TF e1_00 = buf_at(E1, c) + buf_at(b2 - s3, c), e1_10 = buf_at(E1 + s2, c) + buf_at(b2 + s2 - s3, c);
+      const TF e1_01 = buf_at(E1 + s3, c) + buf_at(b2, c), e1_11 = buf_at(E1 + s2 + s3, c) + buf_at(b2 + s2, c);
+      const TF e2_00 = buf_at(E2, c) - buf_at(b1 - s3, c), e2_10 = buf_at(E2 + 1, c) - buf_at(b1 + 1 - s3, c);
+      const TF e2_01 = buf_at(E2 + s3, c) - buf_at(b1, c), e2_11 = buf_at(E2 + s3 + 1, c) - buf_at(b1 + 1, c);
       // the face's field flux is half the sum of the two EMFs bounding it
       const TF h = TF(0.125);
       const double f1b2m = (double)(h * (e3_00 + e3_01)), f1b2p = (double)(h * (e3_10 + e3_11));
@@ -183,52 +233,41 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
       rhs[6] = -((f1b2p - f1b2m) * up.idx1 + (f3b2p - f3b2m) * up.idx3);
       rhs[7] = -((f1b3p - f1b3m) * up.idx1 + (f2b3p - f2b3m) * up.idx2);
     }
-
-    const int toff = tab_of(d, j, i);
-    const double* ck = tab_plane(cent, d, k);
-    Geo<double> g;
-    if constexpr (CKS) cks_centre_geo(box, i, j, k, g);
-    else load_geo(g, ck, d.ts, toff);
-    if (!EARLY_PS) {
+    ZoneGeo g;
+    zone_geo<Z>(g, ct, d, off, i, j, k);
+    double ps[NV], l2;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) ps[v] = Ps[v * d.sv + c];
-    }
-    // geometric source S_nu = sqrt(-g) T^k_l Gamma^l_{nu k}
+    for (int v = 0; v < NV; ++v) ps[v] = buf_at(Ps + v * sv, c);
     {
-      Fluid<double> f;
-      fluid_state(ps, g, up.gam, f);
-      const double eb = f.w + f.bsq, pt = f.p + 0.5 * f.bsq;
-      double T[4][4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int l = 0; l < 4; ++l) T[kk][l] = eb * f.ucon[kk] * f.ucov[l] + (kk == l ? pt : 0.0) - f.bcon[kk] * f.bcov[l];
-#pragma unroll
-      for (int nu = 0; nu < 4; ++nu) {
-        double sacc = 0.0;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-          for (int l = 0; l < 4; ++l) sacc += T[kk][l] * ck[(T_CONN + 10 * l + sidx(nu, kk)) * d.ts + toff];
-        rhs[1 + nu] += g.gdet * sacc;
-      }
+      ZoneState s;
+      zone_state<AXI>(ps, g, s);
+      l2 = s.l2;
+      double S[3];
+      source<AXI>(ps, s, g, up.gam, ct, d, off, S);
+      rhs[2] = rhs[2] + S[0];
+      rhs[3] = rhs[3] + S[1];
+      if constexpr (!AXI) rhs[4] = rhs[4] + S[2];
     }
     double U[NV];
     {
       double pb[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) pb[v] = Pb[v * d.sv + c];
-      Fluid<double> f;
-      fluid_state(pb, g, up.gam, f);
-      flux_of<0>(pb, f, g.gdet, U);
+      for (int v = 0; v < NV; ++v) pb[v] = buf_at(Pb + v * sv, c);
+      ZoneState s;
+      zone_state<AXI>(pb, g, s);
+      conserved<AXI>(pb, s, g, up.gam, U);
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) U[v] = U[v] + dt * rhs[v];
     double pn[NV];
-    failed = invert_1dw(U, ps, g, up.gam, pn) ? 1 : 0;
-    if (up.floors) apply_floors(pn, g, ck[T_RHOFL * d.ts + toff], ck[T_UFL * d.ts + toff], up);
+    failed = invert_1dw<AXI>(U, ps, l2, g, up, pn) ? 1 : 0;
+    if (up.floors) {
+      double rfl, ufl;
+      zone_floors<Z>(rfl, ufl, ct, d, off);
+      apply_floors<AXI>(pn, g, rfl, ufl, up);
+    }
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Pout[v * d.sv + c] = pn[v];
+    for (int v = 0; v < NV; ++v) Pout[v * sv + c] = pn[v];
     flags[c] = (int8_t)failed;
     // Non-finite values left in the state. The hydro primitives of a zone
     // whose inversion succeeded are finite (a non-finite result is a failure,
@@ -239,35 +278,41 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
   block_count_to(failed, &ctr->fail, &ctr->fail_total);
 }
 
-// (256, 3): at least three waves per SIMD, i.e. at most 168 registers a lane.
-// Left free the compiler takes 224 (two waves) and the kernel waits on its
-// loads and long dependency chains with too little to switch to; the FP64
-// variant fits 168 without spilling (the Cartesian Kerr-Schild variants,
-// which evaluate the metric, spill 4 registers and still gain: their loads
-// are the bound).
-template <typename TF, bool DEV_DT, bool CKS = false>
-__global__ __launch_bounds__(256, 3) void update_kernel(Dims d, const double* __restrict__ cent, CksBox box, UpdateParams up,
-                                                     FluxOut<TF> F, const double* Pb,
-                                                     const double* __restrict__ Ps, double* Pout,
-                                                     int8_t* __restrict__ flags, double dt,
-                                                     const double* __restrict__ dt_dev, double dt_scale,
-                                                     Counters* ctr) {
-  if (DEV_DT) dt = dt_scale * *dt_dev;
-  update_body<TF, false, CKS>(d, cent, box, up, F, Pb, Ps, Pout, flags, dt, ctr, (int)blockIdx.x);
+// Bound by HBM: 31 values a zone read (23 in the predictor, whose base state is
+// the flux state), 8 written, at 0.35 ms on the 288 x 128 x 128 torus 4.5 TB/s of
+// the 4.9 a device copy reaches; with the 4 x 4 metric, its inverse and the 40
+// connection coefficients read per zone (66 values against 38 in pairs) and
+// IEEE divisions it took 0.47 ms (mixed precision 0.29 against 0.42, Cartesian
+// Kerr-Schild 0.56 against 0.68). (256, 3): at least three waves per SIMD. Held
+// to four, the FP64 kernel takes 108 registers, keeps fewer loads in flight and
+// 0.46 ms.
+template <typename TF, int Z>
+__global__ __launch_bounds__(256, 3) void update_kernel(Dims d, const double* __restrict__ cent, UpdateParams up,
+                                                        FluxOut<TF> F, const double* Pb, const double* __restrict__ Ps,
+                                                        double* Pout, int8_t* __restrict__ flags, double dt,
+                                                        const double* __restrict__ dt_dev, double dt_scale,
+                                                        Counters* ctr) {
+  if (dt_dev) dt = dt_scale * *dt_dev;
+  update_body<TF, Z>(d, cent, up, F, Pb, Ps, Pout, flags, dt, ctr, (int)blockIdx.x);
 }
 
 // every job of a batch: predictor P -> P_h with dt/2, corrector (P, P_h) -> P with dt
-template <typename TF>
+template <typename TF, bool ALL_AXI>
 __global__ __launch_bounds__(256, 3) void update_batch_kernel(BatchView bv, int corrector) {
   const int* offs = bv.offs + PH_UPDATE * (bv.njobs + 1);
   const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
   const JobDesc& J = bv.jobs[jb];
   const double dt = corrector ? *J.dt : 0.5 * *J.dt;
-  // the FP64 batch variant runs faster with the source state loaded first (and
-  // without spilling); the float-flux one and the single-job kernels slower
-  update_body<TF, std::is_same<TF, double>::value>(J.d, global_ptr(J.t.cent), CksBox{}, J.up, flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv), global_ptr(J.P), global_ptr(corrector ? J.Ph : J.P),
-                  global_ptr(corrector ? J.P : J.Ph), global_ptr(J.flags), dt, global_ptr(J.ctr),
-                  (int)blockIdx.x - offs[jb]);
+  const FluxOut<TF> F = flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv);
+  const double* Ps = global_ptr(corrector ? J.Ph : J.P);
+  double* Pout = global_ptr(corrector ? J.P : J.Ph);
+  const int b = (int)blockIdx.x - offs[jb];
+  if (ALL_AXI || J.d.tk == 0)
+    update_body<TF, ZONE_AXI>(J.d, global_ptr(J.t.cent), J.up, F, global_ptr(J.P), Ps, Pout, global_ptr(J.flags), dt,
+                              global_ptr(J.ctr), b);
+  else
+    update_body<TF, ZONE_CKS>(J.d, global_ptr(J.t.cent), J.up, F, global_ptr(J.P), Ps, Pout, global_ptr(J.flags), dt,
+                              global_ptr(J.ctr), b);
 }
 
 // neighbour index along one direction for the fixup: across a periodic
@@ -316,11 +361,13 @@ __device__ void fixup_body(const Dims& d, const double* __restrict__ cent, const
   if (cnt > 0)
     for (int v = 0; v < 5; ++v) pn[v] = acc[v] / cnt;
   if (up.floors) {
-    const int toff = tab_of(d, j, i);
-    const double* ck = tab_plane(cent, d, k);
-    Geo<double> g;
-    load_geo(g, ck, d.ts, toff);
-    apply_floors(pn, g, ck[T_RHOFL * d.ts + toff], ck[T_UFL * d.ts + toff], up);
+    const int off = tab_of(d, j, i);
+    const double* ct = pair_plane(cent, d, k);
+    ZoneGeo g;
+    zone_geo<ZONE_ANY>(g, ct, d, off, i, j, k);
+    double rfl, ufl;
+    zone_floors<ZONE_ANY>(rfl, ufl, ct, d, off);
+    apply_floors<false>(pn, g, rfl, ufl, up);
   }
   bool fin = true;
   for (int v = 0; v < 5; ++v) {
@@ -348,44 +395,60 @@ __global__ __launch_bounds__(256) void fixup_batch_kernel(BatchView bv, int corr
              global_ptr(J.ctr), 0, (int)blockIdx.x - offs[jb]);
 }
 
+// prim->cons and cons->prim read and write 16 and 24 values a zone and are
+// bound by that traffic; blocks in the update's XCD-aware order
+template <int Z>
 __global__ __launch_bounds__(256) void p2u_kernel(Dims d, const double* __restrict__ cent, double gam,
                                                   const double* __restrict__ P, double* __restrict__ U) {
-  const int i = blockIdx.x * 64 + threadIdx.x;
-  const int j = blockIdx.y * 4 + threadIdx.y;
-  const int k = blockIdx.z;
-  if (i >= d.n1 || j >= d.n2) return;
+  constexpr bool AXI = Z == ZONE_AXI;
+  const TileK tk = xcd_tile_k((int)blockIdx.x, POINT_TX, POINT_TY, d.n1, d.n3);
+  const int i = tk.i0 + (int)threadIdx.x, j = tk.j0 + (int)threadIdx.y, k = tk.k;
+  if (!tk.valid || i >= d.n1 || j >= d.n2) return;
   const int c = cell_of(d, k, j, i);
-  Geo<double> g;
-  load_geo(g, tab_plane(cent, d, k), d.ts, tab_of(d, j, i));
+  const size_t sv = (size_t)d.sv;
   double p[NV], u[NV];
-  for (int v = 0; v < NV; ++v) p[v] = P[v * d.sv + c];
-  Fluid<double> f;
-  fluid_state(p, g, gam, f);
-  flux_of<0>(p, f, g.gdet, u);
-  for (int v = 0; v < NV; ++v) U[v * d.sv + c] = u[v];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) p[v] = buf_at(P + v * sv, c);
+  ZoneGeo g;
+  zone_geo<Z>(g, pair_plane(cent, d, k), d, tab_of(d, j, i), i, j, k);
+  ZoneState s;
+  zone_state<AXI>(p, g, s);
+  conserved<AXI>(p, s, g, gam, u);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) U[v * sv + c] = u[v];
 }
 
+template <int Z>
 __global__ __launch_bounds__(256) void u2p_kernel(Dims d, const double* __restrict__ cent, UpdateParams up,
                                                   const double* __restrict__ U, double* __restrict__ P,
                                                   int8_t* __restrict__ flags, Counters* ctr) {
-  const int i = blockIdx.x * 64 + threadIdx.x;
-  const int j = blockIdx.y * 4 + threadIdx.y;
-  const int k = blockIdx.z;
+  constexpr bool AXI = Z == ZONE_AXI;
+  const TileK tk = xcd_tile_k((int)blockIdx.x, POINT_TX, POINT_TY, d.n1, d.n3);
+  const int i = tk.i0 + (int)threadIdx.x, j = tk.j0 + (int)threadIdx.y, k = tk.k;
   int failed = 0;
-  if (i < d.n1 && j < d.n2) {
+  if (tk.valid && i < d.n1 && j < d.n2) {
     const int c = cell_of(d, k, j, i);
-    const int toff = tab_of(d, j, i);
-    const double* ck = tab_plane(cent, d, k);
-    Geo<double> g;
-    load_geo(g, ck, d.ts, toff);
+    const size_t sv = (size_t)d.sv;
+    const int off = tab_of(d, j, i);
+    const double* ct = pair_plane(cent, d, k);
     double u[NV], guess[NV], pn[NV];
+#pragma unroll
     for (int v = 0; v < NV; ++v) {
-      u[v] = U[v * d.sv + c];
-      guess[v] = P[v * d.sv + c];
+      u[v] = buf_at(U + v * sv, c);
+      guess[v] = buf_at(P + v * sv, c);
     }
-    failed = invert_1dw(u, guess, g, up.gam, pn) ? 1 : 0;
-    if (up.floors) apply_floors(pn, g, ck[T_RHOFL * d.ts + toff], ck[T_UFL * d.ts + toff], up);
-    for (int v = 0; v < NV; ++v) P[v * d.sv + c] = pn[v];
+    ZoneGeo g;
+    zone_geo<Z>(g, ct, d, off, i, j, k);
+    double u1, u2, u3;
+    lower3<AXI>(g, guess[2], guess[3], guess[4], u1, u2, u3);
+    failed = invert_1dw<AXI>(u, guess, guess[2] * u1 + guess[3] * u2 + guess[4] * u3 + 1.0, g, up, pn) ? 1 : 0;
+    if (up.floors) {
+      double rfl, ufl;
+      zone_floors<Z>(rfl, ufl, ct, d, off);
+      apply_floors<AXI>(pn, g, rfl, ufl, up);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) P[v * sv + c] = pn[v];
     flags[c] = (int8_t)failed;
   }
   block_count_to(failed, &ctr->fail);
@@ -393,42 +456,29 @@ __global__ __launch_bounds__(256) void u2p_kernel(Dims d, const double* __restri
 
 }  // namespace
 
+namespace {
+
+template <typename TF>
+void update_for(const Dims& d, const Tables& t, const UpdateParams& up, const void* F, const double* Pb,
+                const double* Ps, double* Pout, int8_t* flags, double dt, const double* dt_dev, double dt_scale,
+                Counters* ctr, hipStream_t s) {
+  const dim3 grd(xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty)), blk(d.utx, d.uty, 1);
+  const FluxOut<TF> f = flux_out<TF>((unsigned char*)F, d.sv);
+  if (d.tk != 0)
+    hipLaunchKernelGGL((update_kernel<TF, ZONE_CKS>), grd, blk, 0, s, d, t.cent, up, f, Pb, Ps, Pout, flags, dt, dt_dev,
+                       dt_scale, ctr);
+  else
+    hipLaunchKernelGGL((update_kernel<TF, ZONE_AXI>), grd, blk, 0, s, d, t.cent, up, f, Pb, Ps, Pout, flags, dt, dt_dev,
+                       dt_scale, ctr);
+}
+
+}  // namespace
+
 hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const UpdateParams& up, const void* F,
-                         const double* Pb, const double* Ps, double* Pout,
-                         int8_t* flags, double dt, const double* dt_dev, double dt_scale, Counters* ctr,
-                         hipStream_t s, const grmhd_problem* cks) {
-  const unsigned nblk = xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty);
-  dim3 blk(d.utx, d.uty, 1), grd(nblk);
-  const CksBox box = cks ? cks_box(*cks) : CksBox{};
-  if (mixed) {
-    const FluxOut<float> f = flux_out<float>((unsigned char*)F, d.sv);
-    if (cks && dt_dev)
-      hipLaunchKernelGGL((update_kernel<float, true, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
-                         Pout, flags, dt, dt_dev, dt_scale, ctr);
-    else if (cks)
-      hipLaunchKernelGGL((update_kernel<float, false, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
-                         Pout, flags, dt, dt_dev, dt_scale, ctr);
-    else if (dt_dev)
-      hipLaunchKernelGGL((update_kernel<float, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
-                         flags, dt, dt_dev, dt_scale, ctr);
-    else
-      hipLaunchKernelGGL((update_kernel<float, false>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
-                         flags, dt, dt_dev, dt_scale, ctr);
-  } else {
-    const FluxOut<double> f = flux_out<double>((unsigned char*)F, d.sv);
-    if (cks && dt_dev)
-      hipLaunchKernelGGL((update_kernel<double, true, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
-                         Pout, flags, dt, dt_dev, dt_scale, ctr);
-    else if (cks)
-      hipLaunchKernelGGL((update_kernel<double, false, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps,
-                         Pout, flags, dt, dt_dev, dt_scale, ctr);
-    else if (dt_dev)
-      hipLaunchKernelGGL((update_kernel<double, true>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
-                         flags, dt, dt_dev, dt_scale, ctr);
-    else
-      hipLaunchKernelGGL((update_kernel<double, false>), grd, blk, 0, s, d, t.cent, box, up, f, Pb, Ps, Pout,
-                         flags, dt, dt_dev, dt_scale, ctr);
-  }
+                         const double* Pb, const double* Ps, double* Pout, int8_t* flags, double dt,
+                         const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s) {
+  if (mixed) update_for<float>(d, t, up, F, Pb, Ps, Pout, flags, dt, dt_dev, dt_scale, ctr, s);
+  else update_for<double>(d, t, up, F, Pb, Ps, Pout, flags, dt, dt_dev, dt_scale, ctr, s);
   return hipGetLastError();
 }
 
@@ -446,8 +496,10 @@ hipError_t launch_batch_update(const BatchView& bv, const int* totals, bool mixe
   const dim3 blk(bv.utx, bv.uty, 1), grd(totals[PH_UPDATE]);
   const int c = corrector ? 1 : 0;
   if (which & 1) {
-    if (mixed) hipLaunchKernelGGL(update_batch_kernel<float>, grd, blk, 0, s, bv, c);
-    else hipLaunchKernelGGL(update_batch_kernel<double>, grd, blk, 0, s, bv, c);
+    if (mixed && bv.axi) hipLaunchKernelGGL((update_batch_kernel<float, true>), grd, blk, 0, s, bv, c);
+    else if (mixed) hipLaunchKernelGGL((update_batch_kernel<float, false>), grd, blk, 0, s, bv, c);
+    else if (bv.axi) hipLaunchKernelGGL((update_batch_kernel<double, true>), grd, blk, 0, s, bv, c);
+    else hipLaunchKernelGGL((update_batch_kernel<double, false>), grd, blk, 0, s, bv, c);
   }
   if (which & 2) hipLaunchKernelGGL(fixup_batch_kernel, grd, blk, 0, s, bv, c);
   return hipGetLastError();
@@ -455,14 +507,16 @@ hipError_t launch_batch_update(const BatchView& bv, const int* totals, bool mixe
 
 hipError_t launch_prim_to_cons(const Dims& d, const Tables& t, double gam, const double* P, double* U,
                                hipStream_t s) {
-  dim3 blk(64, 4, 1), grd((d.n1 + 63) / 64, (d.n2 + 3) / 4, d.n3);
-  hipLaunchKernelGGL(p2u_kernel, grd, blk, 0, s, d, t.cent, gam, P, U);
+  const dim3 blk(POINT_TX, POINT_TY, 1), grd(xcd_grid(d.n1, d.n2, d.n3, POINT_TX, POINT_TY));
+  if (d.tk != 0) hipLaunchKernelGGL(p2u_kernel<ZONE_CKS>, grd, blk, 0, s, d, t.cent, gam, P, U);
+  else hipLaunchKernelGGL(p2u_kernel<ZONE_AXI>, grd, blk, 0, s, d, t.cent, gam, P, U);
   return hipGetLastError();
 }
 
 hipError_t launch_cons_to_prim(const Dims& d, const Tables& t, const UpdateParams& up, const double* U,
                                double* P, int8_t* flags, Counters* ctr, hipStream_t s) {
-  dim3 blk(64, 4, 1), grd((d.n1 + 63) / 64, (d.n2 + 3) / 4, d.n3);
-  hipLaunchKernelGGL(u2p_kernel, grd, blk, 0, s, d, t.cent, up, U, P, flags, ctr);
+  const dim3 blk(POINT_TX, POINT_TY, 1), grd(xcd_grid(d.n1, d.n2, d.n3, POINT_TX, POINT_TY));
+  if (d.tk != 0) hipLaunchKernelGGL(u2p_kernel<ZONE_CKS>, grd, blk, 0, s, d, t.cent, up, U, P, flags, ctr);
+  else hipLaunchKernelGGL(u2p_kernel<ZONE_AXI>, grd, blk, 0, s, d, t.cent, up, U, P, flags, ctr);
   return hipGetLastError();
 }
