@@ -387,48 +387,85 @@ __device__ inline T mc_slope(T pm, T p0, T pp) {
 }
 
 // Value at the right edge of the middle zone of (x1..x5), point-value WENO5
-// with Jiang-Shu smoothness indicators and linear weights (1/16, 5/8, 5/16):
-// weights d_k / (eps + b_k)^2, normalised. Written over a common denominator,
-// scaled by the smallest e_k = eps + b_k so nothing leaves the double range:
-// with r_k = e_k / e_min >= 1, the weights are proportional to d_k times the
-// product of the other two r_j^2 (two divisions instead of four).
+// with Jiang-Shu smoothness indicators b_k and linear weights (1/16, 5/8, 5/16):
+// weights d_k / (eps + b_k)^2, normalised, eps = 1e-26. Written in the
+// differences d_k = x_(k+1) - x_k: the candidates are x3 plus two of them, and
+// 4 b_k = (13/3) t_k^2 + u_k^2 with t_k their differences. e_k = 4 (eps + b_k).
+template <typename T>
+struct Weno {
+  T d1, d2, d3, d4, e0, e1, e2, m;
+  __device__ Weno(T x1, T x2, T x3, T x4, T x5) {
+    d1 = x2 - x1;
+    d2 = x3 - x2;
+    d3 = x4 - x3;
+    d4 = x5 - x4;
+    const T t0 = d2 - d1, t1 = d3 - d2, t2 = d4 - d3;
+    const T u0 = T(2) * d2 + t0, u1 = d2 + d3, u2 = T(2) * d3 - t2;
+    constexpr T C = T(13.0 / 3.0), EPS = T(4e-26);
+    e0 = u0 * u0 + EPS;
+    e1 = u1 * u1 + EPS;
+    e2 = u2 * u2 + EPS;
+    e0 = (C * t0) * t0 + e0;
+    e1 = (C * t1) * t1 + e1;
+    e2 = (C * t2) * t2 + e2;
+    m = fmin(fmin(e0, e1), e2);
+  }
+  // x3 and the mean of the candidates' distances from it with weights a_k
+  __device__ T mean(T x3, T a0, T a1, T a2) const {
+    const T q0 = T(0.875) * d2 - T(0.375) * d1;
+    const T q1 = T(0.375) * d3 + T(0.125) * d2;
+    const T q2 = T(0.625) * d3 - T(0.125) * d4;
+    return (a0 * q0 + a1 * q1 + a2 * q2) * rcp_full(a0 + a1 + a2) + x3;
+  }
+  // the same at the left edge: what mean gives with the zones in reverse order
+  // (d_k <-> -d_(5-k), a_0 <-> a_2), bit for bit
+  __device__ T mirrored(T x3, T a0, T a1, T a2) const {
+    const T q0 = T(0.375) * d4 - T(0.875) * d3;
+    const T q1 = T(-0.375) * d2 - T(0.125) * d3;
+    const T q2 = T(0.125) * d1 - T(0.625) * d2;
+    return (a2 * q0 + a1 * q1 + a0 * q2) * rcp_full(a2 + a1 + a0) + x3;
+  }
+};
+
+// Over a common denominator, scaled by the smallest e_k so nothing leaves the
+// double range: with r_k = e_k / e_min >= 1 the weights are proportional to d_k
+// times the product of the other two r_j^2 (two reciprocals instead of four).
 __device__ inline double weno5_edge(double x1, double x2, double x3, double x4, double x5) {
-  const double q0 = 0.375 * x1 - 1.25 * x2 + 1.875 * x3;
-  const double q1 = -0.125 * x2 + 0.75 * x3 + 0.375 * x4;
-  const double q2 = 0.375 * x3 + 0.75 * x4 - 0.125 * x5;
-  const double t0 = x1 - 2.0 * x2 + x3, u0 = x1 - 4.0 * x2 + 3.0 * x3;
-  const double t1 = x2 - 2.0 * x3 + x4, u1 = x2 - x4;
-  const double t2 = x3 - 2.0 * x4 + x5, u2 = 3.0 * x3 - 4.0 * x4 + x5;
-  const double e0 = 1e-26 + ((13.0 / 12.0) * t0 * t0 + 0.25 * u0 * u0);
-  const double e1 = 1e-26 + ((13.0 / 12.0) * t1 * t1 + 0.25 * u1 * u1);
-  const double e2 = 1e-26 + ((13.0 / 12.0) * t2 * t2 + 0.25 * u2 * u2);
-  const double im = 1.0 / fmin(fmin(e0, e1), e2);
+  const Weno<double> w(x1, x2, x3, x4, x5);
+  const double im = rcp_full(w.m);
   // r_k <= 1e60 keeps the products of two squares finite; such a weight is 0 anyway
-  const double r0 = fmin(e0 * im, 1e60), r1 = fmin(e1 * im, 1e60), r2 = fmin(e2 * im, 1e60);
+  const double r0 = fmin(w.e0 * im, 1e60), r1 = fmin(w.e1 * im, 1e60), r2 = fmin(w.e2 * im, 1e60);
   const double s0 = r0 * r0, s1 = r1 * r1, s2 = r2 * r2;
-  const double a0 = 0.0625 * (s1 * s2), a1 = 0.625 * (s0 * s2), a2 = 0.3125 * (s0 * s1);
-  return (a0 * q0 + a1 * q1 + a2 * q2) / (a0 + a1 + a2);
+  return w.mean(x3, s1 * s2, 10.0 * (s0 * s2), 5.0 * (s0 * s1));
+}
+// both edges of the middle zone, which share the smoothness indicators
+__device__ inline void weno5_edges(double x1, double x2, double x3, double x4, double x5, double& left, double& right) {
+  const Weno<double> w(x1, x2, x3, x4, x5);
+  const double im = rcp_full(w.m);
+  const double r0 = fmin(w.e0 * im, 1e60), r1 = fmin(w.e1 * im, 1e60), r2 = fmin(w.e2 * im, 1e60);
+  const double s0 = r0 * r0, s1 = r1 * r1, s2 = r2 * r2;
+  const double p0 = s1 * s2, p1 = 10.0 * (s0 * s2), p2 = s0 * s1;
+  right = w.mean(x3, p0, p1, 5.0 * p2);
+  left = w.mirrored(x3, 5.0 * p0, p1, p2);
 }
 
 // FP32 form: eps^2 = 1e-52 is below the float range, so the weights use the
 // ratios r_k = e_min / e_k in (0, 1]: d_k r_k^2, normalised; the term of the
-// smallest e_k has r = 1, so the sum is at least 1/16. Reciprocals by the
+// smallest e_k has r = 1, so the sum is at least its d_k. Ratios by the
 // hardware rcp (about 1 ulp), far below the float rounding of the inputs.
 __device__ inline float weno5_edge(float x1, float x2, float x3, float x4, float x5) {
-  const float q0 = 0.375f * x1 - 1.25f * x2 + 1.875f * x3;
-  const float q1 = -0.125f * x2 + 0.75f * x3 + 0.375f * x4;
-  const float q2 = 0.375f * x3 + 0.75f * x4 - 0.125f * x5;
-  const float t0 = x1 - 2.0f * x2 + x3, u0 = x1 - 4.0f * x2 + 3.0f * x3;
-  const float t1 = x2 - 2.0f * x3 + x4, u1 = x2 - x4;
-  const float t2 = x3 - 2.0f * x4 + x5, u2 = 3.0f * x3 - 4.0f * x4 + x5;
-  const float e0 = 1e-26f + ((13.0f / 12.0f) * t0 * t0 + 0.25f * u0 * u0);
-  const float e1 = 1e-26f + ((13.0f / 12.0f) * t1 * t1 + 0.25f * u1 * u1);
-  const float e2 = 1e-26f + ((13.0f / 12.0f) * t2 * t2 + 0.25f * u2 * u2);
-  const float m = fminf(fminf(e0, e1), e2);
-  const float r0 = m * __builtin_amdgcn_rcpf(e0), r1 = m * __builtin_amdgcn_rcpf(e1),
-              r2 = m * __builtin_amdgcn_rcpf(e2);
-  const float a0 = 0.0625f * r0 * r0, a1 = 0.625f * r1 * r1, a2 = 0.3125f * r2 * r2;
-  return (a0 * q0 + a1 * q1 + a2 * q2) * __builtin_amdgcn_rcpf(a0 + a1 + a2);
+  const Weno<float> w(x1, x2, x3, x4, x5);
+  const float r0 = w.m * __builtin_amdgcn_rcpf(w.e0), r1 = w.m * __builtin_amdgcn_rcpf(w.e1),
+              r2 = w.m * __builtin_amdgcn_rcpf(w.e2);
+  return w.mean(x3, r0 * r0, 10.0f * (r1 * r1), 5.0f * (r2 * r2));
+}
+__device__ inline void weno5_edges(float x1, float x2, float x3, float x4, float x5, float& left, float& right) {
+  const Weno<float> w(x1, x2, x3, x4, x5);
+  const float r0 = w.m * __builtin_amdgcn_rcpf(w.e0), r1 = w.m * __builtin_amdgcn_rcpf(w.e1),
+              r2 = w.m * __builtin_amdgcn_rcpf(w.e2);
+  const float p0 = r0 * r0, p1 = 10.0f * (r1 * r1), p2 = r2 * r2;
+  right = w.mean(x3, p0, p1, 5.0f * p2);
+  left = w.mirrored(x3, 5.0f * p0, p1, p2);
 }
 
 // ---------------------------------------------------------------------------
@@ -476,8 +513,10 @@ __host__ __device__ inline FluxOut<T> flux_out(unsigned char* base, int sv) {
   return o;
 }
 
-// its tiles cover the cells -1..n and overlap by one
-__host__ __device__ inline int sweep_tiles(int n, int b) { return (n + 1 + b - 2) / (b - 1); }
+// its tiles cover the cells -1..n; they overlap by two columns in x1 (a face
+// needs the cell before it, a divergence the face after it) and one row in x2
+__host__ __device__ inline int sweep_tiles_x1(int n, int b) { return (n + 1 + b - 3) / (b - 2); }
+__host__ __device__ inline int sweep_tiles_x2(int n, int b) { return (n + 1 + b - 2) / (b - 1); }
 // Block shapes of the face-flux pass, BX x BY threads in rows no longer than a
 // wave. The large one is 64 x 8, or 32 x 16 for FP64 WENO5, whose 64 x 8 plane
 // and exchange take 86 KB of LDS and leave one block a CU (131 x 67 x 45 torus:
@@ -491,7 +530,7 @@ __host__ __device__ constexpr int large_bx(int recon, bool mixed) { return recon
 __host__ __device__ constexpr int large_by(int recon, bool mixed) { return 512 / large_bx(recon, mixed); }
 // blocks of a grid in the shape (bx, by)
 inline long long sweep_grid(const Dims& d, int bx, int by) {
-  return (long long)sweep_tiles(d.n1, bx) * sweep_tiles(d.n2, by) * ((d.n3 + 2 + NXCD - 1) / NXCD) * NXCD;
+  return (long long)sweep_tiles_x1(d.n1, bx) * sweep_tiles_x2(d.n2, by) * ((d.n3 + 2 + NXCD - 1) / NXCD) * NXCD;
 }
 // is the small shape right for a pass that makes so many large blocks? Tiles
 // set below 512 threads ask for it too.
@@ -510,11 +549,11 @@ struct SweepTile {
 // share its geometry and their x3 stencils in the XCD's L2, and the next tile
 // finds the rows it shares with them there
 __device__ inline SweepTile sweep_tile(const Dims& d, int bx, int by, int b) {
-  const int ty = sweep_tiles(d.n2, by), planes = d.n3 + 2, chunk = (planes + NXCD - 1) / NXCD;
+  const int ty = sweep_tiles_x2(d.n2, by), planes = d.n3 + 2, chunk = (planes + NXCD - 1) / NXCD;
   const int x = b % NXCD, w = b / NXCD, tile = w / chunk;
   SweepTile t;
   t.k = -1 + x * chunk + (w - tile * chunk);
-  t.i0 = -1 + (tile / ty) * (bx - 1);
+  t.i0 = -1 + (tile / ty) * (bx - 2);
   t.j0 = -1 + (tile % ty) * (by - 1);
   t.valid = t.k <= d.n3;
   return t;

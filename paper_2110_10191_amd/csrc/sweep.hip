@@ -17,8 +17,8 @@
 // x3 stencil from the state) and computes the x3, x1 and x2 face of each cell.
 // The x1 neighbours' fluxes come from the next and previous lane (a row of the
 // tile lies within a wave), the x2 neighbours' through LDS. A cell's divergence
-// needs the next thread of its row and the next row, its EMFs the previous
-// ones, so neighbouring tiles overlap by one cell; what needs the plane above
+// needs the next thread of its row and the next row, its EMFs and x1 face the
+// previous ones, so neighbouring tiles overlap by two columns and one row; what needs the plane above
 // or below (the x3 fluxes, the x1 and x2 flux of B3) goes out as it is.
 //
 // What bounds it: FP64 issue and the latency of its loads, about half each (a
@@ -35,7 +35,13 @@
 // geometry falls out of the L2 between planes: 0.50 ms.
 //
 // The face states are written in the 3+1 form (side_speeds, side_flux): 12 or
-// 14 geometry values a face.
+// 14 geometry values a face. WENO5 is bound by its arithmetic (2800 VALU
+// instructions a wave in mixed precision). In x1 a lane finds both edges of its
+// own zone, which share the smoothness indicators (MC: the slope), and passes
+// the right one on; with the indicators in differences and one corrected
+// reciprocal per division the pass takes 0.48 ms on the benchmark torus in
+// mixed precision (0.55 with the plain formula at every face) and 89 us on
+// 131 x 67 x 45 in FP64 (117).
 //
 // The per-direction maximum of ctop over the faces with interior transverse
 // index feeds the Courant step (one atomic max per block and direction); a
@@ -67,9 +73,11 @@ enum { GEO_AXI = 0, GEO_TABLE, GEO_CKS };
 // such addresses in registers and spilled).
 template <int RECON, int BX, int BY>
 struct PlaneShape {
-  // halo of the reconstruction: zones below / above the cell (MC 2 / 1, WENO5 3 / 2)
-  static constexpr int LO = RECON == GRMHD_RECON_MC ? 2 : 3, HI = RECON == GRMHD_RECON_MC ? 1 : 2;
-  static constexpr int LW = BX + LO + HI, LH = BY + LO + HI, PLANE = LW * LH, NTHR = BX * BY;
+  // halo: zones before / after the cell in x1 (both edges of the zone are found together) and
+  // below / above it in x2 (the faces of a row need the zones below)
+  static constexpr int LX = RECON == GRMHD_RECON_MC ? 1 : 2, HX = LX;
+  static constexpr int LY = RECON == GRMHD_RECON_MC ? 2 : 3, HY = LY - 1;
+  static constexpr int LW = BX + LX + HX, LH = BY + LY + HY, PLANE = LW * LH, NTHR = BX * BY;
 };
 
 // the value a lane's neighbour holds: the next lane of the wave, or the
@@ -97,7 +105,23 @@ __device__ inline void face_sides(const double* __restrict__ P, size_t sv, const
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const T* ql = q + v * SH::PLANE;
-    constexpr int st = (D == 1) ? 1 : SH::LW;
+    if constexpr (D == 1) {
+      // both edges of the cell's zone, which share slope or smoothness; the left side of its
+      // lower face is the right edge of the zone the lane before holds (a row's first lane
+      // has none: its face is not used)
+      T right;
+      if constexpr (RECON == GRMHD_RECON_MC) {
+        const T e = ql[0];
+        const McSlope<T> m(e - ql[-1], ql[1] - e);
+        R.P[v] = m.below(e);
+        right = m.above(e);
+      } else {
+        weno5_edges(ql[-2], ql[-1], ql[0], ql[1], ql[2], R.P[v], right);
+      }
+      L.P[v] = prev_lane(right);
+      continue;
+    }
+    constexpr int st = SH::LW;
     // the cell's own value from the LDS tile in every direction
     auto at = [&](int o) -> T { return (D == 3 && o != 0) ? (T)buf_f64(P + v * sv, cb + (unsigned)o * pb) : ql[o * st]; };
     if constexpr (RECON == GRMHD_RECON_MC) {
@@ -161,14 +185,15 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
   const bool ok = i <= d.n1 && j <= d.n2;
   extern __shared__ __align__(16) unsigned char sweep_lds[];
   T* const L = reinterpret_cast<T*>(sweep_lds);
-  const T* const q = L + (lj + SH::LO) * SH::LW + li + SH::LO;
+  const T* const q = L + (lj + SH::LY) * SH::LW + li + SH::LX;
   const int tid = lj * BX + li;
   T* const X = L + NV * SH::PLANE + tid;  // this thread's slot of the exchange, [NEXCH][BY][BX]
-  const int ib = t.i0 - SH::LO, jb = t.j0 - SH::LO;
-  // the cells this thread writes: a divergence needs the next thread of the row and the next
-  // row, an EMF the previous ones
-  const bool wd = i >= 0 && i < d.n1 && j >= 0 && j < d.n2 && li < BX - 1 && lj < BY - 1;
-  const bool we = ok && i >= 0 && j >= 0 && li > 0 && lj > 0;
+  const int ib = t.i0 - SH::LX, jb = t.j0 - SH::LY;
+  // the cells this thread writes: an x1 face needs the previous thread of the row, a divergence
+  // the next one and the next row, an EMF the previous ones
+  const bool col = li > 0 && li < BX - 1;
+  const bool wd = col && i >= 0 && i < d.n1 && j >= 0 && j < d.n2 && lj < BY - 1;
+  const bool we = col && ok && i >= 0 && j >= 0 && lj > 0;
   const bool axis = (a.polar_lo && j == 0) || (a.polar_hi && j == d.n2);
   const bool in1 = i >= 0 && i < d.n1, in2 = j >= 0 && j < d.n2;
   // threads beyond the grid, and on faces no one asks for, compute on the nearest cell's data
@@ -222,7 +247,7 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
     geo(1, a.t1, g);
     FaceSide<T> SL, SR;
     face_sides<1, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
-    face_flux<1, AXI, CTOP>(SL, SR, g, a.gam, f, X + SH::NTHR, ok && i >= 0 && in2 && hydro);
+    face_flux<1, AXI, CTOP>(SL, SR, g, a.gam, f, X + SH::NTHR, li > 0 && ok && i >= 0 && in2 && hydro);
     // no mass enters through an outflow boundary: the rest-mass flux through
     // the inner radial face is at most 0, through the outer one at least 0
     if (d.out_lo && i == 0) f[0] = fmin(f[0], T(0));

@@ -9,9 +9,9 @@ import problems
 
 pytestmark = pytest.mark.gpu
 
-# grids of more than 1024 large blocks: whole tiles (188 + 1 = 3 x 63, 62 + 1 =
-# 9 x 7, 185 + 1 = 6 x 31, 59 + 1 = 4 x 15), one cell more, and ragged ones
-GRIDS = [(188, 62, 46), (189, 63, 45), (185, 59, 46), (131, 61, 40)]
+# grids of more than 1024 large blocks: whole tiles (185 + 1 = 3 x 62, 62 + 1 =
+# 9 x 7, 179 + 1 = 6 x 30, 59 + 1 = 4 x 15), one cell more, and ragged ones
+GRIDS = [(185, 62, 46), (186, 63, 45), (179, 59, 46), (131, 61, 40)]
 
 
 @pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "x".join(map(str, g)))
