@@ -32,6 +32,46 @@ __device__ inline double cks_radius(double x, double y, double z, double a) {
   return sqrt(h + sqrt(h * h + a * a * z * z));
 }
 
+// f and l_i at (x, y, z)
+__device__ inline void cks_null(double x, double y, double z, double a, double& f, double& l1, double& l2, double& l3) {
+#pragma clang fp contract(off)
+  const double h = 0.5 * (x * x + y * y + z * z - a * a);
+  const double r = sqrt_full(h + sqrt_full(h * h + a * a * z * z));
+  const double r2 = r * r;
+  f = 2.0 * r2 * r * rcp_full(r2 * r2 + a * a * z * z);
+  const double ira = rcp_full(r2 + a * a);
+  l1 = (r * x + a * y) * ira;
+  l2 = (r * y - a * x) * ira;
+  l3 = z * rcp_full(r);
+}
+
+// step of the centred differences of the metric
+constexpr double FD_DELTA = 1e-5;
+
+// g_mn at (x, y, z) in the symmetric order, by the operations of its formula
+// one by one (the difference quotients multiply a last-place change by 1e5)
+__device__ inline void cks_gcov(double x, double y, double z, double a, double* g) {
+#pragma clang fp contract(off)
+  const double h = 0.5 * (x * x + y * y + z * z - a * a);
+  const double r = sqrt_full(h + sqrt_full(h * h + a * a * z * z));
+  const double r2 = r * r;
+  const double fd = r2 * r2 + a * a * z * z, ra = r2 + a * a;
+  const double f = div_by(2.0 * r2 * r, fd, rcp_full(fd));
+  const double ira = rcp_full(ra);
+  const double l1 = div_by(r * x + a * y, ra, ira), l2 = div_by(r * y - a * x, ra, ira), l3 = div_by(z, r, rcp_full(r));
+  const double f1 = f * l1, f2 = f * l2, f3 = f * l3;
+  g[0] = f - 1.0;
+  g[1] = f1;
+  g[2] = f2;
+  g[3] = f3;
+  g[4] = f1 * l1 + 1.0;
+  g[5] = f1 * l2;
+  g[6] = f1 * l3;
+  g[7] = f2 * l2 + 1.0;
+  g[8] = f2 * l3;
+  g[9] = f3 * l3 + 1.0;
+}
+
 // at the lower D-face (D = 1..3) of cell (i, j, k), in the 3+1 form of the face
 // tables: g_ij = delta_ij + f l_i l_j, alpha^2 = 1/(1 + f), beta^i = alpha^2 f
 // l_i, gamma^ij = delta_ij - alpha^2 f l_i l_j
@@ -40,14 +80,10 @@ __device__ inline void cks_face_geo(const CksBox& b, int D, int i, int j, int k,
   const double x = b.x0[0] + (D == 1 ? (double)i : i + 0.5) * b.dx[0];
   const double y = b.x0[1] + (D == 2 ? (double)j : j + 0.5) * b.dx[1];
   const double z = b.x0[2] + (D == 3 ? (double)k : k + 0.5) * b.dx[2];
-  const double a = b.a;
-  const double r = cks_radius(x, y, z, a);
-  const double r2 = r * r;
-  const double f = 2.0 * r2 * r / (r2 * r2 + a * a * z * z);
-  const double ira = 1.0 / (r2 + a * a);
-  const double l1 = (r * x + a * y) * ira, l2 = (r * y - a * x) * ira, l3 = z / r;
+  double f, l1, l2, l3;
+  cks_null(x, y, z, b.a, f, l1, l2, l3);
   const double f1 = f * l1, f2 = f * l2, f3 = f * l3;
-  const double ia = sqrt(1.0 + f), al = 1.0 / ia, a2 = al * al;
+  const double al = rsqrt_full(1.0 + f), ia = (1.0 + f) * al, a2 = al * al;
   g.g11 = f1 * l1 + 1.0;
   g.g12 = f1 * l2;
   g.g13 = f1 * l3;
@@ -63,20 +99,22 @@ __device__ inline void cks_face_geo(const CksBox& b, int D, int i, int j, int k,
   g.hgdet = 0.5;
 }
 
-// at the centre of cell (i, j, k)
+// the centre of cell (i, j, k), and the geometry there
+__device__ inline void cks_centre(const CksBox& b, int i, int j, int k, double* x) {
+#pragma clang fp contract(off)
+  x[0] = b.x0[0] + (i + 0.5) * b.dx[0];
+  x[1] = b.x0[1] + (j + 0.5) * b.dx[1];
+  x[2] = b.x0[2] + (k + 0.5) * b.dx[2];
+}
 __device__ inline void cks_centre_geo(const CksBox& b, int i, int j, int k, ZoneGeo& g) {
 #pragma clang fp contract(off)
-  const double x = b.x0[0] + (i + 0.5) * b.dx[0];
-  const double y = b.x0[1] + (j + 0.5) * b.dx[1];
-  const double z = b.x0[2] + (k + 0.5) * b.dx[2];
-  const double a = b.a;
-  const double r = cks_radius(x, y, z, a);
-  const double r2 = r * r;
-  const double f = 2.0 * r2 * r / (r2 * r2 + a * a * z * z);
-  const double ira = 1.0 / (r2 + a * a);
-  const double l1 = (r * x + a * y) * ira, l2 = (r * y - a * x) * ira, l3 = z / r;
+  double c[3];
+  cks_centre(b, i, j, k, c);
+  const double x = c[0], y = c[1], z = c[2];
+  double f, l1, l2, l3;
+  cks_null(x, y, z, b.a, f, l1, l2, l3);
   const double f1 = f * l1, f2 = f * l2, f3 = f * l3;
-  const double ia = sqrt(1.0 + f), al = 1.0 / ia, a2 = al * al;
+  const double al = rsqrt_full(1.0 + f), ia = (1.0 + f) * al, a2 = al * al;
   g.g11 = f1 * l1 + 1.0;
   g.g12 = f1 * l2;
   g.g13 = f1 * l3;
@@ -135,11 +173,12 @@ __device__ inline void zone_geo(ZoneGeo& g, const double* ct, const Dims& d, int
 template <int Z>
 __device__ inline void zone_floors(double& rfl, double& ufl, const double* ct, const Dims& d, int off) {
   if (Z == ZONE_CKS || (Z == ZONE_ANY && d.tk != 0)) {
-    rfl = zone_pair(ct, d, off, K_RHOFL & ~1).y;
-    ufl = zone_pair(ct, d, off, K_UFL).x;
+    const double2 q = zone_pair(ct, d, off, K_RHOFL);
+    rfl = q.x;
+    ufl = q.y;
   } else {
     rfl = zone_pair(ct, d, off, C_RHOFL & ~1).y;
     ufl = zone_pair(ct, d, off, C_UFL).x;
   }
 }
-static_assert((K_RHOFL & 1) && !(K_UFL & 1) && (C_RHOFL & 1) && !(C_UFL & 1) && !(C_IGDET & 1), "pairs of the centre table");
+static_assert(!(K_RHOFL & 1) && K_UFL == K_RHOFL + 1 && (C_RHOFL & 1) && !(C_UFL & 1) && !(C_IGDET & 1), "pairs of the centre table");

@@ -28,16 +28,15 @@
 // Centre table components, in pairs. MKS, FMKS and Minkowski (g_23 = beta^3 =
 // 0): the 3+1 metric, the source coefficients S_k of x1 and x2 (eight
 // derivatives each, then the pressure's), gamma^ij, 1/sqrt(-g), floor scales.
-// Cartesian Kerr-Schild, whose metric the kernels evaluate themselves: the
-// source coefficients of x1, x2 and x3 (ten derivatives each, then the
-// pressure's), floor scales and sqrt(-g).
+// Cartesian Kerr-Schild, whose metric and its differences the kernels evaluate
+// themselves: floor scales and sqrt(-g).
 // The source of the momentum along x^n is sqrt(-g) T^km d_n g_km / 2 (zero for
 // the energy, the metric being stationary): the coefficients are sqrt(-g) d_n
 // g_km, halved for k = m, and sqrt(-g) g^km d_n g_km / 2 for the pressure.
 enum {
   C_G11 = 0, C_G12, C_G13, C_G22, C_G33, C_ALPHA, C_B1, C_B2, C_IALPHA, C_GDET,
   C_S1 = 10, C_S2 = 19, C_H11 = 28, C_H12, C_H13, C_H22, C_H23, C_H33, C_IGDET, C_RHOFL, C_UFL,
-  K_S1 = 0, K_S2 = 11, K_S3 = 22, K_RHOFL = 33, K_UFL, K_GDET,
+  K_RHOFL = 0, K_UFL, K_GDET,
   N_CENT = 64  // components the centre table has room for
 };
 // the (k, m) of the eight derivatives of an axisymmetric table
@@ -198,6 +197,13 @@ __device__ inline double sqrt_full(double x) {
   return fma(fma(-g1, g1, x), h1, g1);
 }
 __device__ inline float sqrt_full(float x) { return __builtin_amdgcn_sqrtf(x); }
+
+// a / b from r = rcp_full(b) with one correction of the quotient, which rounds
+// it as the IEEE division does but for rare last-place misses
+__device__ inline double div_by(double a, double b, double r) {
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
 
 // One side of a face of direction D (1..3), in two steps: side_speeds finds the
 // fast-magnetosonic speeds and what it needs for them, and once both sides'

@@ -1,5 +1,6 @@
 // Geometry tables: the metric in 3+1 form at zone centres and faces, the source
-// coefficients (centred differences of the metric) and floor scales at centres.
+// coefficients (centred differences of the metric) and floor scales at centres
+// (in Cartesian Kerr-Schild only floor scales: the kernels evaluate the rest).
 // Implementation Notes section: every metric-dependent quantity is
 // evaluated numerically from an analytic line element, the coordinates act as
 // static mesh refinement (MKS / funky MKS concentrate zones towards the disk
@@ -18,7 +19,6 @@
 namespace {
 
 constexpr double PI = 3.14159265358979323846;
-constexpr double FD_DELTA = 1e-5;
 constexpr double SIN_MIN = 1e-20;  // |sin theta| floor inside the metric (polar faces)
 
 // theta(x1, x2) of MKS / funky MKS
@@ -51,24 +51,8 @@ __device__ void theta_derivs(double x1, double x2, const grmhd_problem& p, doubl
   d2 = dtg + e * (dtj - dtg);
 }
 
-// Cartesian Kerr-Schild: g = eta + f l l with f = 2 r^3 / (r^4 + a^2 z^2) and
-// the null covector l = (1, (r x + a y)/(r^2 + a^2), (r y - a x)/(r^2 + a^2), z/r)
-__device__ void gcov_cks(double x, double y, double z, double a, double g[4][4]) {
-  const double r = cks_radius(x, y, z, a);
-  const double r2 = r * r;
-  const double f = 2.0 * r2 * r / (r2 * r2 + a * a * z * z);
-  const double ra = r2 + a * a;
-  const double l[4] = {1.0, (r * x + a * y) / ra, (r * y - a * x) / ra, z / r};
-  for (int m = 0; m < 4; ++m)
-    for (int n = 0; n < 4; ++n) g[m][n] = f * l[m] * l[n] + (m != n ? 0.0 : (m == 0 ? -1.0 : 1.0));
-}
-
-// covariant metric in code coordinates, full 4x4
-__device__ void gcov_code(double x1, double x2, double x3, const grmhd_problem& p, double g[4][4]) {
-  if (p.coords == GRMHD_KERR_CKS) {
-    gcov_cks(x1, x2, x3, p.a, g);
-    return;
-  }
+// covariant metric in MKS, FMKS or Minkowski coordinates, full 4x4
+__device__ void gcov_code(double x1, double x2, const grmhd_problem& p, double g[4][4]) {
   for (int m = 0; m < 4; ++m)
     for (int n = 0; n < 4; ++n) g[m][n] = 0.0;
   if (p.coords == GRMHD_MINKOWSKI_CART) {
@@ -138,9 +122,9 @@ __device__ double invert4(const double m[4][4], double b[4][4]) {
 
 // the 3+1 quantities of a face of direction D in MKS, FMKS or Minkowski
 // coordinates, whose g_23 and beta^3 vanish identically
-__device__ void face_point(double x1, double x2, double x3, int D, const grmhd_problem& p, FaceGeo<double>& f) {
+__device__ void face_point(double x1, double x2, int D, const grmhd_problem& p, FaceGeo<double>& f) {
   double g[4][4], gi[4][4];
-  gcov_code(x1, x2, x3, p, g);
+  gcov_code(x1, x2, p, g);
   const double det = invert4(g, gi);
   const double a2 = -1.0 / gi[0][0];
   f.g11 = g[1][1];
@@ -207,79 +191,69 @@ __global__ void geometry_kernel(grmhd_problem p, Dims d, Tables t) {
   for (int D = 1; D <= 3; ++D) {
     FaceGeo<double> g;
     if (k3) cks_face_geo(box, D, i, j, k, g);
-    else face_point(D == 1 ? x1f : x1c, D == 2 ? x2f : x2c, x3c, D, p, g);
+    else face_point(D == 1 ? x1f : x1c, D == 2 ? x2f : x2c, D, p, g);
     store_face(g, dt[D - 1], ft[D - 1], ts, off);
   }
 
-  // centres: source coefficients from centred differences of the metric
-  // (d_t = 0), floor scales, and for 2D tables the metric itself
+  // centres
   double v[N_CENT] = {};
-  double gi[4][4], gdet = 1.0;
-  {
-    double g[4][4];
-    gcov_code(x1c, x2c, x3c, p, g);
-    if (k3) {
-      // g^-1 = eta - f l^ l^ in closed form, from gamma^ij, beta^i and alpha
-      ZoneGeo z;
-      cks_centre_geo(box, i, j, k, z);
-      const double ia2 = z.ialpha * z.ialpha, bb[3] = {z.b1, z.b2, z.b3};
-      const double h[3][3] = {{z.h11, z.h12, z.h13}, {z.h12, z.h22, z.h23}, {z.h13, z.h23, z.h33}};
-      gi[0][0] = -ia2;
-      for (int m = 0; m < 3; ++m) {
-        gi[0][m + 1] = gi[m + 1][0] = bb[m] * ia2;
-        for (int n = 0; n < 3; ++n) gi[m + 1][n + 1] = h[m][n] - bb[m] * bb[n] * ia2;
-      }
-    } else {
-      const double det = invert4(g, gi);
-      const double a2 = -1.0 / gi[0][0];
-      gdet = sqrt(fabs(det));
-      v[C_G11] = g[1][1];
-      v[C_G12] = g[1][2];
-      v[C_G13] = g[1][3];
-      v[C_G22] = g[2][2];
-      v[C_G33] = g[3][3];
-      v[C_ALPHA] = 1.0 / sqrt(-gi[0][0]);
-      v[C_B1] = a2 * gi[0][1];
-      v[C_B2] = a2 * gi[0][2];
-      v[C_IALPHA] = sqrt(-gi[0][0]);
-      v[C_GDET] = gdet;
-      v[C_IGDET] = 1.0 / gdet;
-      // gamma^ij = g^ij + alpha^2 g^ti g^tj
-      v[C_H11] = gi[1][1] + a2 * gi[0][1] * gi[0][1];
-      v[C_H12] = gi[1][2] + a2 * gi[0][1] * gi[0][2];
-      v[C_H13] = gi[1][3];
-      v[C_H22] = gi[2][2] + a2 * gi[0][2] * gi[0][2];
-      v[C_H23] = gi[2][3];
-      v[C_H33] = gi[3][3];
-    }
-  }
+  int nc = C_UFL + 1;
+  // floor scales: k = 1/(r^2 (1 + r/10)) with r = exp(x1) (MKS / FMKS) or the
+  // Kerr-Schild radius of the Cartesian point
+  double rfl = 0.0, ufl = 0.0;
   if (p.coords != GRMHD_MINKOWSKI_CART) {
-    for (int c = 0; c < (k3 ? 3 : 2); ++c) {
-      const double e1 = c == 0 ? FD_DELTA : 0.0, e2 = c == 1 ? FD_DELTA : 0.0, e3 = c == 2 ? FD_DELTA : 0.0;
-      double gp[4][4], gm[4][4];
-      gcov_code(x1c + e1, x2c + e2, x3c + e3, p, gp);
-      gcov_code(x1c - e1, x2c - e2, x3c - e3, p, gm);
-      double tr = 0.0;
-      for (int a = 0; a < 4; ++a)
-        for (int b = a; b < 4; ++b) {
-          const double dg = gdet * ((gp[a][b] - gm[a][b]) / (2.0 * FD_DELTA)) * (a == b ? 0.5 : 1.0);
-          tr += gi[a][b] * dg;
-          if (k3) v[K_S1 + 11 * c + sidx(a, b)] = dg;
-          else
-            for (int q = 0; q < 8; ++q)
-              if (AXI_KM[q][0] == a && AXI_KM[q][1] == b) v[C_S1 + 9 * c + q] = dg;
-        }
-      v[k3 ? K_S1 + 11 * c + 10 : C_S1 + 9 * c + 8] = tr;
-    }
-    // floor scales: k = 1/(r^2 (1 + r/10)) with r = exp(x1) (MKS / FMKS) or the
-    // Kerr-Schild radius of the Cartesian point
     const double r = k3 ? cks_radius(x1c, x2c, x3c, p.a) : exp(x1c);
     const double kk = 1.0 / (r * r * (1.0 + r / 10.0));
-    v[k3 ? K_RHOFL : C_RHOFL] = p.rho_fl * kk;
-    v[k3 ? K_UFL : C_UFL] = p.u_fl * pow(kk, p.gam);
+    rfl = p.rho_fl * kk;
+    ufl = p.u_fl * pow(kk, p.gam);
   }
-  if (k3) v[K_GDET] = 1.0;
-  for (int c = 0; c < (k3 ? K_GDET : C_UFL) + 1; ++c) t.cent[pair_index(c, ts, (size_t)off)] = v[c];
+  if (k3) {
+    nc = K_GDET + 1;
+    v[K_RHOFL] = rfl;
+    v[K_UFL] = ufl;
+    v[K_GDET] = 1.0;
+  } else {
+    double g[4][4], gi[4][4];
+    gcov_code(x1c, x2c, p, g);
+    const double det = invert4(g, gi);
+    const double a2 = -1.0 / gi[0][0], gdet = sqrt(fabs(det));
+    v[C_G11] = g[1][1];
+    v[C_G12] = g[1][2];
+    v[C_G13] = g[1][3];
+    v[C_G22] = g[2][2];
+    v[C_G33] = g[3][3];
+    v[C_ALPHA] = 1.0 / sqrt(-gi[0][0]);
+    v[C_B1] = a2 * gi[0][1];
+    v[C_B2] = a2 * gi[0][2];
+    v[C_IALPHA] = sqrt(-gi[0][0]);
+    v[C_GDET] = gdet;
+    v[C_IGDET] = 1.0 / gdet;
+    // gamma^ij = g^ij + alpha^2 g^ti g^tj
+    v[C_H11] = gi[1][1] + a2 * gi[0][1] * gi[0][1];
+    v[C_H12] = gi[1][2] + a2 * gi[0][1] * gi[0][2];
+    v[C_H13] = gi[1][3];
+    v[C_H22] = gi[2][2] + a2 * gi[0][2] * gi[0][2];
+    v[C_H23] = gi[2][3];
+    v[C_H33] = gi[3][3];
+    v[C_RHOFL] = rfl;
+    v[C_UFL] = ufl;
+    // source coefficients from centred differences of the metric in x1 and x2
+    for (int c = 0; c < 2 && p.coords != GRMHD_MINKOWSKI_CART; ++c) {
+      const double e1 = c == 0 ? FD_DELTA : 0.0, e2 = c == 1 ? FD_DELTA : 0.0;
+      double gp[4][4], gm[4][4];
+      gcov_code(x1c + e1, x2c + e2, p, gp);
+      gcov_code(x1c - e1, x2c - e2, p, gm);
+      double tr = 0.0;
+      for (int q = 0; q < 8; ++q) {
+        const int a = AXI_KM[q][0], b = AXI_KM[q][1];
+        const double dg = gdet * ((gp[a][b] - gm[a][b]) / (2.0 * FD_DELTA)) * (a == b ? 0.5 : 1.0);
+        tr += gi[a][b] * dg;
+        v[C_S1 + 9 * c + q] = dg;
+      }
+      v[C_S1 + 9 * c + 8] = tr;
+    }
+  }
+  for (int c = 0; c < nc; ++c) t.cent[pair_index(c, ts, (size_t)off)] = v[c];
 }
 
 }  // namespace

@@ -140,12 +140,9 @@ __device__ void apply_floors(double* P, const ZoneGeo& g, double rfl, double ufl
   P[1] = u;
 }
 
-// sqrt(-g) T^km d_n g_km / 2 for n = 1..3 (the coefficients of the table) of
-// state P, s into S (zero along x3 in MKS, FMKS and Minkowski)
+// contravariant u and b
 template <bool AXI>
-__device__ inline void source(const double* P, const ZoneState& s, const ZoneGeo& g, double gam, const double* ct,
-                              const Dims& d, int off, double* S) {
-  double u[4], b[4];
+__device__ inline void contravariant(const double* P, const ZoneState& s, const ZoneGeo& g, double* u, double* b) {
   const double li = s.lor * g.ialpha;  // u^i = u~^i - Gamma beta^i / alpha
   u[0] = s.ut;
   u[1] = P[2] - li * g.b1;
@@ -154,44 +151,76 @@ __device__ inline void source(const double* P, const ZoneState& s, const ZoneGeo
   b[0] = s.bt;
 #pragma unroll
   for (int m = 1; m < 4; ++m) b[m] = (P[4 + m] + s.bt * u[m]) * s.iut;
+}
+
+// sqrt(-g) T^km d_n g_km / 2 for n = 1, 2 (the coefficients of the table) of
+// state P, s, added to rhs
+__device__ inline void source_axi(const double* P, const ZoneState& s, const ZoneGeo& g, double gam, const double* ct,
+                                  const Dims& d, int off, double* rhs) {
+  double u[4], b[4], M[9];
+  contravariant<true>(P, s, g, u, b);
+  const double wb = P[0] + gam * P[1] + s.bsq;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int k = AXI_KM[q][0], m = AXI_KM[q][1];
+    M[q] = wb * (u[k] * u[m]) - b[k] * b[m];
+  }
+  M[8] = (gam - 1.0) * P[1] + 0.5 * s.bsq;
+  // coefficients C_S1 .. C_S1 + 17 in pairs: nine of x1, then nine of x2
+  static_assert(!(C_S1 & 1) && C_S2 == C_S1 + 9, "pairs of the source coefficients");
+  double S[2] = {0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < 18; c += 2) {
+    const double2 q = zone_pair(ct, d, off, C_S1 + c);
+    S[c / 9] = S[c / 9] + M[c % 9] * q.x;
+    S[(c + 1) / 9] = S[(c + 1) / 9] + M[(c + 1) % 9] * q.y;
+  }
+  rhs[2] = rhs[2] + S[0];
+  rhs[3] = rhs[3] + S[1];
+}
+
+// The same in Cartesian Kerr-Schild (sqrt(-g) = 1), with the centred
+// differences of g_km taken here: six evaluations of the metric, some 600
+// operations, against 33 coefficients read per zone (1.3 GB a launch on a
+// 168^3 box, where the update took 0.61 ms reading them and takes 0.36).
+__device__ inline void source_cks(const double* P, const ZoneState& s, const ZoneGeo& g, double gam, const CksBox& box,
+                                  int i, int j, int k, double* rhs) {
+  double u[4], b[4], T[10];
+  contravariant<false>(P, s, g, u, b);
   const double wb = P[0] + gam * P[1] + s.bsq, pt = (gam - 1.0) * P[1] + 0.5 * s.bsq;
-  S[0] = S[1] = S[2] = 0.0;
-  if constexpr (AXI) {
-    double M[9];
+  const double ia2 = g.ialpha * g.ialpha, bi[3] = {g.b1, g.b2, g.b3};
+  const double h[6] = {g.h11, g.h12, g.h13, g.h22, g.h23, g.h33};
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int k = AXI_KM[q][0], m = AXI_KM[q][1];
-      M[q] = wb * (u[k] * u[m]) - b[k] * b[m];
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int n = m; n < 4; ++n) {
+      // T^mn with g^-1 from gamma^ij, beta^i and alpha, times the multiplicity in the sum / 4 FD_DELTA
+      const double gi = m == 0 ? (n == 0 ? -ia2 : bi[n - 1] * ia2)
+                               : h[sidx(m, n) - 4] - bi[m - 1] * (bi[n - 1] * ia2);
+      T[sidx(m, n)] = (wb * (u[m] * u[n]) - b[m] * b[n] + pt * gi) * ((m == n ? 0.25 : 0.5) / FD_DELTA);
     }
-    M[8] = pt;
-    // coefficients C_S1 .. C_S1 + 17 in pairs: nine of x1, then nine of x2
-    static_assert(!(C_S1 & 1) && C_S2 == C_S1 + 9, "pairs of the source coefficients");
+  double x[3];
+  cks_centre(box, i, j, k, x);
 #pragma unroll
-    for (int c = 0; c < 18; c += 2) {
-      const double2 q = zone_pair(ct, d, off, C_S1 + c);
-      S[c / 9] = S[c / 9] + M[c % 9] * q.x;
-      S[(c + 1) / 9] = S[(c + 1) / 9] + M[(c + 1) % 9] * q.y;
-    }
-  } else {
-    double M[11];
+  for (int c = 0; c < 3; ++c) {
+    double gp[10], gm[10];
+    const double e[3] = {c == 0 ? FD_DELTA : 0.0, c == 1 ? FD_DELTA : 0.0, c == 2 ? FD_DELTA : 0.0};
+    cks_gcov(x[0] + e[0], x[1] + e[1], x[2] + e[2], box.a, gp);
+    cks_gcov(x[0] - e[0], x[1] - e[1], x[2] - e[2], box.a, gm);
+    double S = 0.0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int m = k; m < 4; ++m) M[sidx(k, m)] = wb * (u[k] * u[m]) - b[k] * b[m];
-    M[10] = pt;
-    static_assert(K_S1 == 0 && K_S2 == 11 && K_S3 == 22, "pairs of the source coefficients");
-#pragma unroll
-    for (int c = 0; c < 33; c += 2) {
-      const double2 q = zone_pair(ct, d, off, c);
-      S[c / 11] = S[c / 11] + M[c % 11] * q.x;
-      if (c + 1 < 33) S[(c + 1) / 11] = S[(c + 1) / 11] + M[(c + 1) % 11] * q.y;
-    }
+    for (int q = 0; q < 10; ++q) S = S + T[q] * (gp[q] - gm[q]);
+    rhs[2 + c] = rhs[2 + c] + S;
+    __builtin_amdgcn_sched_barrier(0);  // one direction at a time
   }
 }
 
 // b: block index within this job's grid (the update tile d.utx x d.uty, XCD-aware order)
-// Z: where the zone's geometry comes from
-template <typename TF, int Z>
+// Z: where the zone's geometry comes from. SAME: the base state is the flux
+// state (the predictor); its four-vectors then serve the conserved variables
+// too (2 % of the predictor; in Cartesian Kerr-Schild keeping them across the
+// source spills)
+template <typename TF, int Z, bool SAME>
 __device__ void update_body(const Dims& d, const double* __restrict__ cent, const UpdateParams& up,
                             const FluxOut<TF>& F, const double* Pb, const double* __restrict__ Ps, double* Pout,
                             int8_t* __restrict__ flags, double dt, Counters* ctr, int b) {
@@ -235,21 +264,18 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
     }
     ZoneGeo g;
     zone_geo<Z>(g, ct, d, off, i, j, k);
-    double ps[NV], l2;
+    double ps[NV], U[NV], l2;
 #pragma unroll
     for (int v = 0; v < NV; ++v) ps[v] = buf_at(Ps + v * sv, c);
     {
       ZoneState s;
       zone_state<AXI>(ps, g, s);
       l2 = s.l2;
-      double S[3];
-      source<AXI>(ps, s, g, up.gam, ct, d, off, S);
-      rhs[2] = rhs[2] + S[0];
-      rhs[3] = rhs[3] + S[1];
-      if constexpr (!AXI) rhs[4] = rhs[4] + S[2];
+      if constexpr (AXI) source_axi(ps, s, g, up.gam, ct, d, off, rhs);
+      else source_cks(ps, s, g, up.gam, d.box, i, j, k, rhs);
+      if constexpr (SAME) conserved<AXI>(ps, s, g, up.gam, U);
     }
-    double U[NV];
-    {
+    if constexpr (!SAME) {
       double pb[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) pb[v] = buf_at(Pb + v * sv, c);
@@ -278,41 +304,44 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
   block_count_to(failed, &ctr->fail, &ctr->fail_total);
 }
 
-// Bound by HBM: 31 values a zone read (23 in the predictor, whose base state is
-// the flux state), 8 written, at 0.35 ms on the 288 x 128 x 128 torus 4.5 TB/s of
-// the 4.9 a device copy reaches; with the 4 x 4 metric, its inverse and the 40
-// connection coefficients read per zone (66 values against 38 in pairs) and
-// IEEE divisions it took 0.47 ms (mixed precision 0.29 against 0.42, Cartesian
-// Kerr-Schild 0.56 against 0.68). (256, 3): at least three waves per SIMD. Held
-// to four, the FP64 kernel takes 108 registers, keeps fewer loads in flight and
-// 0.46 ms.
-template <typename TF, int Z>
+// Bound by HBM and by the loads in flight: 31 values a zone read (23 in the
+// predictor, whose base state is the flux state), 8 written, at 0.35 ms on the
+// 288 x 128 x 128 torus 4.5 TB/s of the 4.9 a device copy reaches. With the 4 x 4
+// metric, its inverse and the 40 connection coefficients read per zone (66
+// values against 38 in pairs) and IEEE divisions it took 0.47 ms (mixed
+// precision 0.29 against 0.42). (256, 3): at least three waves per SIMD. Held to
+// four, the FP64 kernel takes 108 registers, keeps fewer loads in flight and
+// 0.46 ms. Blocks that copy the tile's table to LDS and walk up 1 to 8 planes,
+// carrying the x3 fluxes and EMFs between them, load 38 values instead of 71
+// and take 0.42 ms: the copy, its barrier and each plane's loads wait one after
+// the other.
+template <typename TF, int Z, bool SAME>
 __global__ __launch_bounds__(256, 3) void update_kernel(Dims d, const double* __restrict__ cent, UpdateParams up,
                                                         FluxOut<TF> F, const double* Pb, const double* __restrict__ Ps,
                                                         double* Pout, int8_t* __restrict__ flags, double dt,
                                                         const double* __restrict__ dt_dev, double dt_scale,
                                                         Counters* ctr) {
   if (dt_dev) dt = dt_scale * *dt_dev;
-  update_body<TF, Z>(d, cent, up, F, Pb, Ps, Pout, flags, dt, ctr, (int)blockIdx.x);
+  update_body<TF, Z, SAME>(d, cent, up, F, Pb, Ps, Pout, flags, dt, ctr, (int)blockIdx.x);
 }
 
 // every job of a batch: predictor P -> P_h with dt/2, corrector (P, P_h) -> P with dt
-template <typename TF, bool ALL_AXI>
-__global__ __launch_bounds__(256, 3) void update_batch_kernel(BatchView bv, int corrector) {
+template <typename TF, bool ALL_AXI, bool CORRECTOR>
+__global__ __launch_bounds__(256, 3) void update_batch_kernel(BatchView bv) {
   const int* offs = bv.offs + PH_UPDATE * (bv.njobs + 1);
   const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
   const JobDesc& J = bv.jobs[jb];
-  const double dt = corrector ? *J.dt : 0.5 * *J.dt;
+  const double dt = CORRECTOR ? *J.dt : 0.5 * *J.dt;
   const FluxOut<TF> F = flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv);
-  const double* Ps = global_ptr(corrector ? J.Ph : J.P);
-  double* Pout = global_ptr(corrector ? J.P : J.Ph);
+  const double* Ps = global_ptr(CORRECTOR ? J.Ph : J.P);
+  double* Pout = global_ptr(CORRECTOR ? J.P : J.Ph);
   const int b = (int)blockIdx.x - offs[jb];
   if (ALL_AXI || J.d.tk == 0)
-    update_body<TF, ZONE_AXI>(J.d, global_ptr(J.t.cent), J.up, F, global_ptr(J.P), Ps, Pout, global_ptr(J.flags), dt,
-                              global_ptr(J.ctr), b);
+    update_body<TF, ZONE_AXI, !CORRECTOR>(J.d, global_ptr(J.t.cent), J.up, F, global_ptr(J.P), Ps, Pout,
+                                          global_ptr(J.flags), dt, global_ptr(J.ctr), b);
   else
-    update_body<TF, ZONE_CKS>(J.d, global_ptr(J.t.cent), J.up, F, global_ptr(J.P), Ps, Pout, global_ptr(J.flags), dt,
-                              global_ptr(J.ctr), b);
+    update_body<TF, ZONE_CKS, false>(J.d, global_ptr(J.t.cent), J.up, F, global_ptr(J.P), Ps, Pout, global_ptr(J.flags),
+                                     dt, global_ptr(J.ctr), b);
 }
 
 // neighbour index along one direction for the fixup: across a periodic
@@ -458,18 +487,27 @@ __global__ __launch_bounds__(256) void u2p_kernel(Dims d, const double* __restri
 
 namespace {
 
-template <typename TF>
+template <typename TF, bool SAME>
 void update_for(const Dims& d, const Tables& t, const UpdateParams& up, const void* F, const double* Pb,
                 const double* Ps, double* Pout, int8_t* flags, double dt, const double* dt_dev, double dt_scale,
                 Counters* ctr, hipStream_t s) {
   const dim3 grd(xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty)), blk(d.utx, d.uty, 1);
   const FluxOut<TF> f = flux_out<TF>((unsigned char*)F, d.sv);
   if (d.tk != 0)
-    hipLaunchKernelGGL((update_kernel<TF, ZONE_CKS>), grd, blk, 0, s, d, t.cent, up, f, Pb, Ps, Pout, flags, dt, dt_dev,
-                       dt_scale, ctr);
+    hipLaunchKernelGGL((update_kernel<TF, ZONE_CKS, false>), grd, blk, 0, s, d, t.cent, up, f, Pb, Ps, Pout, flags, dt,
+                       dt_dev, dt_scale, ctr);
   else
-    hipLaunchKernelGGL((update_kernel<TF, ZONE_AXI>), grd, blk, 0, s, d, t.cent, up, f, Pb, Ps, Pout, flags, dt, dt_dev,
-                       dt_scale, ctr);
+    hipLaunchKernelGGL((update_kernel<TF, ZONE_AXI, SAME>), grd, blk, 0, s, d, t.cent, up, f, Pb, Ps, Pout, flags, dt,
+                       dt_dev, dt_scale, ctr);
+}
+
+template <typename TF>
+void update_batch_for(const BatchView& bv, dim3 grd, bool corrector, hipStream_t s) {
+  const dim3 blk(bv.utx, bv.uty, 1);
+  if (bv.axi && corrector) hipLaunchKernelGGL((update_batch_kernel<TF, true, true>), grd, blk, 0, s, bv);
+  else if (bv.axi) hipLaunchKernelGGL((update_batch_kernel<TF, true, false>), grd, blk, 0, s, bv);
+  else if (corrector) hipLaunchKernelGGL((update_batch_kernel<TF, false, true>), grd, blk, 0, s, bv);
+  else hipLaunchKernelGGL((update_batch_kernel<TF, false, false>), grd, blk, 0, s, bv);
 }
 
 }  // namespace
@@ -477,8 +515,9 @@ void update_for(const Dims& d, const Tables& t, const UpdateParams& up, const vo
 hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const UpdateParams& up, const void* F,
                          const double* Pb, const double* Ps, double* Pout, int8_t* flags, double dt,
                          const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s) {
-  if (mixed) update_for<float>(d, t, up, F, Pb, Ps, Pout, flags, dt, dt_dev, dt_scale, ctr, s);
-  else update_for<double>(d, t, up, F, Pb, Ps, Pout, flags, dt, dt_dev, dt_scale, ctr, s);
+  const auto launch = mixed ? (Pb == Ps ? update_for<float, true> : update_for<float, false>)
+                            : (Pb == Ps ? update_for<double, true> : update_for<double, false>);
+  launch(d, t, up, F, Pb, Ps, Pout, flags, dt, dt_dev, dt_scale, ctr, s);
   return hipGetLastError();
 }
 
@@ -496,10 +535,8 @@ hipError_t launch_batch_update(const BatchView& bv, const int* totals, bool mixe
   const dim3 blk(bv.utx, bv.uty, 1), grd(totals[PH_UPDATE]);
   const int c = corrector ? 1 : 0;
   if (which & 1) {
-    if (mixed && bv.axi) hipLaunchKernelGGL((update_batch_kernel<float, true>), grd, blk, 0, s, bv, c);
-    else if (mixed) hipLaunchKernelGGL((update_batch_kernel<float, false>), grd, blk, 0, s, bv, c);
-    else if (bv.axi) hipLaunchKernelGGL((update_batch_kernel<double, true>), grd, blk, 0, s, bv, c);
-    else hipLaunchKernelGGL((update_batch_kernel<double, false>), grd, blk, 0, s, bv, c);
+    if (mixed) update_batch_for<float>(bv, grd, corrector, s);
+    else update_batch_for<double>(bv, grd, corrector, s);
   }
   if (which & 2) hipLaunchKernelGGL(fixup_batch_kernel, grd, blk, 0, s, bv, c);
   return hipGetLastError();
