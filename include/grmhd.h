@@ -243,7 +243,7 @@ GRMHD_API int grmhd_courant_dt(const grmhd_ctx *ctx, const double *ctop, int32_t
  * model: GRMHD_HEAT_CONSTANT (f_e = fel, 0 <= fel <= 1) or one of the five
  * models (fel ignored). The ghost zones of E follow the primitives' rules
  * without the axis sign change and the inflow fix. The first call on a context
- * allocates 4 doubles per padded zone of scratch, held until grmhd_free.
+ * allocates 2 doubles per padded zone of scratch, held until grmhd_free.
  * dt_next and the errors as grmhd_step (a non-finite entropy also gives
  * GRMHD_ESTATE); EINVAL also for an unknown model or fel outside [0, 1]. */
 enum {

@@ -140,7 +140,7 @@ Dims make_dims(const grmhd_problem& p) {
 
 void free_all(grmhd_ctx* c) {
   void* ptrs[] = {c->t.cent, c->t.f1, c->t.f2, c->t.f3, c->t.f1f, c->t.f2f, c->t.f3f,
-                  c->Ph, c->F, c->flags, c->ctr, c->Eh, c->Uk};
+                  c->Ph, c->F, c->flags, c->ctr, c->Eh};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
 }
@@ -196,13 +196,6 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
                                  want_ctop ? c->ctr->ctop : nullptr, s),
                 "sweeps");
   }
-  if (el) {
-    // before the update: in the corrector it overwrites the base state in place
-    ProfScope ps(c->prof, s, GRMHD_K_ELECTRONS);
-    HIP_OR_FAIL(c, launch_scalar_advect(c->mixed, c->p.recon, c->d, c->t, c->up, c->F, Pb,
-                                        el->Eb, el->Es, c->Uk, dt, dt_dev, dt_scale, s),
-                "scalar advection");
-  }
   {
     ProfScope ps(c->prof, s, GRMHD_K_UPDATE);
     HIP_OR_FAIL(c, launch_update(c->mixed, c->d, c->t, c->up, c->F, Pb, Ps, Pout,
@@ -215,8 +208,9 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
   }
   if (el) {
     ProfScope ps(c->prof, s, GRMHD_K_ELECTRONS);
-    HIP_OR_FAIL(c, launch_electron_heat(c->d, c->t, c->p.gam, Pout, c->Uk, el->Eout, el->model, el->fel, c->ctr, s),
-                "electron heating");
+    HIP_OR_FAIL(c, launch_electrons(c->mixed, c->p.recon, c->d, c->t, c->up, c->F, Pout == Pb ? nullptr : Pb, Pout, el->Eb,
+                                    el->Es, el->Eout, dt, dt_dev, dt_scale, el->model, el->fel, c->ctr, s),
+                "electron advection and heating");
   }
   return GRMHD_OK;
 }
@@ -327,13 +321,11 @@ hipError_t ctx_electron_scratch(grmhd_ctx* c) {
   if (c->Eh) return hipSuccess;
   const size_t bytes = (size_t)GRMHD_NSCALAR * c->d.sv * sizeof(double);
   hipError_t e = hipMalloc((void**)&c->Eh, bytes);
-  if (e == hipSuccess) e = hipMalloc((void**)&c->Uk, bytes);
   // ghost and padding zones of the half-step entropies that no rule writes stay finite
   if (e == hipSuccess) e = hipMemsetAsync(c->Eh, 0, bytes, c->stream);
   if (e != hipSuccess) {
     if (c->Eh) (void)hipFree(c->Eh);
-    if (c->Uk) (void)hipFree(c->Uk);
-    c->Eh = c->Uk = nullptr;
+    c->Eh = nullptr;
   }
   return e;
 }

@@ -7,8 +7,8 @@
 //   corrector: ghosts(P_h); reset(ctop, fail); sweeps(P_h) + ctop; update((P, P_h) -> P, dt); fixup
 //   dt_j <- min(cfl / sum_d (ctop_d / dx_d), 1.3 dt_j)
 // With electron heating (jobs given entropies E), each substep also fills
-// the scalar ghosts after the fluid ghosts, advects the entropies after the
-// sweeps and heats after the fixup, as a context's electron step does.
+// the scalar ghosts after the fluid ghosts, and advects and heats after the
+// fixup, as a context's electron step does.
 // Every job reads only its own dt, counters and arrays, so its evolution is
 // the same alone or in any mix.
 #include <cstring>
@@ -83,18 +83,13 @@ hipError_t enqueue_step(grmhd_batch* b) {
     }
     if (b->electrons) {
       ProfScope ps(b->prof, s, GRMHD_K_ELECTRONS);
-      if ((e = launch_batch_electrons(bv, b->totals, b->mixed, b->recon, corr == 1, 1, s)) != hipSuccess) return e;
+      if ((e = launch_batch_scalar_ghosts(bv, b->totals, corr == 1, s)) != hipSuccess) return e;
     }
     if ((e = launch_batch_reset(bv, corr ? (1 | 4) : 4, s)) != hipSuccess) return e;
     {
       ProfScope ps(b->prof, s, GRMHD_K_SWEEPS);
       if ((e = launch_batch_sweeps(bv, b->totals, b->recon, b->mixed, corr == 1, corr == 1, s)) != hipSuccess)
         return e;
-    }
-    if (b->electrons) {
-      // before the update: in the corrector it overwrites the base state
-      ProfScope ps(b->prof, s, GRMHD_K_ELECTRONS);
-      if ((e = launch_batch_electrons(bv, b->totals, b->mixed, b->recon, corr == 1, 2, s)) != hipSuccess) return e;
     }
     {
       ProfScope ps(b->prof, s, GRMHD_K_UPDATE);
@@ -106,7 +101,7 @@ hipError_t enqueue_step(grmhd_batch* b) {
     }
     if (b->electrons) {
       ProfScope ps(b->prof, s, GRMHD_K_ELECTRONS);
-      if ((e = launch_batch_electrons(bv, b->totals, b->mixed, b->recon, corr == 1, 3, s)) != hipSuccess) return e;
+      if ((e = launch_batch_electrons(bv, b->totals, b->mixed, b->recon, corr == 1, s)) != hipSuccess) return e;
     }
   }
   return launch_batch_dt(bv, s);
@@ -158,7 +153,6 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
     if (ej) {
       jd.E = E[j];
       jd.Eh = c->Eh;
-      jd.Uk = c->Uk;
       jd.heat_model = model[j];
       jd.fel = fel[j];
     }

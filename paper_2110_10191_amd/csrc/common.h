@@ -384,14 +384,6 @@ struct McSlope {
   __device__ T below(T p) const { return fma(-h, one, p); }
 };
 
-template <typename T>
-__device__ inline T mc_slope(T pm, T p0, T pp) {
-  const T dm = p0 - pm, dp = pp - p0, dc = T(0.5) * (pp - pm);
-  // min(2|dm|, 2|dp|) = 2 min(|dm|, |dp|) exactly
-  const T mag = fmin(T(2) * fmin(fabs(dm), fabs(dp)), fabs(dc));
-  return (dm * dp > T(0)) ? copysign(mag, dc) : T(0);
-}
-
 // Value at the right edge of the middle zone of (x1..x5), point-value WENO5
 // with Jiang-Shu smoothness indicators b_k and linear weights (1/16, 5/8, 5/16):
 // weights d_k / (eps + b_k)^2, normalised, eps = 1e-26. Written in the
@@ -501,18 +493,21 @@ constexpr int UPDATE_MAX_THREADS = 256;  // launch bounds of the update and fixu
 //   b   which are the x2 and the x1 flux of B3;
 //   m   the mass fluxes through the lower x1 and x2 face (electron steps only;
 //       the x3 one is f3's first).
-// T is the precision of the fluxes. 17 values a cell, of the 24 T there is room
-// for (three flux arrays of a state's shape).
+// and the predictor's electron pass leaves
+//   r   sqrt(-g) rho u^t of the base state for the corrector's.
+// T is the precision of the fluxes. 18 values a cell, which fill 96 of the 96
+// bytes there is room for with T = float (three flux arrays of a state's shape).
 template <typename T>
 struct FluxOut {
-  double* D;
+  double *D, *r;
   T *f3, *e, *b, *m;
 };
 template <typename T>
 __host__ __device__ inline FluxOut<T> flux_out(unsigned char* base, int sv) {
   FluxOut<T> o;
   o.D = (double*)base;
-  o.f3 = (T*)(o.D + 5 * (size_t)sv);
+  o.r = o.D + 5 * (size_t)sv;
+  o.f3 = (T*)(o.r + sv);
   o.e = o.f3 + 5 * (size_t)sv;
   o.b = o.e + 3 * (size_t)sv;
   o.m = o.b + 2 * (size_t)sv;

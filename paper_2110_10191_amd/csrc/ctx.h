@@ -94,7 +94,6 @@ struct grmhd_ctx {
   Tables t;
   double* Ph;
   double* Eh;  // electron heating scratch (allocated on first use): half-step entropies
-  double* Uk;  // and the advected sqrt(-g) rho u^t K of the current substep
   void* F;     // what the face-flux pass leaves (FluxOut)
   int8_t* flags;
   Counters* ctr;
@@ -105,8 +104,8 @@ struct grmhd_ctx {
 };
 
 // electron heating helpers shared by the context and batch calls: the model /
-// fel check, and the context's scratch (half-step entropies and U_K),
-// allocated and its half-step array cleared on first use
+// fel check, and the context's scratch (half-step entropies), allocated and cleared
+// on first use
 bool heat_args_ok(int32_t model, double fel);
 hipError_t ctx_electron_scratch(grmhd_ctx* c);
 

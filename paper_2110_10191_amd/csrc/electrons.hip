@@ -1,18 +1,19 @@
 // Electron heating (Implementation Notes: the dissipation is tracked and split
 // between ions and electrons after Ressler et al. 2015, with the heating
 // models of Kawazura et al. 2019, Werner et al. 2018, Rowan et al. 2017,
-// Howes 2010 and Sharma et al. 2007). Two passes per substep around the fluid update:
+// Howes 2010 and Sharma et al. 2007). One pass per substep after the fluid
+// update, bounds and fixup, for both entropies K (K_tot = P_gas / rho^gamma and
+// K_e = P_e / rho^gamma_e, gamma_e = 4/3):
 //
-//   scalar advection (after the sweeps, before the fluid update overwrites the
-//   base state): for both entropies K (K_tot = P_gas / rho^gamma and
-//   K_e = P_e / rho^gamma_e, gamma_e = 4/3)
-//     U_K = sqrt(-g) rho_b u^t_b K_b - dt sum_d [F_K(+) - F_K(-)] / dx_d,
+//   advection: U_K = sqrt(-g) rho_b u^t_b K_b - dt sum_d [F_K(+) - F_K(-)] / dx_d,
 //     F_K = F_mass K*, K* the face value (the fluid's reconstruction) on the
-//     upwind side of the mass flux; the mass flux through a polar axis is 0;
+//     upwind side of the mass flux; the mass flux through a polar axis is 0.
+//     The predictor's pass leaves sqrt(-g) rho u^t of the base state for the
+//     corrector's, whose update has overwritten it;
 //
-//   heating (after the fluid update, bounds and fixup): u <= 3 rho^gamma /
-//   (gamma - 1) (P_gas / rho^gamma < 3); with D = sqrt(-g) rho u^t of the new
-//   state, K_adv = U_K / D and K = (gamma - 1) u / rho^gamma,
+//   heating: u <= 3 rho^gamma / (gamma - 1) (P_gas / rho^gamma < 3); with D =
+//   sqrt(-g) rho u^t of the new state, K_adv = U_K / D and K = (gamma - 1) u /
+//   rho^gamma,
 //     K_e = K_e,adv + f_e (gamma_e - 1)/(gamma - 1) rho^(gamma - gamma_e) (K - K_tot,adv)
 //   (the electrons receive the fraction f_e of the dissipated internal
 //   energy), bounded to [0, rho^(gamma - gamma_e) K] (0 <= P_e <= P_gas), and
@@ -39,99 +40,30 @@ constexpr double GAM_E = 4.0 / 3.0;
 constexpr double KAPPA_MAX = 3.0;
 constexpr double MP_ME = 1836.15267343;
 
-// the two face values of a scalar at the lower face of the zone at q (stride st)
+// value of a scalar on the upwind side of the lower face (mass flux m) of the
+// zone at offset c, zones st apart: the reconstruction of the zone below at its
+// upper edge, or of the zone above at its lower edge, which is the same read in
+// reverse order
 template <int RECON>
-__device__ inline void scalar_faces(const double* q, int st, double& l, double& r) {
+__device__ inline double upwind(const double* E, int c, int st, double m) {
+  const bool up = m >= 0.0;
+  auto at = [&](int lo, int hi) -> double {
+    const double a = buf_at(E + lo * st, c), b = buf_at(E + hi * st, c);
+    return up ? a : b;
+  };
   if (RECON == GRMHD_RECON_MC) {
-    const double a = q[-2 * st], b = q[-st], e = q[0], f = q[st];
-    l = b + 0.5 * mc_slope(a, b, e);
-    r = e - 0.5 * mc_slope(b, e, f);
-  } else {
-    const double x0 = q[-3 * st], x1 = q[-2 * st], x2 = q[-st], x3 = q[0], x4 = q[st], x5 = q[2 * st];
-    l = weno5_edge(x0, x1, x2, x3, x4);
-    r = weno5_edge(x5, x4, x3, x2, x1);
+    const double a = at(-2, 1), b = at(-1, 0), e = at(0, -1);
+    return McSlope<double>(b - a, e - b).above(b);
   }
+  return weno5_edge(at(-3, 2), at(-2, 1), at(-1, 0), at(0, -1), at(1, -2));
 }
 
-// upwind flux of both scalars through the lower face (stride st) of cell c
-template <int RECON>
-__device__ inline void scalar_flux(const double* E, int sv, int c, int st, double m, double f[GRMHD_NSCALAR]) {
-#pragma unroll
-  for (int s = 0; s < GRMHD_NSCALAR; ++s) {
-    double l, r;
-    scalar_faces<RECON>(E + s * sv + c, st, l, r);
-    f[s] = m * (m >= 0.0 ? l : r);
-  }
-}
-
-// b: block index within this job's grid (the update tile, XCD-aware order)
-template <typename TF, int RECON>
-__device__ void scalar_advect_body(const Dims& d, const double* __restrict__ cent, const UpdateParams& up,
-                                   const FluxOut<TF>& F, const double* __restrict__ Pb, const double* __restrict__ Eb,
-                                   const double* __restrict__ Es, double* __restrict__ Uk, double dt, int b) {
-  const TileK tk = xcd_tile_k(b, d.utx, d.uty, d.n1, d.n3);
-  const int i = tk.i0 + (int)threadIdx.x;
-  const int j = tk.j0 + (int)threadIdx.y;
-  if (!tk.valid || i >= d.n1 || j >= d.n2) return;
-  const int c = cell_of(d, tk.k, j, i);
-  const TF *m = F.m, *m2 = F.m + d.sv, *m3 = F.f3;  // mass fluxes
-  const bool pl = up.polar_lo && j == 0;
-  const bool ph = up.polar_hi && j == d.n2 - 1;
-  double fm[GRMHD_NSCALAR], fp[GRMHD_NSCALAR], div[GRMHD_NSCALAR];
-  scalar_flux<RECON>(Es, d.sv, c, 1, (double)m[c], fm);
-  scalar_flux<RECON>(Es, d.sv, c + 1, 1, (double)m[c + 1], fp);
-#pragma unroll
-  for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] = (fp[s] - fm[s]) * up.idx1;
-  scalar_flux<RECON>(Es, d.sv, c, d.s2, pl ? 0.0 : (double)m2[c], fm);
-  scalar_flux<RECON>(Es, d.sv, c + d.s2, d.s2, ph ? 0.0 : (double)m2[c + d.s2], fp);
-#pragma unroll
-  for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] += (fp[s] - fm[s]) * up.idx2;
-  scalar_flux<RECON>(Es, d.sv, c, d.s3, (double)m3[c], fm);
-  scalar_flux<RECON>(Es, d.sv, c + d.s3, d.s3, (double)m3[c + d.s3], fp);
-#pragma unroll
-  for (int s = 0; s < GRMHD_NSCALAR; ++s) div[s] += (fp[s] - fm[s]) * up.idx3;
-
-  // rest-mass density of the base state: sqrt(-g) rho u^t, u^t = Gamma / alpha
-  ZoneGeo g;
-  zone_geo<ZONE_ANY>(g, pair_plane(cent, d, tk.k), d, tab_of(d, j, i), i, j, tk.k);
-  const double v1 = Pb[2 * d.sv + c], v2 = Pb[3 * d.sv + c], v3 = Pb[4 * d.sv + c];
-  double u1, u2, u3;
-  lower3<false>(g, v1, v2, v3, u1, u2, u3);
-  const double l2 = v1 * u1 + v2 * u2 + v3 * u3 + 1.0;
-  const double D = g.gdet * Pb[c] * (l2 * rsqrt_full(l2) * g.ialpha);
-#pragma unroll
-  for (int s = 0; s < GRMHD_NSCALAR; ++s) Uk[s * d.sv + c] = D * Eb[s * d.sv + c] - dt * div[s];
-}
-
-template <typename TF, int RECON>
-__global__ __launch_bounds__(256) void scalar_advect_kernel(Dims d, const double* __restrict__ cent, UpdateParams up,
-                                                            FluxOut<TF> F, const double* __restrict__ Pb,
-                                                            const double* __restrict__ Eb, const double* __restrict__ Es,
-                                                            double* __restrict__ Uk, double dt,
-                                                            const double* __restrict__ dt_dev, double dt_scale) {
-  if (dt_dev) dt = dt_scale * *dt_dev;
-  scalar_advect_body<TF, RECON>(d, cent, up, F, Pb, Eb, Es, Uk, dt, (int)blockIdx.x);
-}
-
-// every job with entropies in one grid: predictor (E -> U_K, base P), corrector
-// (E_h fluxes, base E and P)
-template <typename TF, int RECON>
-__global__ __launch_bounds__(256) void scalar_advect_batch_kernel(BatchView bv, int corrector) {
-  const int* offs = bv.offs + PH_UPDATE * (bv.njobs + 1);
-  const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
-  const JobDesc& J = bv.jobs[jb];
-  if (!J.E) return;
-  const double dt = corrector ? *J.dt : 0.5 * *J.dt;
-  scalar_advect_body<TF, RECON>(J.d, global_ptr(J.t.cent), J.up,
-                                flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv), global_ptr(J.P),
-                                global_ptr(J.E), global_ptr(corrector ? J.Eh : J.E), global_ptr(J.Uk), dt,
-                                (int)blockIdx.x - offs[jb]);
-}
-
-__device__ double heating_fraction(int model, double fel, double rho, double u, double kel, double bsq, double gam) {
+// r43: rho^(4/3)
+__device__ double heating_fraction(int model, double fel, double rho, double r43, double u, double kel, double bsq,
+                                   double gam) {
   if (model == GRMHD_HEAT_CONSTANT) return fel;
   const double pg = (gam - 1.0) * u;
-  const double pe = kel * pow(rho, GAM_E);
+  const double pe = kel * r43;
   const double pi = fmax(pg - pe, 1e-30 * pg + 1e-300);
   const double pb = 0.5 * bsq + 1e-300;
   const double beta = pi / pb;
@@ -161,104 +93,133 @@ __device__ double heating_fraction(int model, double fel, double rho, double u, 
   return 1.0 / (1.0 + qi_qe);
 }
 
-// b: block index within this job's grid
-__device__ void electron_heat_body(const Dims& d, const double* __restrict__ cent, double gam, double* __restrict__ P,
-                                   const double* __restrict__ Uk, double* __restrict__ E, int model, double fel,
-                                   unsigned* bad, int b) {
+// Advection and heating of a zone in one thread, with U_K, the metric and the
+// zone's own entropies kept in registers between them: 0.27 ms on 288x128x128
+// FP64 MC zones, against 0.39 ms for an advection and a heating kernel with U_K
+// in memory. Of that, about 0.15 ms is arithmetic (1050 vector instructions a
+// zone, pow and the model's transcendentals with them) and 0.17 ms the memory's
+// copy rate; the 61 loads keep the address units 77 % busy. Neither 4 waves a
+// SIMD (0.28 ms), the two entropies in turn with 86 registers (0.27 ms), nor the
+// new state's loads first (0.27 ms) made it faster.
+// b: block index within this job's grid (the update tile, XCD-aware order)
+template <typename TF, int RECON>
+__device__ void electron_body(const Dims& d, const double* __restrict__ cent, const UpdateParams& up,
+                              const FluxOut<TF>& F, const double* Pb, double* P, const double* Eb, const double* Es, double* Eout,
+                              double dt, int model, double fel, unsigned* bad, int b) {
   const TileK tk = xcd_tile_k(b, d.utx, d.uty, d.n1, d.n3);
   const int i = tk.i0 + (int)threadIdx.x;
   const int j = tk.j0 + (int)threadIdx.y;
   if (!tk.valid || i >= d.n1 || j >= d.n2) return;
   const int c = cell_of(d, tk.k, j, i);
+  const size_t sv = (size_t)d.sv;
+  const TF *m1 = F.m, *m2 = F.m + sv, *m3 = F.f3;  // mass fluxes
+  const double f[6] = {(double)buf_at(m1, c),
+                       (double)buf_at(m1 + 1, c),
+                       up.polar_lo && j == 0 ? 0.0 : (double)buf_at(m2, c),
+                       up.polar_hi && j == d.n2 - 1 ? 0.0 : (double)buf_at(m2 + d.s2, c),
+                       (double)buf_at(m3, c),
+                       (double)buf_at(m3 + d.s3, c)};
+  ZoneGeo g;
+  zone_geo<ZONE_ANY>(g, pair_plane(cent, d, tk.k), d, tab_of(d, j, i), i, j, tk.k);
+  double Db;
+  if (Pb) {
+    const double v1 = buf_at(Pb + 2 * sv, c), v2 = buf_at(Pb + 3 * sv, c), v3 = buf_at(Pb + 4 * sv, c);
+    double u1, u2, u3;
+    lower3<false>(g, v1, v2, v3, u1, u2, u3);
+    const double l2 = v1 * u1 + v2 * u2 + v3 * u3 + 1.0;
+    Db = g.gdet * buf_at(Pb, c) * (l2 * rsqrt_full(l2) * g.ialpha);
+    F.r[c] = Db;
+  } else {
+    Db = buf_at(F.r, c);
+  }
+  double uk[GRMHD_NSCALAR];
+#pragma unroll
+  for (int s = 0; s < GRMHD_NSCALAR; ++s) {
+    const double* q = Es + s * sv;
+    const double d1 = f[1] * upwind<RECON>(q + 1, c, 1, f[1]) - f[0] * upwind<RECON>(q, c, 1, f[0]);
+    const double d2 = f[3] * upwind<RECON>(q + d.s2, c, d.s2, f[3]) - f[2] * upwind<RECON>(q, c, d.s2, f[2]);
+    const double d3 = f[5] * upwind<RECON>(q + d.s3, c, d.s3, f[5]) - f[4] * upwind<RECON>(q, c, d.s3, f[4]);
+    uk[s] = Db * buf_at(Eb + s * sv, c) - dt * (d1 * up.idx1 + d2 * up.idx2 + d3 * up.idx3);
+  }
+  const double gam = up.gam;
   double p[NV];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) p[v] = P[v * d.sv + c];
+  for (int v = 0; v < NV; ++v) p[v] = buf_at(P + v * sv, c);
   const double rho = p[0];
   const double rg = pow(rho, gam);
   const double umax = KAPPA_MAX * rg / (gam - 1.0);
   if (p[1] > umax) {
     p[1] = umax;
-    P[d.sv + c] = umax;
+    P[sv + c] = umax;
   }
-  ZoneGeo g;
-  zone_geo<ZONE_ANY>(g, pair_plane(cent, d, tk.k), d, tab_of(d, j, i), i, j, tk.k);
-  ZoneState f;
-  zone_state<false>(p, g, f);
-  const double D = g.gdet * rho * f.ut;
-  const double ktot_adv = Uk[c] / D, kel_adv = Uk[d.sv + c] / D;
+  ZoneState st;
+  zone_state<false>(p, g, st);
+  const double iD = 1.0 / (g.gdet * rho * st.ut);
+  const double ktot_adv = uk[0] * iD, kel_adv = uk[1] * iD;
   const double ktot = (gam - 1.0) * p[1] / rg;
-  const double fe = heating_fraction(model, fel, rho, p[1], kel_adv, f.bsq, gam);
-  const double scale = pow(rho, gam - GAM_E);
+  const double r43 = rho * cbrt(rho);
+  const double fe = heating_fraction(model, fel, rho, r43, p[1], kel_adv, st.bsq, gam);
+  const double scale = rg / r43;  // rho^(gam - 4/3)
   double kel = kel_adv + fe * (GAM_E - 1.0) / (gam - 1.0) * scale * (ktot - ktot_adv);
   kel = fmin(fmax(kel, 0.0), scale * ktot);
-  E[c] = ktot;
-  E[d.sv + c] = kel;
+  Eout[c] = ktot;
+  Eout[sv + c] = kel;
   if (!(isfinite(ktot) && isfinite(kel))) atomicAdd(bad, 1u);
 }
 
-__global__ __launch_bounds__(256) void electron_heat_kernel(Dims d, const double* __restrict__ cent, double gam,
-                                                            double* __restrict__ P, const double* __restrict__ Uk,
-                                                            double* __restrict__ E, int model, double fel,
-                                                            Counters* ctr) {
-  electron_heat_body(d, cent, gam, P, Uk, E, model, fel, &ctr->bad, (int)blockIdx.x);
+template <typename TF, int RECON>
+__global__ __launch_bounds__(256) void electron_kernel(Dims d, const double* __restrict__ cent, UpdateParams up,
+                                                       FluxOut<TF> F, const double* Pb, double* P,
+                                                       const double* Eb, const double* Es, double* Eout, double dt, const double* __restrict__ dt_dev,
+                                                       double dt_scale, int model, double fel, Counters* ctr) {
+  if (dt_dev) dt = dt_scale * *dt_dev;
+  electron_body<TF, RECON>(d, cent, up, F, Pb, P, Eb, Es, Eout, dt, model, fel, &ctr->bad, (int)blockIdx.x);
 }
 
-// predictor: heats P_h into E_h; corrector: P into E
-__global__ __launch_bounds__(256) void electron_heat_batch_kernel(BatchView bv, int corrector) {
+// every job with entropies in one grid: predictor (fluxes of E, base E) into
+// E_h, corrector (fluxes of E_h, base E) into E
+template <typename TF, int RECON>
+__global__ __launch_bounds__(256) void electron_batch_kernel(BatchView bv, int corrector) {
   const int* offs = bv.offs + PH_UPDATE * (bv.njobs + 1);
   const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
   const JobDesc& J = bv.jobs[jb];
   if (!J.E) return;
-  electron_heat_body(J.d, global_ptr(J.t.cent), J.p.gam, global_ptr(corrector ? J.P : J.Ph), global_ptr(J.Uk),
-                     global_ptr(corrector ? J.E : J.Eh), J.heat_model, J.fel, global_ptr(&J.ctr->bad),
-                     (int)blockIdx.x - offs[jb]);
+  const double dt = corrector ? *J.dt : 0.5 * *J.dt;
+  electron_body<TF, RECON>(J.d, global_ptr(J.t.cent), J.up, flux_out<TF>(global_ptr((unsigned char*)J.F), J.d.sv),
+                           corrector ? nullptr : global_ptr(J.P), global_ptr(corrector ? J.P : J.Ph), global_ptr(J.E), global_ptr(corrector ? J.Eh : J.E),
+                           global_ptr(corrector ? J.E : J.Eh), dt, J.heat_model, J.fel, global_ptr(&J.ctr->bad),
+                           (int)blockIdx.x - offs[jb]);
 }
 
-template <typename TF>
-void advect_for(int recon, const Dims& d, const Tables& t, const UpdateParams& up, const void* F, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
-                const double* dt_dev, double dt_scale, hipStream_t s) {
+template <typename TF, int RECON>
+void electrons_for(const Dims& d, const Tables& t, const UpdateParams& up, const void* F, const double* Pb, double* P, const double* Eb,
+                   const double* Es, double* Eout, double dt, const double* dt_dev, double dt_scale, int model,
+                   double fel, Counters* ctr, hipStream_t s) {
   const dim3 grid(xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty)), block(d.utx, d.uty, 1);
-  const FluxOut<TF> f = flux_out<TF>((unsigned char*)F, d.sv);
-  if (recon == GRMHD_RECON_MC)
-    hipLaunchKernelGGL((scalar_advect_kernel<TF, GRMHD_RECON_MC>), grid, block, 0, s, d, t.cent, up, f, Pb,
-                       Eb, Es, Uk, dt, dt_dev, dt_scale);
-  else
-    hipLaunchKernelGGL((scalar_advect_kernel<TF, GRMHD_RECON_WENO5>), grid, block, 0, s, d, t.cent, up, f, Pb,
-                       Eb, Es, Uk, dt, dt_dev, dt_scale);
+  hipLaunchKernelGGL((electron_kernel<TF, RECON>), grid, block, 0, s, d, t.cent, up,
+                     flux_out<TF>((unsigned char*)F, d.sv), Pb, P, Eb, Es, Eout, dt, dt_dev, dt_scale, model, fel, ctr);
 }
 
 }  // namespace
 
-hipError_t launch_scalar_advect(bool mixed, int recon, const Dims& d, const Tables& t, const UpdateParams& up,
-                                const void* F, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
-                                const double* dt_dev, double dt_scale, hipStream_t s) {
-  if (mixed) advect_for<float>(recon, d, t, up, F, Pb, Eb, Es, Uk, dt, dt_dev, dt_scale, s);
-  else advect_for<double>(recon, d, t, up, F, Pb, Eb, Es, Uk, dt, dt_dev, dt_scale, s);
+hipError_t launch_electrons(bool mixed, int recon, const Dims& d, const Tables& t, const UpdateParams& up,
+                            const void* F, const double* Pb, double* P, const double* Eb, const double* Es, double* Eout, double dt,
+                            const double* dt_dev, double dt_scale, int model, double fel, Counters* ctr,
+                            hipStream_t s) {
+  const bool mc = recon == GRMHD_RECON_MC;
+  const auto launch = mixed ? (mc ? electrons_for<float, GRMHD_RECON_MC> : electrons_for<float, GRMHD_RECON_WENO5>)
+                            : (mc ? electrons_for<double, GRMHD_RECON_MC> : electrons_for<double, GRMHD_RECON_WENO5>);
+  launch(d, t, up, F, Pb, P, Eb, Es, Eout, dt, dt_dev, dt_scale, model, fel, ctr, s);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_electrons(const BatchView& bv, const int* totals, bool mixed, int recon, bool corrector,
-                                  int which, hipStream_t s) {
-  if (which == 1) return launch_batch_scalar_ghosts(bv, totals, corrector, s);
+                                  hipStream_t s) {
   const dim3 grid(totals[PH_UPDATE]), block(bv.utx, bv.uty, 1);
-  const int c = corrector ? 1 : 0;
-  if (which == 2) {
-    if (mixed) {
-      if (recon == GRMHD_RECON_MC) hipLaunchKernelGGL((scalar_advect_batch_kernel<float, GRMHD_RECON_MC>), grid, block, 0, s, bv, c);
-      else hipLaunchKernelGGL((scalar_advect_batch_kernel<float, GRMHD_RECON_WENO5>), grid, block, 0, s, bv, c);
-    } else {
-      if (recon == GRMHD_RECON_MC) hipLaunchKernelGGL((scalar_advect_batch_kernel<double, GRMHD_RECON_MC>), grid, block, 0, s, bv, c);
-      else hipLaunchKernelGGL((scalar_advect_batch_kernel<double, GRMHD_RECON_WENO5>), grid, block, 0, s, bv, c);
-    }
-  } else {
-    hipLaunchKernelGGL(electron_heat_batch_kernel, grid, block, 0, s, bv, c);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_electron_heat(const Dims& d, const Tables& t, double gam, double* P, const double* Uk, double* E,
-                                int model, double fel, Counters* ctr, hipStream_t s) {
-  const dim3 grid(xcd_grid(d.n1, d.n2, d.n3, d.utx, d.uty)), block(d.utx, d.uty, 1);
-  hipLaunchKernelGGL(electron_heat_kernel, grid, block, 0, s, d, t.cent, gam, P, Uk, E, model, fel, ctr);
+  const bool mc = recon == GRMHD_RECON_MC;
+  const auto kernel =
+      mixed ? (mc ? electron_batch_kernel<float, GRMHD_RECON_MC> : electron_batch_kernel<float, GRMHD_RECON_WENO5>)
+            : (mc ? electron_batch_kernel<double, GRMHD_RECON_MC> : electron_batch_kernel<double, GRMHD_RECON_WENO5>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, s, bv, corrector ? 1 : 0);
   return hipGetLastError();
 }

@@ -64,7 +64,6 @@ struct JobDesc {
   // electron heating (E null: the job has none)
   double* E;        // the job's entropies (caller-owned)
   double* Eh;       // half-step entropies
-  double* Uk;       // advected sqrt(-g) rho u^t K of the current substep
   int heat_model;
   double fel;
 };
@@ -116,10 +115,10 @@ hipError_t launch_batch_update(const BatchView& bv, const int* totals, bool mixe
                                hipStream_t s);
 hipError_t launch_batch_reset(const BatchView& bv, int mask, hipStream_t s);
 // electron passes of the jobs that have entropies (the others' blocks return
-// at once): which 1 the scalar ghosts (ghost phase grids), 2 the advection, 3
-// the heating (update phase grid)
+// at once): the scalar ghosts (ghost phase grids); advection and heating (update
+// phase grid)
 hipError_t launch_batch_electrons(const BatchView& bv, const int* totals, bool mixed, int recon, bool corrector,
-                                  int which, hipStream_t s);
+                                  hipStream_t s);
 hipError_t launch_batch_scalar_ghosts(const BatchView& bv, const int* totals, bool corrector, hipStream_t s);
 // dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 dt) per job, on the device
 hipError_t launch_batch_dt(const BatchView& bv, hipStream_t s);
@@ -184,17 +183,19 @@ hipError_t launch_divb_noalloc(const grmhd_problem& p, const Dims& d, const Tabl
                                double* scr, hipStream_t s);
 
 // electron heating: the ghost zones of the two entropies (the primitives'
-// rules without the axis sign change and the inflow fix); the advection of
-// U_K = sqrt(-g) rho u^t K from the face mass fluxes (F of double or float);
-// the u ceiling and the heating of the new state. The advection's step is dt,
-// or dt_scale * *dt_dev when dt_dev is not null.
+// rules without the axis sign change and the inflow fix); and, after the update
+// and the fixup, the advection of sqrt(-g) rho u^t K with the face mass fluxes
+// in F, the u ceiling and the heating of the new state P into Eout. Eb, Es:
+// base and flux state's entropies (Eout may be Eb). Pb: the base state, or null
+// in the corrector, whose update has overwritten it: the predictor's pass over
+// the same F has left what is needed of it. The step is dt, or
+// dt_scale * *dt_dev when dt_dev is not null.
 hipError_t launch_fill_scalar_ghosts(const grmhd_problem& p, const Dims& d, double* E, const double* dirichlet_src,
                                      hipStream_t s);
-hipError_t launch_scalar_advect(bool mixed, int recon, const Dims& d, const Tables& t, const UpdateParams& up,
-                                const void* F, const double* Pb, const double* Eb, const double* Es, double* Uk, double dt,
-                                const double* dt_dev, double dt_scale, hipStream_t s);
-hipError_t launch_electron_heat(const Dims& d, const Tables& t, double gam, double* P, const double* Uk, double* E,
-                                int model, double fel, Counters* ctr, hipStream_t s);
+hipError_t launch_electrons(bool mixed, int recon, const Dims& d, const Tables& t, const UpdateParams& up,
+                            const void* F, const double* Pb, double* P, const double* Eb, const double* Es, double* Eout,
+                            double dt, const double* dt_dev, double dt_scale, int model, double fel, Counters* ctr,
+                            hipStream_t s);
 
 // zero the counters selected by mask (1: ctop, 2: divb, 4: fail, 8: fail_total and bad)
 hipError_t launch_reset(Counters* ctr, int mask, hipStream_t s);
