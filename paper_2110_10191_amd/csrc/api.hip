@@ -143,6 +143,7 @@ void free_all(grmhd_ctx* c) {
                   c->Ph, c->F, c->flags, c->ctr, c->Eh};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
+  if (c->host) (void)hipHostFree(c->host);
 }
 
 template <typename T>
@@ -183,7 +184,7 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
     HIP_OR_FAIL(c, launch_fill_ghosts(c->p, c->d, c->t, Ps, Pb, s, c->ctr, reset_mask, dtr ? *dtr : DtRule{}),
                 "ghost fill");
   } else {
-    if (dtr) HIP_OR_FAIL(c, launch_ctx_dt(c->ctr, dtr->cfl, dtr->dx[0], dtr->dx[1], dtr->dx[2], s), "dt");
+    if (dtr) HIP_OR_FAIL(c, launch_ctx_dt(c->ctr, dtr->cfl, dtr->dx[0], dtr->dx[1], dtr->dx[2], nullptr, s), "dt");
     HIP_OR_FAIL(c, launch_reset(c->ctr, reset_mask, s), "reset");
   }
   if (el) {
@@ -215,10 +216,12 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
   return GRMHD_OK;
 }
 
-// the context's counters on the host; synchronises
-int read_counters(grmhd_ctx* c, Counters* h) {
-  HIP_OR_FAIL(c, hipMemcpyAsync(h, c->ctr, sizeof(Counters), hipMemcpyDeviceToHost, c->stream), "copy counters");
+// the context's counters on the host; synchronises. cfl > 0: first applies the
+// device's step-size rule
+int read_counters(grmhd_ctx* c, Counters* h, double cfl = 0.0) {
+  HIP_OR_FAIL(c, launch_ctx_dt(c->ctr, cfl, c->dx[0], c->dx[1], c->dx[2], c->host, c->stream), "read counters");
   HIP_OR_FAIL(c, hipStreamSynchronize(c->stream), "synchronize");
+  *h = *c->host;
   return GRMHD_OK;
 }
 
@@ -276,37 +279,30 @@ int electron_prep(grmhd_ctx* ctx, const double* P, const double* E, int32_t mode
 // nsteps steps with the step size kept on the device (E, model, fel: with
 // electron heating when E is not null)
 int run_steps(grmhd_ctx* ctx, double* P, double* E, int32_t model, double fel, int32_t nsteps, double* dt) {
-  struct {
-    double dt;
-    int status;
-  } host{*dt, 0};
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(&ctx->ctr->dt, &host.dt, sizeof(double), hipMemcpyHostToDevice, ctx->stream),
-              "set dt");
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(&ctx->ctr->status, &host.status, sizeof(int), hipMemcpyHostToDevice, ctx->stream),
-              "set status");
   const double* dtp = &ctx->ctr->dt;
   const ElectronPass pred{E, E, ctx->Eh, model, fel};
   const ElectronPass corr{ctx->Eh, E, E, model, fel};
   // each step's predictor ghost fill first takes the step size from the
   // previous step's counters (the host's dt for the first step), then clears
   // the step's totals; the last step's rule runs after the loop
-  const DtRule rule{1, ctx->p.cfl, {ctx->dx[0], ctx->dx[1], ctx->dx[2]}};
+  const DtRule rule{DT_RULE, ctx->p.cfl, {ctx->dx[0], ctx->dx[1], ctx->dx[2]}, 0.0};
+  const DtRule first{DT_SET, 0.0, {1.0, 1.0, 1.0}, *dt};
   for (int s = 0; s < nsteps; ++s) {
     int st = substep(ctx, P, P, ctx->Ph, 0.0, false, dtp, 0.5, true, E ? &pred : nullptr, nullptr, true, 8,
-                     s > 0 ? &rule : nullptr);
+                     s > 0 ? &rule : &first);
     if (st != GRMHD_OK) return st;
     st = substep(ctx, ctx->Ph, P, P, 0.0, true, dtp, 1.0, true, E ? &corr : nullptr);
     if (st != GRMHD_OK) return st;
   }
-  if (nsteps > 0)
-    HIP_OR_FAIL(ctx, launch_ctx_dt(ctx->ctr, ctx->p.cfl, ctx->dx[0], ctx->dx[1], ctx->dx[2], ctx->stream), "dt");
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(&host.dt, &ctx->ctr->dt, sizeof(double), hipMemcpyDeviceToHost, ctx->stream),
-              "read dt");
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(&host.status, &ctx->ctr->status, sizeof(int), hipMemcpyDeviceToHost, ctx->stream),
-              "read status");
-  HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "synchronize");
-  *dt = host.dt;
-  if (host.status) return fail(ctx, GRMHD_ESTATE, "non-finite signal speed or state value");
+  if (nsteps == 0) {
+    HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "synchronize");
+    return GRMHD_OK;
+  }
+  Counters h;
+  const int st = read_counters(ctx, &h, ctx->p.cfl);
+  if (st != GRMHD_OK) return st;
+  *dt = h.dt;
+  if (h.status) return fail(ctx, GRMHD_ESTATE, "non-finite signal speed or state value");
   return GRMHD_OK;
 }
 
@@ -426,7 +422,8 @@ int grmhd_init(const grmhd_problem* p, void* hip_stream, grmhd_ctx** out) {
             dalloc(&c->t.f3f, N_FACE * ts * sizeof(float)) == hipSuccess &&
             dalloc(&c->Ph, NV * sv * sizeof(double)) == hipSuccess &&
             dalloc(&c->F, 3 * NV * sv * fsz) == hipSuccess && dalloc(&c->flags, sv) == hipSuccess &&
-            dalloc(&c->ctr, sizeof(Counters)) == hipSuccess;
+            dalloc(&c->ctr, sizeof(Counters)) == hipSuccess &&
+            hipHostMalloc((void**)&c->host, sizeof(Counters), hipHostMallocDefault) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     free_all(c);
@@ -557,10 +554,10 @@ int grmhd_cons_to_prim(grmhd_ctx* ctx, const double* U, double* P, int8_t* flags
   HIP_OR_FAIL(ctx, launch_cons_to_prim(ctx->d, ctx->t, up, U, P, fl, ctx->ctr, s), "cons_to_prim");
   if (opts & GRMHD_OPT_FIXUP) HIP_OR_FAIL(ctx, launch_fixup(ctx->d, ctx->t, up, P, fl, ctx->ctr, 0, s), "fixup");
   if (n_fail) {
-    unsigned int nf = 0;
-    HIP_OR_FAIL(ctx, hipMemcpyAsync(&nf, &ctx->ctr->fail, sizeof(nf), hipMemcpyDeviceToHost, s), "copy");
-    HIP_OR_FAIL(ctx, hipStreamSynchronize(s), "synchronize");
-    *n_fail = nf;
+    Counters h;
+    const int st = read_counters(ctx, &h);
+    if (st != GRMHD_OK) return st;
+    *n_fail = h.fail;
   }
   return GRMHD_OK;
 }
@@ -569,8 +566,7 @@ int grmhd_get_dt(grmhd_ctx* ctx, double* P, double* dt) {
   if (!ctx) return GRMHD_EINVAL;
   if (!P || !dt) return fail(ctx, GRMHD_EINVAL, "get_dt: NULL argument");
   hipStream_t s = ctx->stream;
-  HIP_OR_FAIL(ctx, launch_fill_ghosts(ctx->p, ctx->d, ctx->t, P, P, s), "ghost fill");
-  HIP_OR_FAIL(ctx, launch_reset(ctx->ctr, 1, s), "reset");
+  HIP_OR_FAIL(ctx, launch_fill_ghosts(ctx->p, ctx->d, ctx->t, P, P, s, ctx->ctr, 1), "ghost fill");
   HIP_OR_FAIL(ctx, launch_sweeps(ctx->p, ctx->mixed, ctx->d, ctx->t, ctx->up, P, ctx->F, false, ctx->ctr->ctop, s),
               "sweeps");
   return read_dt(ctx, dt);
@@ -580,8 +576,7 @@ int grmhd_step(grmhd_ctx* ctx, double* P, double dt, double* dt_next) {
   if (!ctx) return GRMHD_EINVAL;
   if (!P) return fail(ctx, GRMHD_EINVAL, "step: NULL state");
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(ctx, GRMHD_EINVAL, "step: dt must be finite and > 0");
-  HIP_OR_FAIL(ctx, launch_reset(ctx->ctr, 8, ctx->stream), "reset");
-  int st = substep(ctx, P, P, ctx->Ph, 0.5 * dt, false);
+  int st = substep(ctx, P, P, ctx->Ph, 0.5 * dt, false, nullptr, 1.0, true, nullptr, nullptr, true, 8);
   if (st != GRMHD_OK) return st;
   st = substep(ctx, ctx->Ph, P, P, dt, true);
   if (st != GRMHD_OK) return st;
@@ -594,9 +589,8 @@ int grmhd_step_electrons(grmhd_ctx* ctx, double* P, double* E, double dt, int32_
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(ctx, GRMHD_EINVAL, "step_electrons: dt must be finite and > 0");
   int st = electron_prep(ctx, P, E, model, fel, "step_electrons");
   if (st != GRMHD_OK) return st;
-  HIP_OR_FAIL(ctx, launch_reset(ctx->ctr, 8, ctx->stream), "reset");
   const ElectronPass pred{E, E, ctx->Eh, model, fel};
-  st = substep(ctx, P, P, ctx->Ph, 0.5 * dt, false, nullptr, 1.0, true, &pred);
+  st = substep(ctx, P, P, ctx->Ph, 0.5 * dt, false, nullptr, 1.0, true, &pred, nullptr, true, 8);
   if (st != GRMHD_OK) return st;
   const ElectronPass corr{ctx->Eh, E, E, model, fel};
   st = substep(ctx, ctx->Ph, P, P, dt, true, nullptr, 1.0, true, &corr);
@@ -697,23 +691,20 @@ int grmhd_divb_noalloc(grmhd_ctx* ctx, const double* P, double* max_divb) {
 
 int grmhd_step_failures(grmhd_ctx* ctx, int64_t* n_fail) {
   if (!ctx || !n_fail) return GRMHD_EINVAL;
-  unsigned int nf = 0;
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(&nf, &ctx->ctr->fail_total, sizeof(nf), hipMemcpyDeviceToHost, ctx->stream),
-              "copy");
-  HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "synchronize");
-  *n_fail = nf;
-  return GRMHD_OK;
+  Counters h;
+  const int st = read_counters(ctx, &h);
+  if (st == GRMHD_OK) *n_fail = h.fail_total;
+  return st;
 }
 
 int grmhd_divb(grmhd_ctx* ctx, const double* P, double* max_divb) {
   if (!ctx) return GRMHD_EINVAL;
   if (!P || !max_divb) return fail(ctx, GRMHD_EINVAL, "divb: NULL argument");
   HIP_OR_FAIL(ctx, launch_divb(ctx->p, ctx->d, ctx->t, P, ctx->ctr, ctx->stream), "divb");
-  unsigned long long bits = 0;
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(&bits, &ctx->ctr->divb, sizeof(bits), hipMemcpyDeviceToHost, ctx->stream), "copy");
-  HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "synchronize");
-  std::memcpy(max_divb, &bits, sizeof(double));
-  return GRMHD_OK;
+  Counters h;
+  const int st = read_counters(ctx, &h);
+  if (st == GRMHD_OK) std::memcpy(max_divb, &h.divb, sizeof(double));
+  return st;
 }
 
 }  // extern "C"

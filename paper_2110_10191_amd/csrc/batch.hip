@@ -2,9 +2,8 @@
 // kernel phase, one step of all active jobs captured once in a HIP graph.
 //
 // Per step (all active jobs at once):
-//   reset(fail_total)
-//   predictor: ghosts(P); reset(fail); sweeps(P); update(P -> P_h, dt/2); fixup
-//   corrector: ghosts(P_h); reset(ctop, fail); sweeps(P_h) + ctop; update((P, P_h) -> P, dt); fixup
+//   predictor: ghosts(P) + reset(fail, totals); sweeps(P); update(P -> P_h, dt/2); fixup
+//   corrector: ghosts(P_h) + reset(ctop, fail); sweeps(P_h) + ctop; update((P, P_h) -> P, dt); fixup
 //   dt_j <- min(cfl / sum_d (ctop_d / dx_d), 1.3 dt_j)
 // With electron heating (jobs given entropies E), each substep also fills
 // the scalar ghosts after the fluid ghosts, and advects and heats after the
@@ -75,7 +74,6 @@ hipError_t enqueue_step(grmhd_batch* b) {
   const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->sbx, b->sby, b->utx, b->uty, b->axi};
   hipStream_t s = b->stream;
   hipError_t e;
-  if ((e = launch_batch_reset(bv, 8, s)) != hipSuccess) return e;
   for (int corr = 0; corr < 2; ++corr) {
     {
       ProfScope ps(b->prof, s, GRMHD_K_GHOSTS);
@@ -85,7 +83,6 @@ hipError_t enqueue_step(grmhd_batch* b) {
       ProfScope ps(b->prof, s, GRMHD_K_ELECTRONS);
       if ((e = launch_batch_scalar_ghosts(bv, b->totals, corr == 1, s)) != hipSuccess) return e;
     }
-    if ((e = launch_batch_reset(bv, corr ? (1 | 4) : 4, s)) != hipSuccess) return e;
     {
       ProfScope ps(b->prof, s, GRMHD_K_SWEEPS);
       if ((e = launch_batch_sweeps(bv, b->totals, b->recon, b->mixed, corr == 1, corr == 1, s)) != hipSuccess)

@@ -97,6 +97,7 @@ struct grmhd_ctx {
   void* F;     // what the face-flux pass leaves (FluxOut)
   int8_t* flags;
   Counters* ctr;
+  Counters* host;  // pinned: the counters as last read back
   double* noalloc;  // this device's static scratch (grmhd_divb_noalloc), not owned
   UpdateParams up;
   double dx[3];

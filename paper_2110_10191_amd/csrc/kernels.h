@@ -104,7 +104,9 @@ __device__ inline int batch_job(const int* offs, int njobs, int b) {
 void job_phase_blocks(const Dims& d, int counts[PH_COUNT]);
 
 // corrector = false: predictor (ghosts of P, fluxes of P, P_base = P -> P_h, dt/2);
-// corrector = true: ghosts of P_h, fluxes of P_h, (P, P_h) -> P with dt.
+// corrector = true: ghosts of P_h, fluxes of P_h, (P, P_h) -> P with dt. The
+// ghost fill also clears the counters the substep counts into (the predictor's
+// the step's totals).
 // totals[ph] = grid size of phase ph over the batch.
 hipError_t launch_batch_ghosts(const BatchView& bv, const int* totals, bool corrector, hipStream_t s);
 // the face fluxes of all three directions of every job
@@ -113,7 +115,6 @@ hipError_t launch_batch_sweeps(const BatchView& bv, const int* totals, int recon
 // which: 1 the update, 2 the fixup, 3 both
 hipError_t launch_batch_update(const BatchView& bv, const int* totals, bool mixed, bool corrector, int which,
                                hipStream_t s);
-hipError_t launch_batch_reset(const BatchView& bv, int mask, hipStream_t s);
 // electron passes of the jobs that have entropies (the others' blocks return
 // at once): the scalar ghosts (ghost phase grids); advection and heating (update
 // phase grid)
@@ -126,11 +127,14 @@ hipError_t launch_batch_dt(const BatchView& bv, hipStream_t s);
 hipError_t launch_geometry(const grmhd_problem& p, const Dims& d, const Tables& t, hipStream_t s);
 
 // the step-size rule dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 dt) on the
-// counters of the previous step (on = 0: not applied)
+// counters of the previous step (DT_RULE), or the host's step size, with the
+// status cleared (DT_SET)
+enum { DT_NONE = 0, DT_RULE, DT_SET };
 struct DtRule {
   int on;
   double cfl;
   double dx[3];
+  double dt;  // DT_SET
 };
 
 // with ctr: block 0 first applies dt_rule (when on) and then clears the
@@ -154,8 +158,10 @@ hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const Updat
                          const void* F, const double* Pb, const double* Ps, double* Pout, int8_t* flags, double dt,
                          const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s);
 
-// ctr->dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 ctr->dt) on the device
-hipError_t launch_ctx_dt(Counters* ctr, double cfl, double dx1, double dx2, double dx3, hipStream_t s);
+// ctr->dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 ctr->dt) on the device (cfl > 0),
+// then, with host (pinned memory), the counters' values into *host, which the
+// host may read once the stream is synchronised
+hipError_t launch_ctx_dt(Counters* ctr, double cfl, double dx1, double dx2, double dx3, Counters* host, hipStream_t s);
 
 // halo: bit 2 d + side set where the ghost layer on that side of direction d
 // holds a neighbouring part's zones (values and failure flags) for the fixup
