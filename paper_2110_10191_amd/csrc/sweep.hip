@@ -36,12 +36,12 @@
 //
 // The face states are written in the 3+1 form (side_speeds, side_flux): 12 or
 // 14 geometry values a face. WENO5 is bound by its arithmetic (2800 VALU
-// instructions a wave in mixed precision). In x1 a lane finds both edges of its
-// own zone, which share the smoothness indicators (MC: the slope), and passes
-// the right one on; with the indicators in differences and one corrected
-// reciprocal per division the pass takes 0.48 ms on the benchmark torus in
-// mixed precision (0.55 with the plain formula at every face) and 89 us on
-// 131 x 67 x 45 in FP64 (117).
+// instructions a wave in mixed precision before x2 shared its edges). In x1 a
+// lane finds both edges of its own zone, which share the smoothness indicators
+// (MC: the slope), and passes the right one on, in x2 a row does (row_sides);
+// with the indicators in differences and one corrected reciprocal per division
+// the pass takes 0.47 ms on the benchmark torus in mixed precision (0.55 with
+// the plain formula at every face) and 88 us on 131 x 67 x 45 in FP64 (117).
 //
 // The per-direction maximum of ctop over the faces with interior transverse
 // index feeds the Courant step (one atomic max per block and direction); a
@@ -71,12 +71,13 @@ enum { GEO_AXI = 0, GEO_TABLE, GEO_CKS };
 // between variables are then constants, and a stencil read needs no address of
 // its own per variable (with runtime strides the loop over planes kept some 50
 // such addresses in registers and spilled).
-template <int RECON, int BX, int BY>
+template <int RECON, int BX_, int BY_>
 struct PlaneShape {
   // halo: zones before / after the cell in x1 (both edges of the zone are found together) and
   // below / above it in x2 (the faces of a row need the zones below)
   static constexpr int LX = RECON == GRMHD_RECON_MC ? 1 : 2, HX = LX;
   static constexpr int LY = RECON == GRMHD_RECON_MC ? 2 : 3, HY = LY - 1;
+  static constexpr int BX = BX_, BY = BY_;
   static constexpr int LW = BX + LX + HX, LH = BY + LY + HY, PLANE = LW * LH, NTHR = BX * BY;
 };
 
@@ -96,6 +97,20 @@ __device__ inline T next_lane(T x) { return dpp<WAVE_SHL1>(x); }
 template <typename T>
 __device__ inline T prev_lane(T x) { return dpp<WAVE_SHR1>(x); }
 
+// both edges, along the direction whose zones are st apart, of the zone at e:
+// they share its slope or its smoothness indicators
+template <int RECON, typename T>
+__device__ inline void zone_edges(const T* e, int st, T& left, T& right) {
+  if constexpr (RECON == GRMHD_RECON_MC) {
+    const T c = e[0];
+    const McSlope<T> m(c - e[-st], e[st] - c);
+    left = m.below(c);
+    right = m.above(c);
+  } else {
+    weno5_edges(e[-2 * st], e[-st], e[0], e[st], e[2 * st], left, right);
+  }
+}
+
 // both sides of the lower D-face of the cell whose place in the staged plane
 // is q; the other planes of an x3 stencil come from the state, at byte offset cb
 // of each variable (planes pb apart)
@@ -106,18 +121,10 @@ __device__ inline void face_sides(const double* __restrict__ P, size_t sv, const
   for (int v = 0; v < NV; ++v) {
     const T* ql = q + v * SH::PLANE;
     if constexpr (D == 1) {
-      // both edges of the cell's zone, which share slope or smoothness; the left side of its
-      // lower face is the right edge of the zone the lane before holds (a row's first lane
-      // has none: its face is not used)
+      // the left side of the cell's lower face is the right edge of the zone the lane before
+      // holds (a row's first lane has none: its face is not used)
       T right;
-      if constexpr (RECON == GRMHD_RECON_MC) {
-        const T e = ql[0];
-        const McSlope<T> m(e - ql[-1], ql[1] - e);
-        R.P[v] = m.below(e);
-        right = m.above(e);
-      } else {
-        weno5_edges(ql[-2], ql[-1], ql[0], ql[1], ql[2], R.P[v], right);
-      }
+      zone_edges<RECON>(ql, 1, R.P[v], right);
       L.P[v] = prev_lane(right);
       continue;
     }
@@ -135,6 +142,45 @@ __device__ inline void face_sides(const double* __restrict__ P, size_t sv, const
       R.P[v] = weno5_edge(x5, x4, x3, x2, x1);
     }
   }
+}
+
+// Both sides of the lower x2-face of each cell: a row finds both edges of its
+// own zones and hands the upper ones to the row above through LDS, over the
+// staged plane (its last use). The first row's wave also finds those of the
+// zones below, which wait in free, of 8 BX values. All threads of the block
+// take part. WENO5 only: 0.488 -> 0.470 ms on the benchmark torus in mixed
+// precision, 90 -> 88 us on 131 x 67 x 45 in FP64; an MC slope costs less than
+// its way through LDS (0.404 -> 0.406 ms in FP64, mixed 58 -> 60 us on
+// 160 x 96 x 48).
+template <int RECON, typename T, typename SH>
+__device__ inline void row_sides(T* plane, T* free, const T* q, int li, int lj, int tid, FaceSide<T>& L, FaceSide<T>& R) {
+  constexpr int BX = SH::BX, ST = SH::NTHR + BX;  // rows -1..BY-1
+  static_assert(NV * ST <= NV * SH::PLANE, "the exchanged rows fit the staged plane");
+  const bool first = __builtin_amdgcn_readfirstlane(tid) < 64;
+  if (first) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      T lo, hi;
+      zone_edges<RECON>(q + v * SH::PLANE - SH::LW, SH::LW, lo, hi);
+      if (lj == 0) free[v * BX + li] = hi;
+      FACE_FENCE;
+    }
+  }
+  FACE_FENCE;
+  T up[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) zone_edges<RECON>(q + v * SH::PLANE, SH::LW, R.P[v], up[v]);
+  __syncthreads();
+  T* const x = plane + BX + tid;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) x[v * ST] = up[v];
+  if (lj == 0) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) x[v * ST - BX] = free[v * BX + li];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < NV; ++v) L.P[v] = x[v * ST - BX];
 }
 
 // The local Lax-Friedrichs flux of a face (mass, energy, 3 momenta, then the
@@ -264,9 +310,16 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
   FACE_FENCE;
   {
     FaceGeo<T> g;
-    geo(2, a.t2, g);
     FaceSide<T> SL, SR;
-    face_sides<2, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
+    if constexpr (RECON == GRMHD_RECON_MC) {
+      geo(2, a.t2, g);
+      face_sides<2, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
+    } else {
+      // the exchange's fourth and fifth values are still free
+      row_sides<RECON, T, SH>(L, L + NV * SH::PLANE + 3 * SH::NTHR, q, li, lj, tid, SL, SR);
+      FACE_FENCE;
+      geo(2, a.t2, g);
+    }
     face_flux<2, AXI, CTOP>(SL, SR, g, a.gam, f, X + 2 * SH::NTHR, ok && j >= 0 && in1 && hydro);
     if (a.mass && we && hydro) a.mass[sv + c] = f[0];
     if (axis) {
