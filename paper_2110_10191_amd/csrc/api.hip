@@ -567,8 +567,8 @@ int grmhd_get_dt(grmhd_ctx* ctx, double* P, double* dt) {
   if (!P || !dt) return fail(ctx, GRMHD_EINVAL, "get_dt: NULL argument");
   hipStream_t s = ctx->stream;
   HIP_OR_FAIL(ctx, launch_fill_ghosts(ctx->p, ctx->d, ctx->t, P, P, s, ctx->ctr, 1), "ghost fill");
-  HIP_OR_FAIL(ctx, launch_sweeps(ctx->p, ctx->mixed, ctx->d, ctx->t, ctx->up, P, ctx->F, false, ctx->ctr->ctop, s),
-              "sweeps");
+  HIP_OR_FAIL(ctx, launch_sweeps(ctx->p, ctx->mixed, ctx->d, ctx->t, ctx->up, P, nullptr, false, ctx->ctr->ctop, s),
+              "speeds");
   return read_dt(ctx, dt);
 }
 

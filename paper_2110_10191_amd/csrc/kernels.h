@@ -147,7 +147,7 @@ hipError_t launch_fill_ghosts(const grmhd_problem& p, const Dims& d, const Table
 // float for mixed) with the problem's reconstruction and gamma; Cartesian
 // Kerr-Schild computes its face geometry instead of reading the face tables;
 // mass: the mass fluxes as well; ctop (may be null) receives the per-direction
-// maximum signal speeds; sweep_blocks: the launch's grid size
+// maximum signal speeds (F null: nothing else); sweep_blocks: the launch's grid size
 unsigned sweep_blocks(const Dims& d);
 hipError_t launch_sweeps(const grmhd_problem& p, bool mixed, const Dims& d, const Tables& t, const UpdateParams& up,
                          const double* P, void* F, bool mass, unsigned long long* ctop, hipStream_t s);
@@ -160,7 +160,7 @@ hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const Updat
 
 // ctr->dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 ctr->dt) on the device (cfl > 0),
 // then, with host (pinned memory), the counters' values into *host, which the
-// host may read once the stream is synchronised
+// host may read once the stream is synchronised, and the div B maximum to zero
 hipError_t launch_ctx_dt(Counters* ctr, double cfl, double dx1, double dx2, double dx3, Counters* host, hipStream_t s);
 
 // halo: bit 2 d + side set where the ghost layer on that side of direction d
@@ -181,7 +181,7 @@ hipError_t launch_divb(const grmhd_problem& p, const Dims& d, const Tables& t, c
 // div B without library-owned memory: per-block maxima in the device-resident
 // static scratch (DIVB_NOALLOC_PARTS slots, then the result at slot
 // DIVB_NOALLOC_PARTS). noalloc_scratch gives that array's address on the
-// device (which must be current); divb_blocks the number of slots a grid needs.
+// device (which must be current); divb_blocks the slots a grid may need at most.
 constexpr int DIVB_NOALLOC_PARTS = 65536;
 long long divb_blocks(const Dims& d);
 hipError_t noalloc_scratch(int device, double** ptr);
@@ -203,5 +203,5 @@ hipError_t launch_electrons(bool mixed, int recon, const Dims& d, const Tables& 
                             double dt, const double* dt_dev, double dt_scale, int model, double fel, Counters* ctr,
                             hipStream_t s);
 
-// zero the counters selected by mask (1: ctop, 2: divb, 4: fail, 8: fail_total and bad)
+// zero the counters selected by mask (1: ctop, 4: fail, 8: fail_total and bad)
 hipError_t launch_reset(Counters* ctr, int mask, hipStream_t s);

@@ -183,13 +183,12 @@ __device__ inline void row_sides(T* plane, T* free, const T* q, int li, int lj, 
   for (int v = 0; v < NV; ++v) L.P[v] = x[v * ST - BX];
 }
 
-// The local Lax-Friedrichs flux of a face (mass, energy, 3 momenta, then the
-// two transverse field components in ascending order) in f. CTOP: *top takes
-// the signal speed for the Courant maximum, 0 for a face outside it (inner
-// false) and +inf when a speed is not finite (fmax drops a NaN operand, so such
-// a face would report a finite, often zero, speed)
+// Signal speeds of both sides of a face and their largest, ctop. CTOP: *top
+// takes it for the Courant maximum, 0 for a face outside it (inner false) and
+// +inf when a speed is not finite (fmax drops a NaN operand, so such a face
+// would report a finite, often zero, speed)
 template <int D, bool AXI, bool CTOP, typename T>
-__device__ inline void face_flux(FaceSide<T>& L, FaceSide<T>& R, const FaceGeo<T>& g, T gam, T* f, T* top, bool inner) {
+__device__ inline T face_speeds(FaceSide<T>& L, FaceSide<T>& R, const FaceGeo<T>& g, T gam, T* top, bool inner) {
   side_speeds<D, AXI>(L, g, gam);
   side_speeds<D, AXI>(R, g, gam);
   const T ct = fmax(fmax(fmax(T(0), L.cp), R.cp), fmax(-L.cm, -R.cm));
@@ -197,6 +196,14 @@ __device__ inline void face_flux(FaceSide<T>& L, FaceSide<T>& R, const FaceGeo<T
     const T chk = (L.cp + L.cm) + (R.cp + R.cm);
     *top = !inner ? T(0) : chk == chk ? ct : (T)__builtin_inf();
   }
+  return ct;
+}
+
+// The local Lax-Friedrichs flux of a face (mass, energy, 3 momenta, then the
+// two transverse field components in ascending order) in f
+template <int D, bool AXI, bool CTOP, typename T>
+__device__ inline void face_flux(FaceSide<T>& L, FaceSide<T>& R, const FaceGeo<T>& g, T gam, T* f, T* top, bool inner) {
+  const T ct = face_speeds<D, AXI, CTOP>(L, R, g, gam, top, inner);
   T fr[7];
   side_flux<D, AXI>(L, g, gam, ct, f);
   side_flux<D, AXI>(R, g, gam, -ct, fr);
@@ -219,6 +226,23 @@ struct SweepArgs {
   T gam;
   int polar_lo, polar_hi;
 };
+
+// stage the plane: cells [ib, ib + LW) x [jb, jb + LH), those inside the padded
+// state (cells outside it are never read: faces start at cell 0 and end at n)
+template <typename SH, typename T>
+__device__ inline void stage_plane(const Dims& d, const double* P, T* L, int ib, int jb, int k, int tid) {
+#pragma unroll
+  for (int e0 = 0; e0 < SH::PLANE; e0 += SH::NTHR) {
+    const int e = e0 + tid;
+    const int ej = e / SH::LW, ei = e - ej * SH::LW;
+    const int gi = ib + ei, gj = jb + ej;
+    if (e < SH::PLANE && gi >= -NG && gi < d.n1 + NG && gj >= -NG && gj < d.n2 + NG) {
+      const unsigned c = (unsigned)cell_of(d, k, gj, gi) * (unsigned)sizeof(double);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) L[v * SH::PLANE + e] = (T)buf_f64(P + (size_t)v * d.sv, c);
+    }
+  }
+}
 
 // b: block index within this job's grid; BX x BY threads
 template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
@@ -248,19 +272,7 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
   const unsigned pb = (unsigned)d.s3 * (unsigned)sizeof(double);
   const int toff = tab_of(d, jc, ic);
   constexpr bool AXI = GEO == GEO_AXI;
-  // stage the plane: cells [ib, ib + LW) x [jb, jb + LH), those inside the padded state
-  // (cells outside it are never read: faces start at cell 0 and end at n)
-#pragma unroll
-  for (int e0 = 0; e0 < SH::PLANE; e0 += SH::NTHR) {
-    const int e = e0 + tid;
-    const int ej = e / SH::LW, ei = e - ej * SH::LW;
-    const int gi = ib + ei, gj = jb + ej;
-    if (e < SH::PLANE && gi >= -NG && gi < d.n1 + NG && gj >= -NG && gj < d.n2 + NG) {
-      const unsigned c = (unsigned)cell_of(d, k, gj, gi) * (unsigned)sizeof(double);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) L[v * SH::PLANE + e] = (T)buf_f64(a.P + (size_t)v * d.sv, c);
-    }
-  }
+  stage_plane<SH>(d, a.P, L, ib, jb, k, tid);
   __syncthreads();
   const int c = cell_of(d, k, j, i);
   const unsigned cb = (unsigned)cell_of(d, k, jc, ic) * (unsigned)sizeof(double);
@@ -359,6 +371,53 @@ __global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_kernel(
   sweep_body<RECON, T, GEO, CTOP, BX, BY>(d, a, (int)blockIdx.x, ctop);
 }
 
+// The Courant maxima alone, of a state whose fluxes no one asks for: the same
+// tiles, faces and speeds, without flux, exchange or output (85 us on
+// 192 x 96 x 64 FP64 MC zones, 117 to 122 with the fluxes)
+template <int RECON, typename T, int GEO, int BX, int BY>
+__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void speed_kernel(Dims d, SweepArgs<T> a,
+                                                                          unsigned long long* ctop) {
+  using SH = PlaneShape<RECON, BX, BY>;
+  const SweepTile t = sweep_tile(d, BX, BY, (int)blockIdx.x);
+  if (!t.valid || t.k < 0) return;
+  const int li = (int)threadIdx.x, lj = (int)threadIdx.y, tid = lj * BX + li;
+  const int i = t.i0 + li, j = t.j0 + lj, k = t.k;
+  extern __shared__ __align__(16) unsigned char sweep_lds[];
+  T* const L = reinterpret_cast<T*>(sweep_lds);
+  const T* const q = L + (lj + SH::LY) * SH::LW + li + SH::LX;
+  const bool ok = i <= d.n1 && j <= d.n2;
+  const bool in1 = i >= 0 && i < d.n1, in2 = j >= 0 && j < d.n2, in3 = k < d.n3;
+  const int ic = min(i, d.n1), jc = min(j, d.n2);
+  const int toff = tab_of(d, jc, ic);
+  const unsigned pb = (unsigned)d.s3 * (unsigned)sizeof(double);
+  const unsigned cb = (unsigned)cell_of(d, k, jc, ic) * (unsigned)sizeof(double);
+  const size_t sv = (size_t)d.sv;
+  constexpr bool AXI = GEO == GEO_AXI;
+  stage_plane<SH>(d, a.P, L, t.i0 - SH::LX, t.j0 - SH::LY, k, tid);
+  __syncthreads();
+  auto top = [&](auto dir, const T* tab, bool inner) -> double {
+    constexpr int D = decltype(dir)::value;
+    FaceSide<T> SL, SR;
+    if constexpr (D == 2 && RECON != GRMHD_RECON_MC)
+      row_sides<RECON, T, SH>(L, L + NV * SH::PLANE, q, li, lj, tid, SL, SR);
+    else face_sides<D, RECON, T, SH>(a.P, sv, q, cb, pb, SL, SR);
+    FACE_FENCE;
+    FaceGeo<T> g;
+    if constexpr (GEO == GEO_CKS) cks_face_geo(d.box, D, ic, jc, k, g);
+    else load_face_geo<AXI>(g, pair_plane(tab, d, k), d.ts, toff);
+    T m;
+    face_speeds<D, AXI, true>(SL, SR, g, a.gam, &m, inner);
+    double c = (double)m;
+    asm volatile("" : "+v"(c));  // the face ends here
+    FACE_FENCE;
+    return c;
+  };
+  const double c3 = top(std::integral_constant<int, 3>(), a.t3, in1 && in2);
+  const double c1 = top(std::integral_constant<int, 1>(), a.t1, li > 0 && ok && i >= 0 && in2 && in3);
+  const double c2 = top(std::integral_constant<int, 2>(), a.t2, ok && j >= 0 && in1 && in3);
+  block_max3_to(c1, c2, c3, ctop);
+}
+
 template <typename T>
 struct FaceTables;
 template <>
@@ -431,11 +490,24 @@ hipError_t launch_ctop(const Dims& d, const SweepArgs<T>& a, unsigned long long*
 }
 
 template <int RECON, typename T, int GEO>
+hipError_t launch_speeds(const Dims& d, const SweepArgs<T>& a, unsigned long long* ctop, hipStream_t s) {
+  return with_shape<RECON, T>(d, [&](auto bx, auto by) {
+    constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
+    constexpr size_t lds = (size_t)NV * (PlaneShape<RECON, BX, BY>::PLANE + BX) * sizeof(T);
+    const hipError_t e = allow_lds<speed_kernel<RECON, T, GEO, BX, BY>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((speed_kernel<RECON, T, GEO, BX, BY>), dim3(sweep_blocks(d)), dim3(BX, BY, 1), lds, s, d, a, ctop);
+    return hipGetLastError();
+  });
+}
+
+template <int RECON, typename T, int GEO>
 hipError_t launch_geo(const Dims& d, const Tables& t, const UpdateParams& up, const double* P, void* F,
                       bool mass, unsigned long long* ctop, hipStream_t s) {
   const FluxOut<T> out = flux_out<T>((unsigned char*)F, d.sv);
   const SweepArgs<T> a{P,       FaceTables<T>::f1(t), FaceTables<T>::f2(t), FaceTables<T>::f3(t), out, mass ? out.m : nullptr,
                        up.idx1, up.idx2,              up.idx3,              (T)up.gam,            up.polar_lo, up.polar_hi};
+  if (!F) return launch_speeds<RECON, T, GEO>(d, a, ctop, s);
   if (ctop) return launch_ctop<RECON, T, GEO, true>(d, a, ctop, s);
   return launch_ctop<RECON, T, GEO, false>(d, a, ctop, s);
 }
