@@ -23,6 +23,7 @@
 // Bounds (Implementation Notes): Gamma <= gamma_max by rescaling u~; then
 // rho >= max(rho_fl k, b^2/sigma_max); u >= max(u_fl k^gamma, beta_min b^2/(2(gamma-1)));
 // rho >= u/uorho_max; k = 1/(r^2 (1 + r/10)).
+#include <algorithm>
 #include <type_traits>
 
 #include "cks_geometry.h"
@@ -416,12 +417,17 @@ __global__ __launch_bounds__(256) void fixup_kernel(Dims d, const double* __rest
   for (int b = (int)blockIdx.x; b < ntiles; b += (int)gridDim.x) fixup_body(d, cent, up, P, flags, ctr, halo, b);
 }
 
-__global__ __launch_bounds__(256) void fixup_batch_kernel(BatchView bv, int corrector) {
-  const int* offs = bv.offs + PH_UPDATE * (bv.njobs + 1);
-  const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
+// per blocks a job stride over its tiles, with the same early exit: a block per
+// tile took 45 us a substep on 16 jobs of 10 million zones in all, none of them failed
+__global__ __launch_bounds__(256) void fixup_batch_kernel(BatchView bv, int corrector, int per) {
+  const int jb = (int)blockIdx.x / per;
   const JobDesc& J = bv.jobs[jb];
-  fixup_body(J.d, global_ptr(J.t.cent), J.up, global_ptr(corrector ? J.P : J.Ph), global_ptr(J.flags),
-             global_ptr(J.ctr), 0, (int)blockIdx.x - offs[jb]);
+  Counters* ctr = global_ptr(J.ctr);
+  if (ctr->fail == 0u) return;
+  const int* offs = bv.offs + PH_UPDATE * (bv.njobs + 1);
+  const int ntiles = offs[jb + 1] - offs[jb];
+  for (int b = (int)blockIdx.x - jb * per; b < ntiles; b += per)
+    fixup_body(J.d, global_ptr(J.t.cent), J.up, global_ptr(corrector ? J.P : J.Ph), global_ptr(J.flags), ctr, 0, b);
 }
 
 // prim->cons and cons->prim read and write 16 and 24 values a zone and are
@@ -538,7 +544,11 @@ hipError_t launch_batch_update(const BatchView& bv, const int* totals, bool mixe
     if (mixed) update_batch_for<float>(bv, grd, corrector, s);
     else update_batch_for<double>(bv, grd, corrector, s);
   }
-  if (which & 2) hipLaunchKernelGGL(fixup_batch_kernel, grd, blk, 0, s, bv, c);
+  if (which & 2) {
+    // as many blocks in all as a single job's fixup, 64 or more a job
+    const int per = std::min(std::max(64, (int)FIXUP_BLOCKS / bv.njobs), totals[PH_UPDATE]);
+    hipLaunchKernelGGL(fixup_batch_kernel, dim3(bv.njobs * per), blk, 0, s, bv, c, per);
+  }
   return hipGetLastError();
 }
 
