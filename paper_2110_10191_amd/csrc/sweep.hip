@@ -22,13 +22,15 @@
 // or below (the x3 fluxes, the x1 and x2 flux of B3) goes out as it is.
 //
 // What bounds it: FP64 issue and the latency of its loads, about half each (a
-// wave issues some 1300 VALU instructions, 500 of them the MC slopes). It runs
+// wave issues 1270 VALU instructions, 1410 with the Courant maxima, 480 of them the
+// MC slopes). It runs
 // at four waves a SIMD, so a face may hold 128 registers: sums and speeds wait
 // in LDS, and FACE_FENCE keeps the three faces apart. On the 288 x 128 x 128
-// torus in FP64 with MC slopes it takes 0.410 ms; writing the three flux arrays
-// it took 0.451, and the update, which read 66 of their values a cell and now
-// reads 35, 0.605 against 0.470 (mixed-precision WENO5: the pass 0.50 -> 0.55,
-// the update 0.57 -> 0.42). The tiles are walked x2 first, so a block finds the
+// torus in FP64 with MC slopes it takes 0.403 ms. Writing the three flux arrays
+// it took 0.451 where this form took 0.410, and the update, which then read 66 of
+// their values a cell and now reads 35, 0.605 against 0.470 (0.363 with its later
+// changes; mixed-precision WENO5: the pass 0.50 -> 0.55, now 0.47, the update
+// 0.57 -> 0.42, now 0.31). The tiles are walked x2 first, so a block finds the
 // rows it shares with the tile before in the XCD's L2 (0.94 -> 0.61 GB read).
 // A block that walks along 4 to 32 planes with running sums writes 8 values a
 // cell instead of 15, but its registers leave three waves a SIMD and its
