@@ -196,6 +196,7 @@ __device__ inline double sqrt_full(double x) {
   const double g1 = fma(g, e, g), h1 = fma(h, e, h);
   return fma(fma(-g1, g1, x), h1, g1);
 }
+// subnormal arguments count as 0: for numbers of order one, as side_speeds has them
 __device__ inline float sqrt_full(float x) { return __builtin_amdgcn_sqrtf(x); }
 
 // a / b from r = rcp_full(b) with one correction of the quotient, which rounds
@@ -220,8 +221,11 @@ __device__ inline double div_by(double a, double b, double r) {
 // c_s^2 (1 - v_A^2) as one quotient). With m = den - num = rho + gamma (2 -
 // gamma) u, q = num/Gamma^2 and y = u~^D/u^t the two roots of the dispersion
 // relation are
-//   (m y +- sqrt(q ((m + q) H - m y^2)))/(m + q) - beta^D,
-// with no cancelling products.
+//   z +- sqrt(q/(m + q) (H - z y)) - beta^D,  z = m y/(m + q),
+// with no cancelling products, and quotients of densities alone: the product of
+// two, q ((m + q) H - m y^2) under the root, is subnormal in FP32 where rho u is
+// below 1e-38 (rho of 1e-14 and u of 3e-20 in a torus' outer atmosphere, with H
+// = 1/r^2), and the hardware's root takes a subnormal number as 0.
 // Flux and conserved variables differ in one factor only, v^D against 1 and
 // b^D against b^t, so F + s U (s = ctop on the left, -ctop on the right) is the
 // flux with the velocity W = v^D + s in place of v^D:
@@ -263,13 +267,10 @@ __device__ inline void side_speeds(FaceSide<T>& s, const FaceGeo<T>& g, T gam) {
   const T gp = gam * (gam - T(1));
   const T m = P[0] + (gam - gp) * P[1];
   const T q = (gp * P[1] + s.bsq) * (rl * rl);
-  const T A = m + q;
+  const T iA = rcp_full(m + q);
   const T y = P[1 + D] * s.iut;
-  const T my = m * y;
-  const T disc = q * (A * g.H - my * y);
-  const T iA = rcp_full(A);
-  const T r = fabs(sqrt_full(fmax(disc, T(0))) * iA);
-  T mid = my * iA;
+  T mid = m * y * iA;
+  const T r = sqrt_full(fmax((q * iA) * (g.H - mid * y), T(0)));
   if constexpr (D == 1) mid = mid - g.b1;
   else if constexpr (D == 2) mid = mid - g.b2;
   else if constexpr (!AXI) mid = mid - g.b3;

@@ -463,7 +463,8 @@ __global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_batch_k
                        global_ptr(FaceTables<T>::f2(J.t)), global_ptr(FaceTables<T>::f3(J.t)), out,
                        J.E ? out.m : nullptr, J.up.idx1, J.up.idx2, J.up.idx3, (T)J.p.gam, J.up.polar_lo,
                        J.up.polar_hi};
-  sweep_body<RECON, T, GEO, CTOP, BX, BY>(J.d, a, (int)blockIdx.x - offs[jb], CTOP ? global_ptr(J.ctr->ctop) : nullptr);
+  const Dims d = J.d;  // kept: read from the table where needed, the FP64 MC predictor spills 6 registers
+  sweep_body<RECON, T, GEO, CTOP, BX, BY>(d, a, (int)blockIdx.x - offs[jb], CTOP ? global_ptr(J.ctr->ctop) : nullptr);
 }
 
 template <int RECON, typename T, int BX, int BY>
