@@ -309,10 +309,13 @@ GRMHD_API int grmhd_profile_read(grmhd_ctx *ctx, int32_t kernel, double *total_m
  * update and fixup kernels (GRMHD_TILE_UPDATE): tx zones along x1 by ty along
  * x2, one thread per zone; tx a power of two in [16, 256], tx * ty a multiple
  * of 64 and at most 512 (sweeps) or 256 (update). The update uses the tile as
- * it is. The face-flux kernel has two block shapes, 512 threads (64 x 8, FP64
- * WENO5 32 x 16) and 32 x 8; it takes the small one for a tile of 256 threads or
- * fewer and on grids too small to fill the device with large blocks. Defaults:
- * sweeps 64 x 8, update 64 x 1. Results do not depend on the tile. A batch uses
+ * it is. The face-flux kernel has three block shapes, 512 threads (64 x 8, FP64
+ * WENO5 32 x 16), 32 x 8 and 16 x 8. With the default tile the grid decides (the
+ * first, the second on grids that it covers with fewer threads or that are too
+ * small to fill the device, the third at up to 14 zones in x1); any other tile
+ * names a shape: the third if it is 16 zones wide, otherwise the first above 256
+ * threads and the second up to there. Defaults: sweeps 64 x 8, update 64 x 1.
+ * Results do not depend on the tile. A batch, whose jobs share a shape, uses
  * the tiles of its first job for every job. Errors: EINVAL. */
 enum { GRMHD_TILE_SWEEP = 0, GRMHD_TILE_UPDATE = 1 };
 GRMHD_API int grmhd_set_tiles(grmhd_ctx *ctx, int32_t which, int32_t tx, int32_t ty);

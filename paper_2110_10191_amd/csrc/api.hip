@@ -110,7 +110,9 @@ int validate(const grmhd_problem* p, std::string& why) {
 // the block shape of the face-flux pass from the tile asked for and the grid
 void pick_sweep_shape(Dims& d, const grmhd_problem& p) {
   const bool mixed = p.precision == GRMHD_MIXED;
-  sweep_shape(d, p.recon, mixed, sweep_small(d, sweep_grid(d, large_bx(p.recon, mixed), large_by(p.recon, mixed))));
+  SweepBlocks blocks;
+  blocks.add(d, p.recon, mixed);
+  set_sweep_shape(d, sweep_shape(d.stx, d.sty, blocks, p.recon, mixed), p.recon, mixed);
 }
 
 Dims make_dims(const grmhd_problem& p) {

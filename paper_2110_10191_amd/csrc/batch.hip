@@ -38,7 +38,7 @@ struct grmhd_batch {
   int nactive = 0;
   int axi = 1;                     // no active job has Cartesian Kerr-Schild coordinates
   int stx = TILE_X, sty = SWEEP_TILE_Y, utx = TILE_X, uty = TILE_Y;  // tiles of every job
-  int sbx = SMALL_BX, sby = SMALL_BY;  // block shape of the face-flux pass
+  int shape = SWEEP_SMALL;         // block shape of the face-flux pass
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   Profiler prof;  // when on, steps run eagerly with each launch bracketed by events
@@ -71,7 +71,7 @@ void drop_graph(grmhd_batch* b) {
 // enqueue one step of every job in the current job table (events around the
 // launches only when profiling, which never happens under capture)
 hipError_t enqueue_step(grmhd_batch* b) {
-  const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->sbx, b->sby, b->utx, b->uty, b->axi};
+  const BatchView bv{b->d_jobs, b->d_offs, b->nactive, b->shape, b->utx, b->uty, b->axi};
   hipStream_t s = b->stream;
   hipError_t e;
   for (int corr = 0; corr < 2; ++corr) {
@@ -112,7 +112,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
   std::vector<int> counts;  // [job][phase]
   bool electrons = false;
   int axi = 1;
-  long long large = 0;  // blocks of the face-flux pass in its large shape, over all jobs
+  SweepBlocks blocks;  // of the face-flux pass over all jobs
   for (int j = 0; j < n; ++j) {
     if (active && !active[j]) continue;
     if (!P[j]) return bfail(b, GRMHD_EINVAL, "batch_step: NULL state for an active job");
@@ -154,12 +154,11 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
       jd.fel = fel[j];
     }
     jobs.push_back(jd);
-    large += sweep_grid(jd.d, large_bx(b->recon, b->mixed), large_by(b->recon, b->mixed));
+    blocks.add(jd.d, b->recon, b->mixed);
   }
+  const int shape = sweep_shape(b->stx, b->sty, blocks, b->recon, b->mixed);
   for (JobDesc& jd : jobs) {
-    sweep_shape(jd.d, b->recon, b->mixed, sweep_small(jd.d, large));
-    b->sbx = jd.d.sbx;
-    b->sby = jd.d.sby;
+    set_sweep_shape(jd.d, shape, b->recon, b->mixed);
     int cnt[PH_COUNT];
     job_phase_blocks(jd.d, cnt);
     counts.insert(counts.end(), cnt, cnt + PH_COUNT);
@@ -194,6 +193,7 @@ int configure(grmhd_batch* b, double* const* P, double* const* E, const int32_t*
       }
   b->electrons = electrons;
   b->axi = axi;
+  b->shape = shape;
   if (na == 0) return GRMHD_OK;
   // on the batch's stream, which may be a non-blocking one: a copy on the
   // null stream is not ordered before the graph launched on it, and a copy

@@ -75,7 +75,8 @@ struct Dims {
   int ts;          // table component stride (p2 * p1, or p3 * p2 * p1 for 3D tables)
   int tk;          // table k stride (0 for 2D tables, s3 for 3D)
   int stx, sty;    // thread-block tile (x1 x x2) asked for the sweeps
-  int sbx, sby;    // and the block shape they use (sweep_shape)
+  int shape;       // and the block shape they use (sweep_shape)
+  int sbx, sby;    // its extents
   int utx, uty;    // thread-block tile of the update and fixup
   int out_lo, out_hi;  // x1 lower / upper boundary is an outflow boundary
   CksBox box;          // Cartesian Kerr-Schild (tk != 0) only
@@ -515,33 +516,62 @@ __host__ __device__ inline FluxOut<T> flux_out(unsigned char* base, int sv) {
   return o;
 }
 
-// its tiles cover the cells -1..n; they overlap by two columns in x1 (a face
-// needs the cell before it, a divergence the face after it) and one row in x2
-__host__ __device__ inline int sweep_tiles_x1(int n, int b) { return (n + 1 + b - 3) / (b - 2); }
+// Its tiles cover the cells -1..n. They overlap by two columns in x1 (a face needs
+// the cell before it, a divergence the face after it) and one row in x2; the last
+// tile's last column, which has no face after it, may be cell n, which has no
+// divergence.
+__host__ __device__ inline int sweep_tiles_x1(int n, int b) { return (n + b - 3) / (b - 2); }
 __host__ __device__ inline int sweep_tiles_x2(int n, int b) { return (n + 1 + b - 2) / (b - 1); }
-// Block shapes of the face-flux pass, BX x BY threads in rows no longer than a
-// wave. The large one is 64 x 8, or 32 x 16 for FP64 WENO5, whose 64 x 8 plane
-// and exchange take 86 KB of LDS and leave one block a CU (131 x 67 x 45 torus:
-// 156 us against 117). The small one, 32 x 8, is for grids that make fewer than
-// 1024 large blocks, two rounds of the two a CU holds, and would leave CUs idle
-// (64 x 64 x 1: 14 us against 12; 96 x 64 x 32, 680 large blocks: 35 against
-// 33; 160 x 96 x 48, 2100 blocks: 58 against 61).
-constexpr int SMALL_BX = 32, SMALL_BY = 8;
-constexpr long long SMALL_BELOW = 1024;
-__host__ __device__ constexpr int large_bx(int recon, bool mixed) { return recon == GRMHD_RECON_WENO5 && !mixed ? 32 : 64; }
-__host__ __device__ constexpr int large_by(int recon, bool mixed) { return 512 / large_bx(recon, mixed); }
+// Block shapes of the face-flux pass, bx x by threads in rows no longer than a
+// wave: the large one is 64 x 8, or 32 x 16 for FP64 WENO5, whose 64 x 8 plane
+// and exchange take 86 KB of LDS and leave one block a CU; the small one 32 x 8,
+// the narrow one 16 x 8.
+enum { SWEEP_LARGE = 0, SWEEP_SMALL, SWEEP_NARROW, SWEEP_SHAPES };
+__host__ __device__ constexpr int sweep_bx(int shape, int recon, bool mixed) {
+  return shape == SWEEP_NARROW ? 16 : shape == SWEEP_SMALL || (recon == GRMHD_RECON_WENO5 && !mixed) ? 32 : 64;
+}
+__host__ __device__ constexpr int sweep_by(int shape, int recon, bool mixed) {
+  return shape == SWEEP_LARGE ? 512 / sweep_bx(shape, recon, mixed) : 8;
+}
 // blocks of a grid in the shape (bx, by)
 inline long long sweep_grid(const Dims& d, int bx, int by) {
   return (long long)sweep_tiles_x1(d.n1, bx) * sweep_tiles_x2(d.n2, by) * ((d.n3 + 2 + NXCD - 1) / NXCD) * NXCD;
 }
-// is the small shape right for a pass that makes so many large blocks? Tiles
-// set below 512 threads ask for it too.
-inline bool sweep_small(const Dims& d, long long large_blocks) {
-  return d.stx * d.sty <= SMALL_BX * SMALL_BY || large_blocks < SMALL_BELOW;
+// blocks of a pass (over one grid, or the jobs of a batch) in each shape
+struct SweepBlocks {
+  long long n[SWEEP_SHAPES] = {0, 0, 0};
+  void add(const Dims& d, int recon, bool mixed) {
+    for (int q = 0; q < SWEEP_SHAPES; ++q) n[q] += sweep_grid(d, sweep_bx(q, recon, mixed), sweep_by(q, recon, mixed));
+  }
+};
+// The shape of a pass. Tiles asked for (stx x sty other than the default) name
+// it: 16 zones wide the narrow one, otherwise above 256 threads the large one.
+// Left to the grid, the large shape, but
+// * below 1024 of its blocks, two rounds of the two a CU holds, the small one:
+//   the large would leave CUs idle (64 x 64 x 1: 13.7 us against 10.9);
+// * the small one where it covers the grid with 7/8 of the threads or less
+//   (30 x 200 x 100: 89 us against 52; 131 x 67 x 45, 5/6: 51 against 44; 192 x 96 x
+//   64, 7/8: 139 against 127; with equal threads 160 x 96 x 48 takes 83 against 77, but
+//   288 x 128 x 128 0.42 ms against 0.46, mixed 0.33 against 0.38);
+// * the narrow one where it takes 2/3 of the threads or less, at n1 <= 14 (8 x 256
+//   x 128: 70 us against 43; with equal threads, 24 x 128 x 128, 45 against 50; with
+//   3/4, 40^3 mixed, 15.9 against 16.6), in FP64 WENO5, whose large shape spans 15
+//   rows, 5/6 where it fills the device (62 x 7 x 900: 168 us against 152; 64^3 75
+//   against 71; with fewer blocks, 64 x 64 x 1, 17.7 against 21.5).
+inline int sweep_shape(int stx, int sty, const SweepBlocks& blocks, int recon, bool mixed) {
+  if (stx != SWEEP_TILE_X || sty != SWEEP_TILE_Y)
+    return stx < 32 ? SWEEP_NARROW : stx * sty > 256 ? SWEEP_LARGE : SWEEP_SMALL;
+  const auto threads = [&](int q) { return blocks.n[q] * sweep_bx(q, recon, mixed) * sweep_by(q, recon, mixed); };
+  int shape = SWEEP_LARGE;
+  if (blocks.n[SWEEP_LARGE] < 1024 || 8 * threads(SWEEP_SMALL) <= 7 * threads(SWEEP_LARGE)) shape = SWEEP_SMALL;
+  const bool rows = recon == GRMHD_RECON_WENO5 && !mixed && blocks.n[SWEEP_NARROW] >= 1024;
+  if (6 * threads(SWEEP_NARROW) <= (rows ? 5 : 4) * threads(shape)) shape = SWEEP_NARROW;
+  return shape;
 }
-inline void sweep_shape(Dims& d, int recon, bool mixed, bool small) {
-  d.sbx = small ? SMALL_BX : large_bx(recon, mixed);
-  d.sby = small ? SMALL_BY : large_by(recon, mixed);
+inline void set_sweep_shape(Dims& d, int shape, int recon, bool mixed) {
+  d.shape = shape;
+  d.sbx = sweep_bx(shape, recon, mixed);
+  d.sby = sweep_by(shape, recon, mixed);
 }
 struct SweepTile {
   int i0, j0, k;   // first cell of the tile and its plane

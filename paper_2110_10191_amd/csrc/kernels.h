@@ -75,7 +75,8 @@ struct BatchView {
   const JobDesc* jobs;
   const int* offs;
   int njobs;
-  int sbx, sby, utx, uty;  // block shapes shared by every job of the batch
+  int shape;               // block shape of the face-flux pass (sweep_shape)
+  int utx, uty;            // update and fixup tile; both shared by every job of the batch
   int axi;                 // every job's coordinates have g_23 = beta^3 = 0 (none is Cartesian Kerr-Schild)
 };
 

@@ -267,9 +267,9 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
   const int ib = t.i0 - SH::LX, jb = t.j0 - SH::LY;
   // the cells this thread writes: an x1 face needs the previous thread of the row, a divergence
   // the next one and the next row, an EMF the previous ones
-  const bool col = li > 0 && li < BX - 1;
-  const bool wd = col && i >= 0 && i < d.n1 && j >= 0 && j < d.n2 && lj < BY - 1;
-  const bool we = col && ok && i >= 0 && j >= 0 && lj > 0;
+  const bool wd = li > 0 && li < BX - 1 && i >= 0 && i < d.n1 && j >= 0 && j < d.n2 && lj < BY - 1;
+  const int last = BX - 2 + (t.i0 + BX - 1 == d.n1);  // cell n may be the last column
+  const bool we = li > 0 && li <= last && ok && i >= 0 && j >= 0 && lj > 0;
   const bool axis = (a.polar_lo && j == 0) || (a.polar_hi && j == d.n2);
   const bool in1 = i >= 0 && i < d.n1, in2 = j >= 0 && j < d.n2;
   // threads beyond the grid, and on faces no one asks for, compute on the nearest cell's data
@@ -384,8 +384,14 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
   if (CTOP) block_max3_to(c1, c2, c3, ctop);
 }
 
+// At least four waves a SIMD in FP64, six in FP32 (three blocks a CU, as the LDS
+// has it) and no more: left to aim at eight, the scheduler waits for each load of
+// an x3 stencil before the next, 0.47 -> 0.52 ms on the benchmark torus with WENO5.
+#define SWEEP_BOUNDS \
+  __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 6, sizeof(T) == 8 ? 8 : 6)))
+
 template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
-__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_kernel(Dims d, SweepArgs<T> a,
+__global__ SWEEP_BOUNDS void sweep_kernel(Dims d, SweepArgs<T> a,
                                                                           unsigned long long* ctop) {
   sweep_body<RECON, T, GEO, CTOP, BX, BY>(d, a, (int)blockIdx.x, ctop);
 }
@@ -454,7 +460,7 @@ struct FaceTables<float> {
 
 // every job of a batch in one grid; predictor sweeps P, corrector sweeps P_h
 template <int RECON, typename T, int GEO, bool CTOP, int BX, int BY>
-__global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void sweep_batch_kernel(BatchView bv, int corrector) {
+__global__ SWEEP_BOUNDS void sweep_batch_kernel(BatchView bv, int corrector) {
   const int* offs = bv.offs + PH_SWEEP * (bv.njobs + 1);
   const int jb = batch_job(offs, bv.njobs, (int)blockIdx.x);
   const JobDesc& J = bv.jobs[jb];
@@ -487,18 +493,23 @@ hipError_t allow_lds(size_t bytes) {
   return e;
 }
 
-// f(std::integral_constant BX, BY) for the block shape in d
-template <int RECON, typename T, typename F>
-hipError_t with_shape(const Dims& d, F f) {
+// f(std::integral_constant BX, BY) for a block shape
+template <int RECON, typename T, int SHAPE, typename F>
+hipError_t with_extents(F f) {
   constexpr bool MIXED = std::is_same<T, float>::value;
-  if (d.sbx == SMALL_BX && d.sby == SMALL_BY)
-    return f(std::integral_constant<int, SMALL_BX>(), std::integral_constant<int, SMALL_BY>());
-  return f(std::integral_constant<int, large_bx(RECON, MIXED)>(), std::integral_constant<int, large_by(RECON, MIXED)>());
+  return f(std::integral_constant<int, sweep_bx(SHAPE, RECON, MIXED)>(),
+           std::integral_constant<int, sweep_by(SHAPE, RECON, MIXED)>());
+}
+template <int RECON, typename T, typename F>
+hipError_t with_shape(int shape, F f) {
+  if (shape == SWEEP_NARROW) return with_extents<RECON, T, SWEEP_NARROW>(f);
+  if (shape == SWEEP_SMALL) return with_extents<RECON, T, SWEEP_SMALL>(f);
+  return with_extents<RECON, T, SWEEP_LARGE>(f);
 }
 
 template <int RECON, typename T, int GEO, bool CTOP>
 hipError_t launch_ctop(const Dims& d, const SweepArgs<T>& a, unsigned long long* ctop, hipStream_t s) {
-  return with_shape<RECON, T>(d, [&](auto bx, auto by) {
+  return with_shape<RECON, T>(d.shape, [&](auto bx, auto by) {
     constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
     constexpr size_t lds = tile_bytes<RECON, T, BX, BY>();
     const hipError_t e = allow_lds<sweep_kernel<RECON, T, GEO, CTOP, BX, BY>>(lds);
@@ -511,7 +522,7 @@ hipError_t launch_ctop(const Dims& d, const SweepArgs<T>& a, unsigned long long*
 
 template <int RECON, typename T, int GEO>
 hipError_t launch_speeds(const Dims& d, const SweepArgs<T>& a, unsigned long long* ctop, hipStream_t s) {
-  return with_shape<RECON, T>(d, [&](auto bx, auto by) {
+  return with_shape<RECON, T>(d.shape, [&](auto bx, auto by) {
     constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
     constexpr size_t lds = (size_t)NV * (PlaneShape<RECON, BX, BY>::PLANE + BX) * sizeof(T);
     const hipError_t e = allow_lds<speed_kernel<RECON, T, GEO, BX, BY>>(lds);
@@ -548,8 +559,8 @@ hipError_t launch_for(const grmhd_problem& p, const Dims& d, const Tables& t, co
 // a batch whose jobs all have g_23 = beta^3 = 0 reads the shorter tables (the
 // same bits: the components left out are zeros)
 template <int RECON, typename T, int GEO, bool CTOP>
-hipError_t launch_batch_ctop(const BatchView& bv, const Dims& d, dim3 grd, int c, hipStream_t s) {
-  return with_shape<RECON, T>(d, [&](auto bx, auto by) {
+hipError_t launch_batch_ctop(const BatchView& bv, dim3 grd, int c, hipStream_t s) {
+  return with_shape<RECON, T>(bv.shape, [&](auto bx, auto by) {
     constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
     constexpr size_t lds = tile_bytes<RECON, T, BX, BY>();
     const hipError_t e = allow_lds<sweep_batch_kernel<RECON, T, GEO, CTOP, BX, BY>>(lds);
@@ -561,14 +572,11 @@ hipError_t launch_batch_ctop(const BatchView& bv, const Dims& d, dim3 grd, int c
 
 template <int RECON, typename T>
 hipError_t launch_batch_for(const BatchView& bv, dim3 grd, int c, bool ctop, hipStream_t s) {
-  Dims d{};
-  d.sbx = bv.sbx;
-  d.sby = bv.sby;
   if (bv.axi)
-    return ctop ? launch_batch_ctop<RECON, T, GEO_AXI, true>(bv, d, grd, c, s)
-                : launch_batch_ctop<RECON, T, GEO_AXI, false>(bv, d, grd, c, s);
-  return ctop ? launch_batch_ctop<RECON, T, GEO_TABLE, true>(bv, d, grd, c, s)
-              : launch_batch_ctop<RECON, T, GEO_TABLE, false>(bv, d, grd, c, s);
+    return ctop ? launch_batch_ctop<RECON, T, GEO_AXI, true>(bv, grd, c, s)
+                : launch_batch_ctop<RECON, T, GEO_AXI, false>(bv, grd, c, s);
+  return ctop ? launch_batch_ctop<RECON, T, GEO_TABLE, true>(bv, grd, c, s)
+              : launch_batch_ctop<RECON, T, GEO_TABLE, false>(bv, grd, c, s);
 }
 
 }  // namespace
