@@ -189,6 +189,12 @@ __device__ inline float rcp_full(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
+// and 1/0 = inf, 1/inf = 0, where the correction would make a NaN of them
+__device__ inline double rcp_ends(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return e == e ? fma(r, fma(e, e, e), r) : r;
+}
 // x >= 0; 0 below the smallest argument the estimate is taken at
 __device__ inline double sqrt_full(double x) {
   const double y = __builtin_amdgcn_rsq(fmax(x, 1e-290));

@@ -39,7 +39,7 @@ constexpr double V2MAX = 1.0 - 1e-12;
 
 // guess_l2: Gamma^2 of the guess. Divisions and square roots by rcp_full and
 // rsqrt_full (an IEEE division is some ten instructions, and an iteration had
-// three and a square root), but for the Newton step, whose divisor may be 0.
+// three and a square root).
 template <bool AXI>
 __device__ bool invert_1dw(const double* U, const double* guess, double guess_l2, const ZoneGeo& g,
                            const UpdateParams& up, double* P) {
@@ -82,7 +82,7 @@ __device__ bool invert_1dw(const double* U, const double* guess, double guess_l2
     if (v2raw > V2MAX || v2raw < 0.0) dv2 = 0.0;
     const double dp = gf * (g2 + (0.5 * D * is - W) * dv2);
     const double df = 1.0 - dp + 0.5 * bsq * dv2 + qdb2 * (iW2 * iW);
-    const double dx = -f / df;  // IEEE: a derivative of 0 gives -inf, which halves W below
+    const double dx = -f * rcp_ends(df);  // a derivative of 0 gives -inf, which halves W below
     double xn = x + dx;
     if (xn + D <= 0.0) xn = 0.5 * W - D;
     x = xn;
