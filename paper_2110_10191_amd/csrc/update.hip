@@ -99,9 +99,9 @@ __device__ bool invert_1dw(const double* U, const double* guess, double guess_l2
   bool failed = (extra < 0) || !(W > 0.0) || !(v2 < V2MAX) || !isfinite(v2) || !isfinite(W);
   const double v2c = fmin(fmax(v2, 0.0), V2MAX);
   const double g2 = 1.0 - v2c;
-  const double lor = rsqrt_full(g2), s = g2 * lor;
+  const double lor = rsqrt_full(g2), s = sqrt_by(g2, lor);
   P[0] = D * s;
-  P[1] = (x * g2 - D * s * v2c * rcp_full(1.0 + s)) * up.igam;
+  P[1] = div_by(x * g2 - D * s * v2c * rcp_full(1.0 + s), up.gam, up.igam);
   const double fac = lor * (W * rwb), qw = qdb * (bw * rwb);
   P[2] = fac * (qt1 + qw * B1);
   P[3] = fac * (qt2 + qw * B2);
