@@ -478,18 +478,18 @@ constexpr size_t tile_bytes() {
   return ((size_t)NV * PlaneShape<RECON, BX, BY>::PLANE + (size_t)NEXCH * BX * BY) * sizeof(T);
 }
 
-// A kernel may use more dynamic LDS than the default 64 KiB only once the
-// limit is raised for it; the largest limit set so far is kept per kernel.
+// A kernel may use more dynamic LDS than the default 64 KiB only once the limit
+// is raised for it, on each device: the default FP64 MC pass takes 75 KB.
 template <auto KERNEL>
 hipError_t allow_lds(size_t bytes) {
-  static std::atomic<size_t> allowed{65536};
-  if (bytes <= allowed.load()) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) {
-    size_t cur = allowed.load();
-    while (cur < bytes && !allowed.compare_exchange_weak(cur, bytes)) {
-    }
-  }
+  constexpr int DEVICES = 64;
+  static std::atomic<bool> raised[DEVICES];
+  if (bytes <= 65536) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess || (dev < DEVICES && raised[dev].load())) return e;
+  e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess && dev < DEVICES) raised[dev].store(true);
   return e;
 }
 
