@@ -171,7 +171,7 @@ struct ElectronPass {
 // flags: the failure flags the update writes (the context's own when null);
 // fix: run the fixup (with the context's flags and no halo sides) as well.
 // extra_reset: further counters to clear first (8: the step's totals);
-// dtr: first set the device step size from the previous step's counters.
+// dtr: first set the device step size (DtRule); the ghost fill does it, so only with fill.
 int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool want_ctop,
             const double* dt_dev = nullptr, double dt_scale = 1.0, bool fill = true,
             const ElectronPass* el = nullptr, int8_t* flags = nullptr, bool fix = true, int extra_reset = 0,
@@ -186,7 +186,6 @@ int substep(grmhd_ctx* c, double* Ps, double* Pb, double* Pout, double dt, bool 
     HIP_OR_FAIL(c, launch_fill_ghosts(c->p, c->d, c->t, Ps, Pb, s, c->ctr, reset_mask, dtr ? *dtr : DtRule{}),
                 "ghost fill");
   } else {
-    if (dtr) HIP_OR_FAIL(c, launch_ctx_dt(c->ctr, dtr->cfl, dtr->dx[0], dtr->dx[1], dtr->dx[2], nullptr, s), "dt");
     HIP_OR_FAIL(c, launch_reset(c->ctr, reset_mask, s), "reset");
   }
   if (el) {
@@ -392,9 +391,6 @@ int grmhd_init(const grmhd_problem* p, void* hip_stream, grmhd_ctx** out) {
   c->dx[1] = (p->x2max - p->x2min) / p->n2;
   c->dx[2] = (p->x3max - p->x3min) / p->n3;
   c->up.gam = p->gam;
-  c->up.sigma_max = p->sigma_max;
-  c->up.beta_min = p->beta_min;
-  c->up.uorho_max = p->uorho_max;
   c->up.gamma_max = p->gamma_max;
   c->up.dx1 = c->dx[0];
   c->up.dx2 = c->dx[1];

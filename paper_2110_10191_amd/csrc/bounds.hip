@@ -344,10 +344,8 @@ __global__ void dt_ctx_kernel(Counters* ctr, double cfl, double dx1, double dx2,
   if (threadIdx.x != 0) return;
   const double dx[3] = {dx1, dx2, dx3};
   if (cfl > 0.0) device_dt(ctr->ctop, ctr->bad, dx, cfl, &ctr->dt, &ctr->status);
-  if (host) {
-    *host = *ctr;
-    ctr->divb = 0ull;  // for the next div B call
-  }
+  *host = *ctr;
+  ctr->divb = 0ull;  // for the next div B call
 }
 
 __global__ void dt_batch_kernel(BatchView bv) {

@@ -34,8 +34,7 @@ struct Counters {
 
 // physical constants the update kernels need
 struct UpdateParams {
-  double gam;
-  double sigma_max, beta_min, uorho_max, gamma_max;
+  double gam, gamma_max;
   double dx1, dx2, dx3;
   double idx1, idx2, idx3;  // 1 / dx_d
   double igam, gf;                 // 1 / gam, (gam - 1) / gam
@@ -160,8 +159,8 @@ hipError_t launch_update(bool mixed, const Dims& d, const Tables& t, const Updat
                          const double* dt_dev, double dt_scale, Counters* ctr, hipStream_t s);
 
 // ctr->dt <- min(cfl / sum_d(ctop_d / dx_d), 1.3 ctr->dt) on the device (cfl > 0),
-// then, with host (pinned memory), the counters' values into *host, which the
-// host may read once the stream is synchronised, and the div B maximum to zero
+// then the counters' values into *host (pinned memory), which the host may read
+// once the stream is synchronised, and the div B maximum to zero
 hipError_t launch_ctx_dt(Counters* ctr, double cfl, double dx1, double dx2, double dx3, Counters* host, hipStream_t s);
 
 // halo: bit 2 d + side set where the ghost layer on that side of direction d
