@@ -1,11 +1,12 @@
 """Tile autotuner for the stencil kernels.
 
-The sweep kernels (face fluxes) and the update/fixup kernels each take a
-thread-block tile of tx zones along x1 by ty rows along x2 (one thread per
-zone; a launch covers x3 in XCD-contiguous chunks). The best tile depends on
-the grid's x1 extent (a tile wider than n1 idles lanes), on the reconstruction
-(stencil reach) and on the precision (register pressure), so the tuner times
-each candidate on the device and keeps the fastest per
+The update/fixup kernels take a thread-block tile of tx zones along x1 by ty
+rows along x2 (one thread per zone; a launch covers x3 in XCD-contiguous
+chunks). The face-flux kernel has three block shapes, which a tile names
+(SWEEP_SHAPES); its default leaves the choice to the library's own rule on the
+grid. The best one depends on the grid's x1 extent (a tile wider than n1 idles
+lanes), on the reconstruction (stencil reach) and on the precision (register
+pressure), so the tuner times each candidate on the device and keeps the fastest per
 
     (device, library build, reconstruction, precision, grid bucket)
 
@@ -31,10 +32,17 @@ import statistics
 from . import _binding as B
 
 # x1 tile widths and rows per block; waves per block = tx * ty / 64
-WIDTHS = (32, 64, 128, 256)
+WIDTHS = {"sweep": (16, 32, 64, 128, 256), "update": (32, 64, 128, 256)}
 ROWS = (1, 2, 4, 8, 16)
 MAX_THREADS = {"sweep": 512, "update": 256}   # the kernels' launch bounds
 DEFAULT = {"sweep": (64, 8), "update": (64, 1)}
+# a tile for each thing a sweep tile can ask for: the grid's own choice, and the
+# 512-thread, the 32 x 8 and the 16 x 8 shape
+SWEEP_SHAPES = ((64, 8), (128, 4), (32, 8), (16, 8))
+# a named sweep shape has to be this much faster than the default, which on most
+# grids is the same kernel: a label won by noise would hold for every grid of the
+# bucket, and for a batch, whose rule looks at all its jobs
+SWEEP_MARGIN = 0.02
 
 SWEEP_CLASSES = ("sweeps",)
 UPDATE_CLASSES = ("update", "fixup")
@@ -46,7 +54,7 @@ def candidates(cls="update"):
     """Every legal tile of the candidate set for a kernel class: tx * ty a
     multiple of 64, at most the class's launch bound."""
     out = []
-    for tx in WIDTHS:
+    for tx in WIDTHS[cls]:
         for ty in ROWS:
             n = tx * ty
             if n % 64 == 0 and n <= MAX_THREADS[cls]:
@@ -139,15 +147,16 @@ class TileCache:
         os.replace(tmp, self.path)
 
 
-def pick(times):
+def pick(times, margin=0.0):
     """Fastest candidate of {tile: [per-repeat ms]} by median; ties keep the
-    earlier candidate (the candidate order puts the default first)."""
-    best, best_t = None, None
-    for tile, ts in times.items():
-        m = statistics.median(ts)
-        if best_t is None or m < best_t:
-            best, best_t = tile, m
-    return best, best_t
+    earlier candidate (the candidate order puts the default first), and the
+    first stays unless another is faster by more than ``margin`` of its time."""
+    med = {tile: statistics.median(ts) for tile, ts in times.items()}
+    best = min(med, key=med.get)
+    first = next(iter(med))
+    if med[best] >= (1.0 - margin) * med[first]:
+        best = first
+    return best, med[best]
 
 
 def _ordered(cls, default=None):
@@ -172,7 +181,7 @@ def time_classes(sim, P, dt, classes, steps, repeats):
 
 
 def tune_sim(sim, P, steps=3, repeats=3):
-    """Time every candidate tile for the sweep and the update classes, each
+    """Time every sweep shape and every candidate tile of the update class, each
     starting from state P (restored afterwards), and return
     ({"sweep": t, "update": t}, {"sweep": ms, "update": ms}). Leaves the best
     tiles set on ``sim``. Every candidate runs one untimed step first, and the
@@ -181,8 +190,8 @@ def tune_sim(sim, P, steps=3, repeats=3):
     P0 = P.clone()
     dt = sim.get_dt(P)
     result, timings = {}, {}
-    for cls, classes in (("sweep", SWEEP_CLASSES), ("update", UPDATE_CLASSES)):
-        order = _ordered(cls)
+    for cls, classes, order, margin in (("sweep", SWEEP_CLASSES, SWEEP_SHAPES, SWEEP_MARGIN),
+                                        ("update", UPDATE_CLASSES, _ordered("update"), 0.0)):
         times = {tile: [] for tile in order}
         for tile in order:
             sim.set_tiles(cls, *tile)
@@ -193,7 +202,7 @@ def tune_sim(sim, P, steps=3, repeats=3):
                 sim.set_tiles(cls, *tile)
                 P.copy_(P0)
                 times[tile] += time_classes(sim, P, dt, classes, steps, 1)
-        best, best_ms = pick(times)
+        best, best_ms = pick(times, margin)
         sim.set_tiles(cls, *best)
         result[cls] = best
         timings[cls] = best_ms
@@ -202,23 +211,25 @@ def tune_sim(sim, P, steps=3, repeats=3):
     return result, timings
 
 
-def search(measure, repeats=3):
+def search(measure, repeats=3, sweep=None, margin=0.0):
     """Coordinate search over the two tile classes with a caller's timer.
 
     measure(tiles) -> seconds (or ms) of some fixed work run with
     tiles = {"sweep": (tx, ty), "update": (tx, ty)}. The sweep tile is chosen
     with the update tile at its default, then the update tile with the chosen
-    sweep tile. Returns (tiles, {cls: best median})."""
+    sweep tile. sweep: the sweep tiles to try, the default first (every
+    candidate when not given); margin: see pick, for the sweep tile. Returns
+    (tiles, {cls: best median})."""
     tiles = dict(DEFAULT)
     best_t = {}
     for cls in ("sweep", "update"):
-        order = _ordered(cls)
+        order = sweep if cls == "sweep" and sweep else _ordered(cls)
         times = {tile: [] for tile in order}
         # the repeats go round all candidates in turn (no drift favours the first)
         for _ in range(repeats):
             for tile in order:
                 times[tile].append(measure(dict(tiles, **{cls: tile})))
-        tiles[cls], best_t[cls] = pick(times)
+        tiles[cls], best_t[cls] = pick(times, margin if cls == "sweep" else 0.0)
     return tiles, best_t
 
 
@@ -246,7 +257,7 @@ def tune_batch(sims, states, steps=3, repeats=3, stream=None):
         finally:
             b.close()
 
-    tiles, best = search(measure, repeats=repeats)
+    tiles, best = search(measure, repeats=repeats, sweep=SWEEP_SHAPES, margin=SWEEP_MARGIN)
     sims[0].set_tiles("sweep", *tiles["sweep"])
     sims[0].set_tiles("update", *tiles["update"])
     return tiles, best
