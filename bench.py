@@ -23,16 +23,16 @@ algorithmic bytes per launch over its mean duration against 8 TB/s, where the
 algorithmic bytes are the method's compulsory bytes (the P^n, P_h, P^n+1
 state traffic of a step plus the 2D geometry, 338.75 B per zone-cycle on the
 benchmark torus) for the zone-cycles one launch advances; this design's own
-byte model (face fluxes included) is a separate view. The line also carries a
+byte model (what passes between the two kernels included) is a separate view. The line also carries a
 few steps of the 64-job batched workload against the per-job FP64 loop
 (``many``), the serving loop's p50 / p99 job latency on a short Poisson stream
 of uneven jobs (``serving``), and the oracle (NumPy FP64, one core) timed on a
 bounded sample of the same torus.
 
 ``--coords cks`` times another workload instead: a magnetised Michel flow on a
-168^3 Cartesian Kerr-Schild box, whose geometry tables are 3D (every zone
-reads its own connection: 992 B per zone-cycle compulsory in FP64, where
-the metric is evaluated in closed form).
+168^3 Cartesian Kerr-Schild box, whose metric depends on x3; it is evaluated
+in closed form, and a zone reads only its two floor scales (352 B per
+zone-cycle in FP64; the FP32 face-flux pass reads 3D face tables as well).
 
 Prints one JSON line on stdout.
 """
@@ -60,12 +60,10 @@ def compulsory_bytes_per_zone_cycle(prm):
     P^{n+1} (corrector), 5 x 64 = 320 B a zone; plus, on a Kerr grid, the
     axisymmetric geometry, about 150 doubles per (x1, x2) column per substep,
     shared by the n3 zones of the column. 338.75 B on the 288 x 128 x 128 torus.
-    Cartesian Kerr-Schild geometry depends on x3, so every zone reads its own
-    connection (40 values, by centred differences) and floor scales (2) each
-    substep; the metric, its inverse, sqrt(-g) and the lapse have closed
-    forms that the kernels evaluate instead of reading (the update at the
-    centre; the FP64 face-flux pass at the faces, while the mixed-precision
-    one reads the float face tables, 3 x 22 values)."""
+    Cartesian Kerr-Schild geometry depends on x3: here every zone reads its own
+    connection (40 values) and floor scales (2) each substep, in mixed
+    precision 3 x 22 face values too, the bytes of a method that stores its
+    connection. The kernels evaluate it (step_bytes_per_zone_cycle)."""
     if prm["coords"] == CKS:
         faces = 3 * 22 * 4 if prm["precision"] == 1 else 0
         return 320.0 + 2 * (42 * 8 + faces)
@@ -73,12 +71,47 @@ def compulsory_bytes_per_zone_cycle(prm):
     return 320.0 + geo
 
 
+def step_bytes_per_zone_cycle(prm):
+    """compulsory_bytes_per_zone_cycle of the coordinates as the kernels have
+    them: in Cartesian Kerr-Schild the metric and its differences are evaluated
+    and a substep reads the two floor scales of a zone, in mixed precision the
+    three float face tables (14 values) as well."""
+    if prm["coords"] != CKS:
+        return compulsory_bytes_per_zone_cycle(prm)
+    faces = 3 * 14 * 4 if prm["precision"] == 1 else 0
+    return 320.0 + 2 * (2 * 8 + faces)
+
+
+def design_bytes(kernel, prm, mixed):
+    """Bytes one launch of the two-kernel design moves at minimum: every value
+    it reads once and every value it writes once (stencil re-reads are cache
+    traffic), including the 15 values a zone that pass between the kernels, five
+    of them float64 in either precision. A view of the design, not of the
+    method: the method's compulsory bytes are compulsory_bytes_per_zone_cycle."""
+    n1, n2, n3 = prm["n1"], prm["n2"], prm["n3"]
+    zones, points = n1 * n2 * n3, n1 * n2
+    fb = 4 if mixed else 8
+    between = 5 * 8 + 10 * fb     # divergence; x3 fluxes, EMFs and the fluxes of B3 that complete them
+    if kernel == "sweeps":
+        reach = 3 if prm["recon"] == 1 else 2          # zones below / above+1 a face
+        cells = (n1 + 2 * reach) * (n2 + 2 * reach) * (n3 + 2 * reach)
+        if prm["coords"] == CKS:
+            geo = 3 * 14 * fb * zones if mixed else 0
+        else:
+            geo = 3 * 12 * fb * points
+        return 64 * cells + between * zones + geo
+    if kernel == "update":
+        # the states read: one in the predictor (P_base = P_s = P), two in the
+        # corrector (P, P_h), 96 B a zone on average over the two launches of a
+        # step; P_out written; one flag byte; the centre table once
+        geo = 2 * 8 * zones if prm["coords"] == CKS else 38 * 8 * points
+        return zones * (between + 96 + 64 + 1) + geo
+    raise KeyError(kernel)
+
+
 def split_design_bytes(kernel, prm, mixed):
-    """Bytes one launch of this split design moves at minimum: every value it
-    reads once and every value it writes once (stencil re-reads are cache
-    traffic), including the face fluxes the sweeps write and the update reads
-    back. A view of the design, not of the method: the method's compulsory
-    bytes are compulsory_bytes_per_zone_cycle."""
+    """The same of a design that passes the three face-flux arrays between the
+    kernels, seven components a face, for comparison with design_bytes."""
     n1, n2, n3 = prm["n1"], prm["n2"], prm["n3"]
     fb = 4 if mixed else 8
     recon_reach = 3 if prm["recon"] == 1 else 2          # zones below / above+1 a face
@@ -503,7 +536,7 @@ def main():
     dom = max(("sweeps", "update"), key=lambda k: kernels[k][0])
     ms, n = kernels[dom]
     t_launch = ms / n / 1e3
-    per_zc = compulsory_bytes_per_zone_cycle(prm)
+    per_zc = step_bytes_per_zone_cycle(prm)
     per_launch = per_zc * zones / 2
     achieved = per_launch / t_launch
     workload = f"{'cks_bondi' if cks else 'fm_torus'}_{n1}x{n2}x{n3}_{args.recon}_{args.precision}"
@@ -517,7 +550,7 @@ def main():
                 "kernel": dom, "mean_launch_ms": ms / n,
                 "algorithmic_bytes_per_launch": per_launch,
                 "algorithmic_basis": (f"{per_zc:.2f} B per zone-cycle (P^n, P_h, P^n+1 traffic of the two substeps "
-                                      + ("plus the 3D geometry tables of every zone" if cks else
+                                      + ("plus the 3D tables of every zone that the kernels read" if cks else
                                          "plus the 2D geometry over n3")
                                       + f") x {zones} zones / 2 (one substep)")}
     if traffic:
@@ -538,17 +571,18 @@ def main():
         del a, b
 
     # other views: the whole step's compulsory bytes at the measured step
-    # rate; this split design's own per-launch byte model (face fluxes
-    # included); measured bytes over time; against the nominal peak and a
-    # plain device copy measured here
+    # rate; this design's own per-launch byte model, and that of one that keeps
+    # the three face-flux arrays; measured bytes over time; against the nominal
+    # peak and a plain device copy measured here
     copy_bw = device_copy_bandwidth(torch, dev)
-    split = split_design_bytes(dom, prm, mixed)
+    design = design_bytes(dom, prm, mixed)
     views = {"copy_GBps": copy_bw / 1e9,
              "step_compulsory_bytes_per_zone_cycle": per_zc,
              "step_compulsory_frac": value * per_zc / HBM_PEAK,
              "step_compulsory_frac_of_copy": value * per_zc / copy_bw,
-             "split_design_bytes_per_launch": split,
-             "split_design_frac": split / t_launch / HBM_PEAK}
+             "design_bytes_per_launch": design,
+             "design_frac": design / t_launch / HBM_PEAK,
+             "three_flux_arrays_bytes_per_launch": split_design_bytes(dom, prm, mixed)}
     if roofline["traffic"]:
         views["measured_frac"] = roofline["traffic"] / t_launch / HBM_PEAK
         views["measured_frac_of_copy"] = roofline["traffic"] / t_launch / copy_bw
@@ -571,13 +605,14 @@ def main():
     roofline["views"] = views
 
     if args.electrons:
-        # the electron passes of a step (scalar ghosts, advection, heating, two
-        # substeps each) against their own compulsory bytes: advection reads
-        # rho and u~ of the base state, both entropies of the base and the flux
-        # state and the three mass fluxes and writes U_K; heating reads the
-        # new primitives and U_K and writes both entropies
+        # the electron launches of a step (scalar ghosts, then advection and heating
+        # in one pass, two substeps each) against their own compulsory bytes: both
+        # passes read the three mass fluxes and the new primitives and write both
+        # entropies; the predictor reads rho and u~ of the base state and its
+        # entropies, which are the flux state's too, and leaves sqrt(-g) rho u^t,
+        # which the corrector reads with both states' entropies
         fb = 4 if mixed else 8
-        per_zone = 2 * ((4 + 2 + 2 + 2) * 8 + 3 * fb + (8 + 2 + 2) * 8)
+        per_zone = 2 * (3 * fb + (8 + 2) * 8) + (4 + 2 + 1) * 8 + (1 + 2 + 2) * 8
         # the electron classes are timed in the pass after the timed region
         e_ms = kernels["electrons"][0] / other_steps
         roofline["electron_passes"] = {"ms_per_step": e_ms, "algorithmic_bytes_per_zone_cycle": per_zone,

@@ -111,8 +111,8 @@ typedef struct grmhd_problem {
 typedef struct grmhd_ctx grmhd_ctx;
 
 /* Validate the problem, build the geometry tables on the device (metric,
- * inverse, sqrt(-g), lapse at zone centres and faces; connection at centres by
- * centred differences) and allocate scratch. hip_stream: a hipStream_t, or NULL
+ * inverse, sqrt(-g), lapse at zone centres and faces; derivatives of the metric at
+ * centres by centred differences) and allocate scratch. hip_stream: a hipStream_t, or NULL
  * for the null stream. Errors: EINVAL (bad problem), ENOMEM, EDEVICE. */
 GRMHD_API int grmhd_init(const grmhd_problem *p, void *hip_stream, grmhd_ctx **out);
 

@@ -2,13 +2,13 @@
 //
 // Layout (see grmhd.h): a state is [8][n3+6][n2+6][n1p] float64, x1 fastest.
 // The results of the face-flux pass (FluxOut) use the same cells, a quantity
-// of a lower face or edge at the cell it belongs to. Geometry tables hold centre quantities
-// (metric, inverse, sqrt(-g), lapse, connection, floor scales) and face
-// quantities (metric, inverse, sqrt(-g), lapse) per direction. Axisymmetric
-// coordinates store them as 2D tables [component][n2+6][n1p] (k stride 0),
-// and the x3 faces share the centre geometry; Cartesian Kerr-Schild, whose
-// metric depends on x3, stores 3D tables [component][n3+6][n2+6][n1p] (k
-// stride = the state's) with an x3-face table of its own.
+// of a lower face or edge at the cell it belongs to. Geometry tables hold the
+// metric in 3+1 form, at the centres with the inverse of the spatial metric, the
+// derivatives the source needs and the floor scales, and per direction at the
+// faces. Axisymmetric coordinates store them as 2D tables [pair][n2+6][n1p][2]
+// (k stride 0); Cartesian Kerr-Schild, whose metric depends on x3, has 3D tables
+// [pair][n3+6][n2+6][n1p][2] (k stride = the state's), at the centres of the floor
+// scales alone. The x3-face table of 2D tables holds centre values.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -37,7 +37,7 @@ enum {
   C_G11 = 0, C_G12, C_G13, C_G22, C_G33, C_ALPHA, C_B1, C_B2, C_IALPHA, C_GDET,
   C_S1 = 10, C_S2 = 19, C_H11 = 28, C_H12, C_H13, C_H22, C_H23, C_H33, C_IGDET, C_RHOFL, C_UFL,
   K_RHOFL = 0, K_UFL, K_GDET,
-  N_CENT = 64  // components the centre table has room for
+  N_CENT = 64  // components the centre table has room for (38 or 3 are used; the allocation is part of the interface)
 };
 // the (k, m) of the eight derivatives of an axisymmetric table
 constexpr int AXI_KM[8][2] = {{0, 0}, {0, 1}, {0, 3}, {1, 1}, {1, 2}, {1, 3}, {2, 2}, {3, 3}};
@@ -52,7 +52,7 @@ enum {
   F_G11 = 0, F_G12, F_G13, F_G22, F_G33, F_ALPHA,
   F_B1, F_B2, F_IALPHA, F_H, F_HGDET,  // 1/alpha, H, sqrt(-g)/2
   F_B3, F_AXI = F_B3 + 1, F_G23 = F_AXI, F_USED = F_G23 + 2,  // a pair is read at a time
-  N_FACE = 22  // components a face table has room for
+  N_FACE = 22  // components a face table has room for (12 or 14 are used)
 };
 
 __host__ __device__ constexpr int sidx(int m, int n) {
@@ -195,6 +195,7 @@ __device__ inline double rcp_ends(double x) {
   const double e = fma(-x, r, 1.0);
   return e == e ? fma(r, fma(e, e, e), r) : r;
 }
+// A Goldschmidt step from the estimate, then one correction in the residual.
 // x >= 0; 0 below the smallest argument the estimate is taken at
 __device__ inline double sqrt_full(double x) {
   const double y = __builtin_amdgcn_rsq(fmax(x, 1e-290));

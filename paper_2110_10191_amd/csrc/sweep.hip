@@ -22,15 +22,15 @@
 // or below (the x3 fluxes, the x1 and x2 flux of B3) goes out as it is.
 //
 // What bounds it: FP64 issue and the latency of its loads, about half each (a
-// wave issues 1270 VALU instructions, 1410 with the Courant maxima, 480 of them the
+// wave issues 1260 VALU instructions, 1410 with the Courant maxima, 480 of them the
 // MC slopes). It runs
 // at four waves a SIMD, so a face may hold 128 registers: sums and speeds wait
 // in LDS, and FACE_FENCE keeps the three faces apart. On the 288 x 128 x 128
-// torus in FP64 with MC slopes it takes 0.403 ms. Writing the three flux arrays
-// it took 0.451 where this form took 0.410, and the update, which then read 66 of
-// their values a cell and now reads 35, 0.605 against 0.470 (0.363 with its later
-// changes; mixed-precision WENO5: the pass 0.50 -> 0.55, now 0.47, the update
-// 0.57 -> 0.42, now 0.31). The tiles are walked x2 first, so a block finds the
+// torus in FP64 with MC slopes it takes 0.401 ms, 0.415 with the maxima. Writing
+// the three flux arrays it took 0.451 where this form took 0.410, and the update,
+// which then read 66 of their values a cell and now reads 35, 0.605 against 0.470
+// (0.361 with its later changes; mixed-precision WENO5: the pass 0.50 -> 0.55, now
+// 0.48, the update 0.57 -> 0.42, now 0.31). The tiles are walked x2 first, so a block finds the
 // rows it shares with the tile before in the XCD's L2 (0.94 -> 0.61 GB read).
 // A block that walks along 4 to 32 planes with running sums writes 8 values a
 // cell instead of 15, but its registers leave three waves a SIMD and its
@@ -42,7 +42,7 @@
 // lane finds both edges of its own zone, which share the smoothness indicators
 // (MC: the slope), and passes the right one on, in x2 a row does (row_sides);
 // with the indicators in differences and one corrected reciprocal per division
-// the pass takes 0.47 ms on the benchmark torus in mixed precision (0.55 with
+// the pass takes 0.48 ms on the benchmark torus in mixed precision (0.55 with
 // the plain formula at every face) and 88 us on 131 x 67 x 45 in FP64 (117).
 //
 // The per-direction maximum of ctop over the faces with interior transverse
@@ -282,7 +282,7 @@ __device__ void sweep_body(const Dims& d, const SweepArgs<T>& a, int b, unsigned
   const size_t sv = (size_t)d.sv;
   stage_plane<SH>(d, a.P, L, ib, jb, k, tid);
   // Cartesian Kerr-Schild: the other planes' values are on their way while the
-  // face's metric is evaluated (0.488 -> 0.461 ms on 168^3 zones; where the
+  // face's metric is evaluated (0.488 -> 0.466 ms on 168^3 zones; where the
   // metric is read, the registers cost more: 0.403 -> 0.406 on 288 x 128 x 128)
   constexpr bool AHEAD = RECON == GRMHD_RECON_MC && GEO == GEO_CKS;
   double z[AHEAD ? 3 * NV : 1];
@@ -398,7 +398,9 @@ __global__ SWEEP_BOUNDS void sweep_kernel(Dims d, SweepArgs<T> a,
 
 // The Courant maxima alone, of a state whose fluxes no one asks for: the same
 // tiles, faces and speeds, without flux, exchange or output (85 us on
-// 192 x 96 x 64 FP64 MC zones, 117 to 122 with the fluxes)
+// 192 x 96 x 64 FP64 MC zones, 117 to 122 with the fluxes). With WENO5 a row's
+// edges cost 28 to 65 spilled registers in FP64, up to 8 in FP32; grmhd_get_dt
+// takes 234 and 146 us there on that grid, 345 and 217 with the fluxes.
 template <int RECON, typename T, int GEO, int BX, int BY>
 __global__ __launch_bounds__(BX * BY, sizeof(T) == 8 ? 4 : 6) void speed_kernel(Dims d, SweepArgs<T> a,
                                                                           unsigned long long* ctop) {

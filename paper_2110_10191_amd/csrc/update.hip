@@ -3,7 +3,7 @@
 // pointwise prim->cons / cons->prim calls.
 //
 //   U* = U(P_base) + dt (-sum_d [F_d(+) - F_d(-)]/dx_d + S(P_s)),
-//   S_nu = sqrt(-g) T^k_l Gamma^l_{nu k}                       (energy, momenta)
+//   S_n = sqrt(-g) T^km d_n g_km / 2                                   (momenta)
 //   P_out = invert(U*; guess P_s), then the bounds, then the fixup.
 //
 // Flux-CT (Implementation Notes, after Toth 2000): the B fluxes through each
@@ -305,12 +305,13 @@ __device__ void update_body(const Dims& d, const double* __restrict__ cent, cons
   block_count_to(failed, &ctr->fail, &ctr->fail_total);
 }
 
-// Bound by HBM and by the loads in flight: 31 values a zone read (23 in the
-// predictor, whose base state is the flux state), 8 written, at 0.35 ms on the
-// 288 x 128 x 128 torus 4.5 TB/s of the 4.9 a device copy reaches. With the 4 x 4
-// metric, its inverse and the 40 connection coefficients read per zone (66
-// values against 38 in pairs) and IEEE divisions it took 0.47 ms (mixed
-// precision 0.29 against 0.42). (256, 3): at least three waves per SIMD. Held to
+// Bound by the address units (95 % busy: 71 loads a wave, 63 in the predictor,
+// whose base state is the flux state) and HBM: 0.382 ms, predictor 0.341, on the
+// 288 x 128 x 128 torus, 1.48 GB a launch of real traffic, 4.1 TB/s of the 4.9 a
+// device copy reaches. With the 4 x 4 metric, its inverse and the 40 connection
+// coefficients read per zone (66 values against 38 in pairs) and IEEE divisions
+// both took 0.47 ms in the mean where they then took 0.35 (mixed precision 0.42
+// against 0.29). (256, 3): at least three waves per SIMD. Held to
 // four, the FP64 kernel takes 108 registers, keeps fewer loads in flight and
 // 0.46 ms. Blocks that copy the tile's table to LDS and walk up 1 to 8 planes,
 // carrying the x3 fluxes and EMFs between them, load 38 values instead of 71
